@@ -1,15 +1,34 @@
-// float32 jagged HSTU attention (forward and backward) on the vector ALUs.
+// float32 jagged HSTU attention (forward and backward) on the fp32 matrix
+// cores of gfx950.
 //
-// Same definition as the bf16 MFMA kernels, all arithmetic in fp32.  One
-// work-group of 64 threads per (work-list entry, head); each thread owns one
-// row of the 64-row tile (a query for the forward and dQ, a key for dK/dV)
-// and walks its causal partners; every thread of a wave reads the same
-// partner row at the same time, so those loads are broadcasts.  Table
-// gradients are float atomics straight into the (zeroed) outputs, or, in the
-// deterministic mode, 64-bit fixed-point atomics into workspace tables that a
-// last pass converts (integer sums do not depend on order).  This path
-// serves the fp32 workload and precision checks; it is not the throughput
-// path.
+// Same definition as the bf16 kernels with every operand, product and sum in
+// fp32 (v_mfma_f32_32x32x2_f32; the two bias-table gradients are summed in
+// float64 or 64-bit fixed point).
+//
+// An item is a 32-row half of one 64-row work-list tile of one head: 32
+// queries for the forward and dQ, 32 keys for dK/dV.  The four waves of a
+// work-group take every fourth 32-row tile of the item's streamed side, each
+// on its own -- a wave stages its tile in its own part of the LDS, so the
+// loop has no barrier; each operand's loads are in flight under the product
+// before it, through one set of registers -- and their partial sums are added through LDS in wave order at
+// the end (the result does not depend on timing).
+//
+// What bounds it: a 32 x 32 tile is D/2 matrix instructions of 64 cycles for
+// every product, and a batch of short sequences is as long as its longest
+// item.  Hence 32-row items split over four waves (a 512-token sequence's
+// longest dK/dV item is 4 tiles deep in every wave), and the score-side
+// products read their streamed operand by rows out of LDS (16 bytes a lane)
+// while the accumulating products use the scores where the first product
+// left them: its accumulator register r holds streamed row c_row(r, g) of
+// this lane's stationary row, which is the B operand of a K = 2 step over
+// rows c_row(r, 0) and c_row(r, 1).
+// Measured against one thread per row on the vector ALUs (48 power-law
+// sequences of 16..512 tokens, H = 4, d = 64, both biases): forward 582 ->
+// 32 us, backward 7796 -> 107 us (6886 of them were one double atomic on a
+// table entry per pair), error against 64 bits 4.3e-7 -> 3.6e-7; four
+// sequences of up to 64 tokens, H = 2, d = 32: forward 27 -> 6.4 us.
+#include <algorithm>
+
 #include "internal.h"
 #include "device.h"
 
@@ -17,176 +36,599 @@ namespace hstu {
 
 namespace {
 
-constexpr int F32_THREADS = TILE;
+constexpr int F32_THREADS = 256;           // 4 waves
+constexpr int F32_WAVES = F32_THREADS / 64;
+constexpr int FT = 32;                     // rows of an item and of a streamed tile
+// A work-group's d_time histogram sits in LDS up to this many buckets (16
+// KB); above it every finished run goes straight to the table.
+constexpr int F32_LDS_BUCKETS = 2048;
 
 struct F32Params {
   const float *q, *k, *v, *dO;
   const float *pos_w, *time_w;
   const int64_t *ts;
   const int32_t *ctrl;
-  const SeqInfo *info;
-  const WorkEntry *list;
-  float *out0, *out1, *out2;
+  const WorkEntry *list_q, *list_k;
+  float *o, *dq, *dk, *dv;
   // table-gradient sums in the workspace: double (default mode; many
   // thousands of terms land on one entry, more than float keeps to 1e-5 of
   // the table) or 64-bit fixed point (deterministic mode)
-  double *acc_pos, *acc_time;
-  unsigned long long *fix_pos, *fix_time;
+  void *acc_pos, *acc_time;
   int32_t H, N, nb;
   float inv_n, alpha;
 };
 
-__device__ __forceinline__ float bias(const F32Params &P, int h, int64_t i,
-                                      int64_t j, int64_t ri, int64_t rj) {
-  float b = 0.0f;
-  if (P.pos_w) b += P.pos_w[(int64_t)h * (2 * (int64_t)P.N - 1) + (j - i + P.N - 1)];
-  if (P.time_w) b += P.time_w[(int64_t)h * P.nb + time_bucket(P.ts[ri] - P.ts[rj], P.nb)];
+// K = 2 step of a 32 x 32 product: lane l gives A[l % 32][l / 32] and
+// B[l / 32][l % 32]; the accumulator has the layout of mfma32's.
+__device__ __forceinline__ f32x16 mfma2(float a, float b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+// The thread index as a value the compiler cannot trace back: per-lane
+// addresses are rebuilt for each item instead of living across them.
+__device__ __forceinline__ int opaque_tid() {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  return tid;
+}
+
+template <int D> constexpr int F32_ROW = D + 4;       // LDS row: the 16 rows of a 16-byte
+                                                      // read phase fall on all 64 banks
+
+// The rows of one head of a sequence as a buffer source: rows at or past the
+// sequence's length read as zeros.  At most 65536 * 64 * 128 * 4 = 2^31 bytes.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_of(const F32Params &P, const float *p,
+                                                          const WorkEntry &e, int h, int D) {
+  const uint32_t row = 4u * (uint32_t)(P.H * D);
+  // up to the end of the last row's D floats, not of the whole last row
+  return make_rsrc(p + (e.start * P.H + h) * D, (uint32_t)(e.len - 1) * row + 4u * (uint32_t)D);
+}
+
+// Stationary rows of an item, one per lane: lane (l32, g) holds dims g D/2 ..
+// of row row0 + l32.
+template <int D>
+__device__ __forceinline__ void load_rows(const F32Params &P, __amdgpu_buffer_rsrc_t rs, int row,
+                                          int g, float (&reg)[D / 2]) {
+  const uint32_t at = 4u * (uint32_t)(P.H * D) * (uint32_t)row + 2u * (uint32_t)(g * D);
+#pragma unroll
+  for (int x = 0; x < D / 8; ++x) {
+    const float4 f = __builtin_bit_cast(float4, buf_load16(rs, at + 16u * x));
+    reg[4 * x] = f.x; reg[4 * x + 1] = f.y; reg[4 * x + 2] = f.z; reg[4 * x + 3] = f.w;
+  }
+}
+
+// A 32-row tile of one head on its way to LDS, 16-byte chunks of a wave.
+template <int D>
+struct F32Tile {
+  static constexpr int CH = FT * D / 4 / 64;
+  uint4 c[CH];
+  static constexpr int RPC = 64 / (D / 4);          // rows per chunk step
+  __device__ __forceinline__ void load(const F32Params &P, __amdgpu_buffer_rsrc_t rs, int row0,
+                                       int lane) {
+    const uint32_t row_bytes = 4u * (uint32_t)(P.H * D);
+    const uint32_t at = row_bytes * (uint32_t)(row0 + lane / (D / 4)) + 16u * (lane % (D / 4));
+#pragma unroll
+    for (int x = 0; x < CH; ++x) c[x] = buf_load16(rs, at + (uint32_t)(x * RPC) * row_bytes);
+  }
+  __device__ __forceinline__ void store(float *lds, int lane) const {
+#pragma unroll
+    for (int x = 0; x < CH; ++x) {
+      const int ch = lane + 64 * x, row = ch / (D / 4), col = ch % (D / 4);
+      *(uint4 *)(lds + row * F32_ROW<D> + 4 * col) = c[x];
+    }
+  }
+};
+
+// Product of the tile's rows in LDS (rows of the result) with the
+// stationary rows (columns): result register r of lane (l32, g) is tile row
+// c_row(r, g) times stationary row l32.
+template <int D>
+__device__ __forceinline__ f32x16 tile_scores(const float *lds, const float (&st)[D / 2], int l32,
+                                              int g) {
+  f32x16 s;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+  const float *p = lds + l32 * F32_ROW<D> + g * (D / 2);
+#pragma unroll
+  for (int x = 0; x < D / 8; ++x) {
+    const float4 f = *(const float4 *)(p + 4 * x);
+    s = mfma2(f.x, st[4 * x], s);
+    s = mfma2(f.y, st[4 * x + 1], s);
+    s = mfma2(f.z, st[4 * x + 2], s);
+    s = mfma2(f.w, st[4 * x + 3], s);
+  }
+  return s;
+}
+
+// Orders the wave's own LDS traffic across lanes (the hardware keeps a
+// wave's LDS operations in order; this keeps the compiler to it).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+// acc[db] += X^T P: X = the tile's rows in LDS, P the pair values in the
+// layout tile_scores leaves them in.  acc register r of lane (l32, g) is dim
+// 32 db + c_row(r, g) of stationary row l32.  On an `edge` tile some pairs do
+// not exist (their value is 0; `ok` bit r: pair (c_row(r, g), l32) does):
+// should X hold an infinity or NaN, which 0 would not cancel, those elements
+// are added for the existing pairs alone and leave the tile first.
+template <int D>
+__device__ __forceinline__ void tile_accumulate(float *lds, const float (&p)[16], bool edge,
+                                                uint32_t ok, int l32, int g,
+                                                f32x16 (&acc)[D / 32]) {
+  if (edge) {
+    bool bad = false;
+#pragma unroll 4
+    for (int x = l32 + 32 * g; x < FT * D; x += 64)
+      bad |= !(__builtin_fabsf(lds[(x / D) * F32_ROW<D> + x % D]) < __builtin_inff());
+    if (__any(bad)) {
+      auto odd = [](float f) { return !(__builtin_fabsf(f) < __builtin_inff()); };
+#pragma unroll 1
+      for (int row = 0; row < FT; ++row) {
+        const int src = l32 + 32 * ((row >> 2) & 1), reg = 4 * (row >> 3) + (row & 3);
+        float pv = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) pv = r == reg ? p[r] : pv;
+        pv = __shfl(pv, src, 64);
+        const bool have = (__shfl((int)ok, src, 64) >> reg) & 1;
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float f = lds[row * F32_ROW<D> + 32 * db + c_row(r, g)];
+            if (have && odd(f)) acc[db][r] = __builtin_fmaf(pv, f, acc[db][r]);
+          }
+      }
+      wave_lds_fence();
+      for (int x = l32 + 32 * g; x < FT * D; x += 64) {
+        float &f = lds[(x / D) * F32_ROW<D> + x % D];
+        if (odd(f)) f = 0.0f;
+      }
+      wave_lds_fence();
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+      acc[db] = mfma2(lds[c_row(r, g) * F32_ROW<D> + 32 * db + l32], p[r], acc[db]);
+}
+
+// Sum of the four waves' accumulators (each through its own LDS part, in
+// wave order) and the store of the item's rows (those below `valid`) times
+// `scale`.
+template <int D>
+__device__ __forceinline__ void sum_store(float *lds0, int part, const f32x16 (&acc)[D / 32],
+                                          int tid, float *out, int row_stride, int valid,
+                                          float scale) {
+  const int lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+  float *mine = lds0 + (tid >> 6) * part;
+  __syncthreads();
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *(float4 *)(mine + l32 * F32_ROW<D> + 32 * db + 8 * q + 4 * g) =
+          make_float4(acc[db][4 * q], acc[db][4 * q + 1], acc[db][4 * q + 2], acc[db][4 * q + 3]);
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < FT * D / 4 / F32_THREADS; ++x) {
+    const int ch = tid + F32_THREADS * x, row = ch / (D / 4), col = ch % (D / 4);
+    if (row >= valid) continue;
+    float4 s = *(const float4 *)(lds0 + row * F32_ROW<D> + 4 * col);
+#pragma unroll
+    for (int w = 1; w < F32_WAVES; ++w) {
+      const float4 t = *(const float4 *)(lds0 + w * part + row * F32_ROW<D> + 4 * col);
+      s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+    }
+    *(float4 *)(out + (int64_t)row * row_stride + 4 * col) =
+        make_float4(scale * s.x, scale * s.y, scale * s.z, scale * s.w);
+  }
+}
+
+// The bias sources of one head of one item.
+struct F32Bias {
+  __amdgpu_buffer_rsrc_t pos;          // the head's position table (0 outside it)
+  const float *time;
+  int64_t ts_own;                      // timestamp of this lane's stationary row
+};
+
+__device__ __forceinline__ F32Bias bias_of(const F32Params &P, const WorkEntry &e, int h,
+                                           int row) {
+  F32Bias b;
+  const int span = 2 * P.N - 1;
+  b.pos = make_rsrc(P.pos_w ? P.pos_w + (int64_t)h * span : P.q,
+                    P.pos_w ? 4u * (uint32_t)span : 0u);
+  b.time = P.time_w ? P.time_w + (int64_t)h * P.nb : nullptr;
+  b.ts_own = P.time_w ? P.ts[e.start + (row < e.len ? row : e.len - 1)] : 0;
   return b;
 }
 
+// Time buckets of a lane's 16 pairs, four to a register (a bucket is at most
+// 4 * 62 + 3).
+struct Buckets {
+  uint32_t b[4];
+  __device__ __forceinline__ int at(int r) const { return (int)((b[r >> 2] >> (8 * (r & 3))) & 255u); }
+};
+
+// s = alpha s + biases of the tile's pairs.  `off` = j - i of the pair of
+// streamed row 0 and this lane's stationary row, `dir` the change of j - i
+// per streamed row (+1 where the streamed side is keys, -1 queries); `bk`
+// receives the time buckets.  The scheduling barrier keeps the bias loads
+// out of the products' registers.
+__device__ __forceinline__ void add_bias(const F32Params &P, const F32Bias &b, f32x16 &s, int off,
+                                         int dir, const int64_t *ts, int g, Buckets &bk) {
+  __builtin_amdgcn_sched_barrier(0);
+  if (P.pos_w) {
+    float pw[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      pw[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+          b.pos, 4 * (off + dir * c_row(r, g) + P.N - 1), 0, 0));
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = __builtin_fmaf(P.alpha, s[r], pw[r]);
+  } else {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] *= P.alpha;
+  }
+  if (P.time_w) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      bk.b[q] = 0;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        bk.b[q] |= (uint32_t)time_bucket32(b.ts_own - ts[c_row(4 * q + c, g)], P.nb) << (8 * c);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    float tw[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) tw[r] = b.time[bk.at(r)];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] += tw[r];
+  }
+}
+
+// Timestamps of the streamed tile in the wave's part of LDS (rows past the
+// sequence repeat its last one; their pairs do not exist).
+__device__ __forceinline__ void stage_ts(const F32Params &P, const WorkEntry &e, int row0,
+                                         int64_t *ts, int lane) {
+  if (P.time_w && lane < FT) {
+    const int r = row0 + lane;
+    ts[lane] = P.ts[e.start + (r < e.len ? r : e.len - 1)];
+  }
+}
+
+// Pairs of a tile whose streamed rows are keys row0.. and this lane's query
+// i, or (KEYS false) queries row0.. and this lane's key: bit r set where the
+// pair exists.
+template <bool KEYS>
+__device__ __forceinline__ uint32_t pair_bits(int row0, int own, int len, int g) {
+  uint32_t ok = 0;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int x = row0 + c_row(r, g);
+    const bool have = KEYS ? x <= own && own < len : x >= own && x < len;
+    ok |= have ? 1u << r : 0u;
+  }
+  return ok;
+}
+
+// Work item `item` of `list`: entry, head and 32-row half; false if the half
+// lies past the sequence.
+__device__ __forceinline__ bool item_of(const F32Params &P, const WorkEntry *list, int64_t item,
+                                        WorkEntry &e, int &h, int &row0) {
+  const int64_t eh = item >> 1;
+  const int64_t entry = eh / P.H;
+  h = (int)(eh - entry * P.H);
+  e = list[entry];
+  row0 = e.tile * TILE + FT * (int)(item & 1);
+  return row0 < e.len;
+}
+
 template <int D>
-__global__ void __launch_bounds__(F32_THREADS)
+struct F32FwdSmem {
+  float tile[F32_WAVES][2][FT * F32_ROW<D>];     // K, V of each wave's tile
+  int64_t ts[F32_WAVES][FT];
+};
+
+template <int D>
+__device__ __forceinline__ void f32_fwd_item(const F32Params &P, F32FwdSmem<D> &sm, int64_t item) {
+  WorkEntry e;
+  int h, i0;
+  if (!item_of(P, P.list_q, item, e, h, i0)) return;
+  const int tid = opaque_tid(), lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = i0 + l32;
+  float *ks = sm.tile[w][0], *vs = sm.tile[w][1];
+  const __amdgpu_buffer_rsrc_t rq = rows_of(P, P.q, e, h, D), rk = rows_of(P, P.k, e, h, D),
+                               rv = rows_of(P, P.v, e, h, D);
+  F32Tile<D> t;
+  t.load(P, rk, FT * w, lane);
+  float qreg[D / 2];
+  load_rows<D>(P, rq, i, g, qreg);
+  const F32Bias bias = bias_of(P, e, h, i);
+  f32x16 acc[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[db][r] = 0.0f;
+
+  const int last = i0 / FT;
+  for (int kt = w; kt <= last; kt += F32_WAVES) {
+    const int j0 = FT * kt;
+    t.store(ks, lane);
+    stage_ts(P, e, j0, sm.ts[w], lane);
+    wave_lds_fence();
+    t.load(P, rv, j0, lane);
+    f32x16 s = tile_scores<D>(ks, qreg, l32, g);
+    t.store(vs, lane);
+    wave_lds_fence();
+    t.load(P, rk, j0 + FT * F32_WAVES, lane);
+    Buckets bk;
+    add_bias(P, bias, s, j0 - i, 1, sm.ts[w], g, bk);
+    const bool edge = kt == last;
+    float a[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) a[r] = s[r] * sigmoid_f(s[r]) * P.inv_n;
+    uint32_t ok = 0;
+    if (edge) {
+      ok = pair_bits<true>(j0, i, e.len, g);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) a[r] = (ok >> r) & 1 ? a[r] : 0.0f;
+    }
+    tile_accumulate<D>(vs, a, edge, ok, l32, g, acc);
+    wave_lds_fence();
+  }
+  sum_store<D>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, acc, tid,
+               P.o + ((e.start + i0) * P.H + h) * D, P.H * D, e.len - i0, 1.0f);
+}
+
+template <int D>
+__global__ void __launch_bounds__(F32_THREADS, D == 128 ? 1 : 2)
 f32_fwd_kernel(F32Params P) {
-  const int entry = blockIdx.x / P.H, h = blockIdx.x % P.H;
-  if (entry >= P.ctrl[CTRL_N_ENTRIES]) return;
-  const WorkEntry e = P.list[entry];
-  const SeqInfo si = P.info[e.seq];
-  const int64_t i = (int64_t)e.tile * TILE + threadIdx.x;
-  if (i >= si.len) return;
-  const int64_t ri = si.start + i;
-  float qi[D], acc[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) {
-    qi[c] = P.q[(ri * P.H + h) * D + c];
-    acc[c] = 0.0f;
-  }
-  for (int64_t j = 0; j <= i; ++j) {
-    const int64_t rj = si.start + j;
-    const float *kj = P.k + (rj * P.H + h) * D;
-    const float *vj = P.v + (rj * P.H + h) * D;
-    float s = 0.0f;
-#pragma unroll
-    for (int c = 0; c < D; ++c) s = fmaf(qi[c], kj[c], s);
-    s = P.alpha * s + bias(P, h, i, j, ri, rj);
-    const float a = s * sigmoid_f(s) * P.inv_n;
-#pragma unroll
-    for (int c = 0; c < D; ++c) acc[c] = fmaf(a, vj[c], acc[c]);
-  }
-#pragma unroll
-  for (int c = 0; c < D; ++c) P.out0[(ri * P.H + h) * D + c] = acc[c];
-}
-
-template <int D>
-__global__ void __launch_bounds__(F32_THREADS)
-f32_dq_kernel(F32Params P) {
-  const int entry = blockIdx.x / P.H, h = blockIdx.x % P.H;
-  if (entry >= P.ctrl[CTRL_N_ENTRIES]) return;
-  const WorkEntry e = P.list[entry];
-  const SeqInfo si = P.info[e.seq];
-  const int64_t i = (int64_t)e.tile * TILE + threadIdx.x;
-  if (i >= si.len) return;
-  const int64_t ri = si.start + i;
-  float qi[D], doi[D], acc[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) {
-    qi[c] = P.q[(ri * P.H + h) * D + c];
-    doi[c] = P.dO[(ri * P.H + h) * D + c];
-    acc[c] = 0.0f;
-  }
-  for (int64_t j = 0; j <= i; ++j) {
-    const int64_t rj = si.start + j;
-    const float *kj = P.k + (rj * P.H + h) * D;
-    const float *vj = P.v + (rj * P.H + h) * D;
-    float s = 0.0f, da = 0.0f;
-#pragma unroll
-    for (int c = 0; c < D; ++c) {
-      s = fmaf(qi[c], kj[c], s);
-      da = fmaf(doi[c], vj[c], da);
-    }
-    s = P.alpha * s + bias(P, h, i, j, ri, rj);
-    const float sg = sigmoid_f(s);
-    const float ds = da * sg * (1.0f + s * (1.0f - sg)) * P.inv_n;
-#pragma unroll
-    for (int c = 0; c < D; ++c) acc[c] = fmaf(ds, kj[c], acc[c]);
-  }
-#pragma unroll
-  for (int c = 0; c < D; ++c) P.out0[(ri * P.H + h) * D + c] = P.alpha * acc[c];
-}
-
-template <int D>
-__global__ void __launch_bounds__(F32_THREADS)
-f32_dkv_kernel(F32Params P) {
-  const int entry = blockIdx.x / P.H, h = blockIdx.x % P.H;
-  if (entry >= P.ctrl[CTRL_N_ENTRIES]) return;
-  const WorkEntry e = P.list[entry];
-  const SeqInfo si = P.info[e.seq];
-  const int64_t j = (int64_t)e.tile * TILE + threadIdx.x;
-  if (j >= si.len) return;
-  const int64_t rj = si.start + j;
-  float kj[D], vj[D], dk[D], dv[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) {
-    kj[c] = P.k[(rj * P.H + h) * D + c];
-    vj[c] = P.v[(rj * P.H + h) * D + c];
-    dk[c] = 0.0f;
-    dv[c] = 0.0f;
-  }
-  for (int64_t i = j; i < si.len; ++i) {
-    const int64_t ri = si.start + i;
-    const float *qi = P.q + (ri * P.H + h) * D;
-    const float *doi = P.dO + (ri * P.H + h) * D;
-    float s = 0.0f, da = 0.0f;
-#pragma unroll
-    for (int c = 0; c < D; ++c) {
-      s = fmaf(qi[c], kj[c], s);
-      da = fmaf(doi[c], vj[c], da);
-    }
-    s = P.alpha * s + bias(P, h, i, j, ri, rj);
-    const float sg = sigmoid_f(s);
-    const float a = s * sg * P.inv_n;
-    const float ds = da * sg * (1.0f + s * (1.0f - sg)) * P.inv_n;
-#pragma unroll
-    for (int c = 0; c < D; ++c) {
-      dv[c] = fmaf(a, doi[c], dv[c]);
-      dk[c] = fmaf(ds, qi[c], dk[c]);
-    }
-    const int64_t xp = (int64_t)h * (2 * (int64_t)P.N - 1) + (j - i + P.N - 1);
-    if (P.acc_pos) atomicAdd(&P.acc_pos[xp], (double)ds);
-    if (P.fix_pos) atomicAdd(&P.fix_pos[xp], to_fix(ds));
-    if (P.acc_time || P.fix_time) {
-      const int64_t xt = (int64_t)h * P.nb + time_bucket(P.ts[ri] - P.ts[rj], P.nb);
-      if (P.acc_time) atomicAdd(&P.acc_time[xt], (double)ds);
-      if (P.fix_time) atomicAdd(&P.fix_time[xt], to_fix(ds));
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < D; ++c) {
-    P.out1[(rj * P.H + h) * D + c] = P.alpha * dk[c];
-    P.out2[(rj * P.H + h) * D + c] = dv[c];
+  __shared__ __attribute__((aligned(16))) F32FwdSmem<D> sm;
+  const int64_t n_items = 2 * (int64_t)P.ctrl[CTRL_N_ENTRIES] * P.H;
+  for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+    f32_fwd_item<D>(P, sm, item);
+    __syncthreads();
   }
 }
 
-__global__ void fill_zero_kernel(float *p, int64_t n) {
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n;
+// Table-gradient sums: LDS and global in double, or (deterministic mode)
+// 64-bit fixed point, whose integer additions give the same result in any
+// order.
+template <bool DET> struct F32Tab;
+template <> struct F32Tab<false> {
+  typedef double T;
+  static __device__ __forceinline__ T of(float v) { return (double)v; }
+};
+template <> struct F32Tab<true> {
+  typedef unsigned long long T;
+  static __device__ __forceinline__ T of(float v) { return to_fix(v); }
+};
+
+template <int D, bool DET>
+struct F32BwdSmem {
+  float tile[F32_WAVES][2][FT * F32_ROW<D>];     // K, V or Q, dO of each wave's tile
+  int64_t ts[F32_WAVES][FT];
+  // diagonal sums of each wave's tile, one copy per lane group (the lanes of
+  // an atomic hit distinct slots)
+  typename F32Tab<DET>::T win[F32_WAVES][2][2 * FT];
+};
+
+template <int D, bool DET>
+__device__ __forceinline__ void f32_dq_item(const F32Params &P, F32BwdSmem<D, DET> &sm,
+                                            int64_t item) {
+  WorkEntry e;
+  int h, i0;
+  if (!item_of(P, P.list_q, item, e, h, i0)) return;
+  const int tid = opaque_tid(), lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = i0 + l32;
+  float *ks = sm.tile[w][0], *vs = sm.tile[w][1];
+  const __amdgpu_buffer_rsrc_t rk = rows_of(P, P.k, e, h, D), rv = rows_of(P, P.v, e, h, D);
+  F32Tile<D> t;
+  t.load(P, rk, FT * w, lane);
+  float qreg[D / 2], oreg[D / 2];
+  load_rows<D>(P, rows_of(P, P.q, e, h, D), i, g, qreg);
+  load_rows<D>(P, rows_of(P, P.dO, e, h, D), i, g, oreg);
+  const F32Bias bias = bias_of(P, e, h, i);
+  f32x16 acc[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[db][r] = 0.0f;
+
+  const int last = i0 / FT;
+  for (int kt = w; kt <= last; kt += F32_WAVES) {
+    const int j0 = FT * kt;
+    t.store(ks, lane);
+    stage_ts(P, e, j0, sm.ts[w], lane);
+    wave_lds_fence();
+    t.load(P, rv, j0, lane);
+    f32x16 s = tile_scores<D>(ks, qreg, l32, g);
+    t.store(vs, lane);
+    wave_lds_fence();
+    t.load(P, rk, j0 + FT * F32_WAVES, lane);
+    const f32x16 da = tile_scores<D>(vs, oreg, l32, g);
+    Buckets bk;
+    add_bias(P, bias, s, j0 - i, 1, sm.ts[w], g, bk);
+    const bool edge = kt == last;
+    float ds[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float sg = sigmoid_f(s[r]);
+      ds[r] = da[r] * sg * (1.0f + s[r] * (1.0f - sg)) * P.inv_n;
+    }
+    uint32_t ok = 0;
+    if (edge) {
+      ok = pair_bits<true>(j0, i, e.len, g);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) ds[r] = (ok >> r) & 1 ? ds[r] : 0.0f;
+    }
+    tile_accumulate<D>(ks, ds, edge, ok, l32, g, acc);
+    wave_lds_fence();
+  }
+  sum_store<D>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, acc, tid,
+               P.dq + ((e.start + i0) * P.H + h) * D, P.H * D, e.len - i0, P.alpha);
+}
+
+template <int D, bool DET>
+__device__ __forceinline__ void f32_dkv_item(const F32Params &P, F32BwdSmem<D, DET> &sm,
+                                             typename F32Tab<DET>::T *hist, int64_t item) {
+  typedef F32Tab<DET> A;
+  WorkEntry e;
+  int h, j0;
+  if (!item_of(P, P.list_k, item, e, h, j0)) return;
+  const int tid = opaque_tid(), lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = j0 + l32;
+  const int first = j0 / FT, tiles = (e.len + FT - 1) / FT;
+  float *qs = sm.tile[w][0], *os = sm.tile[w][1];
+  const __amdgpu_buffer_rsrc_t rq = rows_of(P, P.q, e, h, D), ro = rows_of(P, P.dO, e, h, D);
+  F32Tile<D> t;
+  t.load(P, rq, j0 + FT * w, lane);
+  float kreg[D / 2], vreg[D / 2];
+  load_rows<D>(P, rows_of(P, P.k, e, h, D), j, g, kreg);
+  load_rows<D>(P, rows_of(P, P.v, e, h, D), j, g, vreg);
+  const F32Bias bias = bias_of(P, e, h, j);
+  const bool time_g = P.acc_time != nullptr;
+  const bool in_lds = P.nb <= F32_LDS_BUCKETS;
+  typename A::T *gt = time_g ? (typename A::T *)P.acc_time + (int64_t)h * P.nb : nullptr;
+  typename A::T *gp = P.acc_pos
+                          ? (typename A::T *)P.acc_pos + (int64_t)h * (2 * (int64_t)P.N - 1)
+                          : nullptr;
+  for (int x = lane; x < 4 * FT; x += 64) (&sm.win[w][0][0])[x] = 0;
+  if (time_g && in_lds)
+    for (int x = tid; x < P.nb; x += F32_THREADS) hist[x] = 0;
+  __syncthreads();
+  f32x16 dk[D / 32], dv[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { dk[db][r] = 0.0f; dv[db][r] = 0.0f; }
+
+  for (int qt = first + w; qt < tiles; qt += F32_WAVES) {
+    const int i0 = FT * qt;
+    t.store(qs, lane);
+    stage_ts(P, e, i0, sm.ts[w], lane);
+    wave_lds_fence();
+    t.load(P, ro, i0, lane);
+    f32x16 s = tile_scores<D>(qs, kreg, l32, g);
+    t.store(os, lane);
+    wave_lds_fence();
+    t.load(P, rq, i0 + FT * F32_WAVES, lane);
+    const f32x16 da = tile_scores<D>(os, vreg, l32, g);
+    Buckets bk;
+    add_bias(P, bias, s, j - i0, -1, sm.ts[w], g, bk);
+    const bool edge = qt == first || qt == tiles - 1 || j0 + FT > e.len;
+    float a[16], ds[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float sg = sigmoid_f(s[r]);
+      a[r] = s[r] * sg * P.inv_n;
+      ds[r] = da[r] * sg * (1.0f + s[r] * (1.0f - sg)) * P.inv_n;
+    }
+    uint32_t ok = 0xffffu;
+    if (edge) {
+      ok = pair_bits<false>(i0, j, e.len, g);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        a[r] = (ok >> r) & 1 ? a[r] : 0.0f;
+        ds[r] = (ok >> r) & 1 ? ds[r] : 0.0f;
+      }
+    }
+    if (gp) {
+      // slot i - j + 31 (- the tile's offset) of this lane group's window,
+      // then the window's 63 diagonals to the table
+      typename A::T *pw = &sm.win[w][g][FT - 1 - l32];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) atomicAdd(pw + c_row(r, g), A::of(ds[r]));
+      wave_lds_fence();
+      const typename A::T v = sm.win[w][0][lane] + sm.win[w][1][lane];
+      sm.win[w][0][lane] = 0;
+      sm.win[w][1][lane] = 0;
+      const int m = i0 - j0 + lane - (FT - 1);
+      if (v != 0 && m >= 0 && m < e.len) atomicAdd(&gp[P.N - 1 - m], v);
+    }
+    if (time_g) {
+      // runs of equal buckets down this lane's queries (ordered timestamps
+      // change bucket rarely), summed like the table
+      typename A::T run = 0;
+      int cur = bk.at(0);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        if (bk.at(r) != cur) {
+          if (in_lds) atomicAdd(&hist[cur], run);
+          else atomicAdd(&gt[cur], run);
+          run = 0;
+          cur = bk.at(r);
+        }
+        run += A::of(ds[r]);
+      }
+      if (in_lds) atomicAdd(&hist[cur], run);
+      else atomicAdd(&gt[cur], run);
+    }
+    tile_accumulate<D>(os, a, edge, ok, l32, g, dv);
+    tile_accumulate<D>(qs, ds, edge, ok, l32, g, dk);
+    wave_lds_fence();
+  }
+  sum_store<D>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dk, tid,
+               P.dk + ((e.start + j0) * P.H + h) * D, P.H * D, e.len - j0, P.alpha);
+  sum_store<D>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dv, tid,
+               P.dv + ((e.start + j0) * P.H + h) * D, P.H * D, e.len - j0, 1.0f);
+  if (time_g && in_lds)
+    for (int x = tid; x < P.nb; x += F32_THREADS)
+      if (hist[x] != 0) atomicAdd(&gt[x], hist[x]);
+}
+
+// Both item kinds of the backward in one launch, a dK/dV and a dQ item in
+// turn down the longest-first lists, so that neither kind's tail is alone.
+template <int D, bool DET>
+__global__ void __launch_bounds__(F32_THREADS, D == 128 ? 1 : 2)
+f32_bwd_kernel(F32Params P) {
+  __shared__ __attribute__((aligned(16))) F32BwdSmem<D, DET> sm;
+  extern __shared__ double dyn_f32[];              // d_time histogram of the item's head
+  const int64_t n_items = 4 * (int64_t)P.ctrl[CTRL_N_ENTRIES] * P.H;
+  for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+    if (item & 1) f32_dq_item<D, DET>(P, sm, item >> 1);
+    else f32_dkv_item<D, DET>(P, sm, (typename F32Tab<DET>::T *)dyn_f32, item >> 1);
+    __syncthreads();
+  }
+}
+
+// The two tables' sums cleared, and converted to float (either may be absent).
+__global__ void f32_tables_zero_kernel(unsigned long long *pos, int64_t n_pos,
+                                       unsigned long long *time, int64_t n_time) {
+  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n_pos + n_time;
        x += (int64_t)gridDim.x * blockDim.x)
-    p[x] = 0.0f;
+    (x < n_pos ? pos[x] : time[x - n_pos]) = 0;
 }
 
-// Double table sums -> float tables.
-__global__ void double_to_float_kernel(const double *acc, float *out, int64_t n) {
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n;
-       x += (int64_t)gridDim.x * blockDim.x)
-    out[x] = (float)acc[x];
+template <bool DET>
+__global__ void f32_tables_out_kernel(const void *pos, int64_t n_pos, const void *time,
+                                      int64_t n_time, float *d_pos, float *d_time) {
+  typedef typename F32Tab<DET>::T T;
+  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n_pos + n_time;
+       x += (int64_t)gridDim.x * blockDim.x) {
+    const bool p = x < n_pos;
+    const T v = p ? ((const T *)pos)[x] : ((const T *)time)[x - n_pos];
+    const float f = DET ? (float)((double)(long long)v * (1.0 / FIX_ONE)) : (float)v;
+    if (p) d_pos[x] = f;
+    else d_time[x - n_pos] = f;
+  }
 }
 
-// Fixed-point table sums -> float tables.
-__global__ void fix_to_float_kernel(const unsigned long long *fix, float *out, int64_t n) {
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n;
-       x += (int64_t)gridDim.x * blockDim.x)
-    out[x] = (float)((double)(long long)fix[x] * (1.0 / FIX_ONE));
+// One work-group per item (`per` of them to a list entry and head) up to a
+// million, which then take the rest in turn.
+dim3 f32_grid(const Problem &p, int per) {
+  return dim3((unsigned)std::max<int64_t>(
+      1, std::min<int64_t>((int64_t)1 << 20, per * p.max_entries * p.H)));
 }
 
-F32Params make_params(const AttnArgs &a, const WorkEntry *list) {
+F32Params make_params(const AttnArgs &a) {
   const char *ws = (const char *)a.ws;
   F32Params P{};
   P.q = (const float *)a.q;
@@ -196,8 +638,8 @@ F32Params make_params(const AttnArgs &a, const WorkEntry *list) {
   P.time_w = a.time_w;
   P.ts = a.ts;
   P.ctrl = (const int32_t *)(ws + a.L.ctrl);
-  P.info = (const SeqInfo *)(ws + a.L.seqinfo);
-  P.list = list;
+  P.list_q = (const WorkEntry *)(ws + a.L.list_q);
+  P.list_k = (const WorkEntry *)(ws + a.L.list_k);
   P.H = a.p.H;
   P.N = a.p.N;
   P.nb = a.p.has_time ? a.p.nb : 0;
@@ -206,21 +648,14 @@ F32Params make_params(const AttnArgs &a, const WorkEntry *list) {
   return P;
 }
 
-#define HSTU_F32_DISPATCH(NAME, D, GRID, S, P)                                       \
-  do {                                                                              \
-    if (D == 32) hipLaunchKernelGGL(NAME<32>, GRID, dim3(F32_THREADS), 0, S, P);     \
-    else if (D == 64) hipLaunchKernelGGL(NAME<64>, GRID, dim3(F32_THREADS), 0, S, P); \
-    else hipLaunchKernelGGL(NAME<128>, GRID, dim3(F32_THREADS), 0, S, P);            \
-  } while (0)
-
 }  // namespace
 
 hipError_t launch_attn_fwd_f32(const AttnArgs &a, void *o, hipStream_t s) {
-  const char *ws = (const char *)a.ws;
-  F32Params P = make_params(a, (const WorkEntry *)(ws + a.L.list_q));
-  P.out0 = (float *)o;
-  const dim3 grid((unsigned)(a.p.max_entries * a.p.H));
-  HSTU_F32_DISPATCH(f32_fwd_kernel, a.p.d, grid, s, P);
+  F32Params P = make_params(a);
+  P.o = (float *)o;
+  auto kfn = a.p.d == 32 ? f32_fwd_kernel<32> : a.p.d == 64 ? f32_fwd_kernel<64>
+                                                            : f32_fwd_kernel<128>;
+  hipLaunchKernelGGL(kfn, f32_grid(a.p, 2), dim3(F32_THREADS), 0, s, P);
   return hipGetLastError();
 }
 
@@ -229,49 +664,44 @@ hipError_t launch_attn_bwd_f32(const AttnArgs &a, const void *dO, void *dq,
                                hipStream_t s) {
   const char *ws = (const char *)a.ws;
   const Problem &p = a.p;
-  const int64_t n_pos = (int64_t)p.H * (2 * (int64_t)p.N - 1), n_time = (int64_t)p.H * p.nb;
-  // table-shaped staging sums in the workspace (8 bytes per entry): 64-bit
-  // fixed point in the deterministic mode, double otherwise; converted to
-  // the float tables after the dK/dV kernel (zeros when T = 0)
+  // table-shaped sums in the workspace (8 bytes per entry): 64-bit fixed
+  // point in the deterministic mode, double otherwise; converted to the
+  // float tables after the kernel (zeros when T = 0)
+  const int64_t n_pos = d_pos ? (int64_t)p.H * (2 * (int64_t)p.N - 1) : 0;
+  const int64_t n_time = d_time ? (int64_t)p.H * p.nb : 0;
   void *st_pos = d_pos ? (void *)(ws + a.L.dpos_part) : nullptr;
   void *st_time = d_time ? (void *)(ws + a.L.dtime_part) : nullptr;
-  if (st_pos)
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(64), dim3(256), 0, s, (float *)st_pos, 2 * n_pos);
-  if (st_time)
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(8), dim3(256), 0, s, (float *)st_time, 2 * n_time);
-  unsigned long long *fix_pos = p.deterministic ? (unsigned long long *)st_pos : nullptr;
-  unsigned long long *fix_time = p.deterministic ? (unsigned long long *)st_time : nullptr;
-  double *acc_pos = p.deterministic ? nullptr : (double *)st_pos;
-  double *acc_time = p.deterministic ? nullptr : (double *)st_time;
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (p.T > 0) {
-  const dim3 grid((unsigned)(p.max_entries * p.H));
-  F32Params P = make_params(a, (const WorkEntry *)(ws + a.L.list_q));
-  P.dO = (const float *)dO;
-  P.out0 = (float *)dq;
-  HSTU_F32_DISPATCH(f32_dq_kernel, p.d, grid, s, P);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  F32Params K = make_params(a, (const WorkEntry *)(ws + a.L.list_k));
-  K.dO = (const float *)dO;
-  K.out1 = (float *)dk;
-  K.out2 = (float *)dv;
-  K.acc_pos = acc_pos;
-  K.acc_time = acc_time;
-  K.fix_pos = fix_pos;
-  K.fix_time = fix_time;
-  HSTU_F32_DISPATCH(f32_dkv_kernel, p.d, grid, s, K);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const bool tables = n_pos + n_time > 0;
+  const dim3 tgrid((unsigned)std::min<int64_t>(256, (n_pos + n_time + 255) / 256));
+  hipError_t e = hipSuccess;
+  if (tables) {
+    hipLaunchKernelGGL(f32_tables_zero_kernel, tgrid, dim3(256), 0, s,
+                       (unsigned long long *)st_pos, n_pos, (unsigned long long *)st_time, n_time);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (fix_pos)
-    hipLaunchKernelGGL(fix_to_float_kernel, dim3(64), dim3(256), 0, s, fix_pos, d_pos, n_pos);
-  if (fix_time)
-    hipLaunchKernelGGL(fix_to_float_kernel, dim3(8), dim3(256), 0, s, fix_time, d_time, n_time);
-  if (acc_pos)
-    hipLaunchKernelGGL(double_to_float_kernel, dim3(64), dim3(256), 0, s, acc_pos, d_pos, n_pos);
-  if (acc_time)
-    hipLaunchKernelGGL(double_to_float_kernel, dim3(8), dim3(256), 0, s, acc_time, d_time,
-                       n_time);
+  if (p.T > 0) {
+    F32Params P = make_params(a);
+    P.dO = (const float *)dO;
+    P.dq = (float *)dq;
+    P.dk = (float *)dk;
+    P.dv = (float *)dv;
+    P.acc_pos = st_pos;
+    P.acc_time = st_time;
+    const size_t dyn = d_time && p.nb <= F32_LDS_BUCKETS ? sizeof(double) * (size_t)p.nb : 0;
+    auto kfn = p.deterministic
+                   ? (p.d == 32 ? f32_bwd_kernel<32, true>
+                                : p.d == 64 ? f32_bwd_kernel<64, true> : f32_bwd_kernel<128, true>)
+                   : (p.d == 32 ? f32_bwd_kernel<32, false>
+                                : p.d == 64 ? f32_bwd_kernel<64, false>
+                                            : f32_bwd_kernel<128, false>);
+    hipLaunchKernelGGL(kfn, f32_grid(p, 4), dim3(F32_THREADS), dyn, s, P);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (tables) {
+    auto kfn = p.deterministic ? f32_tables_out_kernel<true> : f32_tables_out_kernel<false>;
+    hipLaunchKernelGGL(kfn, tgrid, dim3(256), 0, s, (const void *)st_pos, n_pos,
+                       (const void *)st_time, n_time, d_pos, d_time);
+  }
   return hipGetLastError();
 }
 

@@ -69,6 +69,22 @@ __device__ __forceinline__ int time_bucket(int64_t delta, int nb) {
   return b < nb - 1 ? b : nb - 1;
 }
 
+// The same rule with a 32-bit path while |delta| < 2^32 (the usual case: a
+// 64-bit leading-zero count and shift are several instructions each).
+__device__ __forceinline__ int time_bucket32(int64_t delta, int nb) {
+  const uint64_t x = delta < 0 ? (uint64_t)0 - (uint64_t)delta : (uint64_t)delta;
+  if (x >> 32) return time_bucket(delta, nb);
+  const uint32_t y = (uint32_t)x;
+  int b;
+  if (y < 4) {
+    b = (int)y;
+  } else {
+    const int e = 31 - __clz((int)y);
+    b = 4 * (e - 1) + (int)((y >> (e - 2)) & 3u);
+  }
+  return b < nb - 1 ? b : nb - 1;
+}
+
 // Work-group barrier that orders LDS only: it waits for this wave's
 // outstanding LDS operations, not for its global loads, stores or atomics
 // (__syncthreads waits for those too).  For kernels whose threads exchange
