@@ -140,14 +140,6 @@ __device__ __forceinline__ f32x16 tile_scores(const float *lds, const float (&st
   return s;
 }
 
-// Orders the wave's own LDS traffic across lanes (the hardware keeps a
-// wave's LDS operations in order; this keeps the compiler to it).
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
-
 // acc[db] += X^T P: X = the tile's rows in LDS, P the pair values in the
 // layout tile_scores leaves them in.  acc register r of lane (l32, g) is dim
 // 32 db + c_row(r, g) of stationary row l32.  On an `edge` tile some pairs do

@@ -69,12 +69,10 @@ __device__ __forceinline__ int time_bucket(int64_t delta, int nb) {
   return b < nb - 1 ? b : nb - 1;
 }
 
-// The same rule with a 32-bit path while |delta| < 2^32 (the usual case: a
-// 64-bit leading-zero count and shift are several instructions each).
-__device__ __forceinline__ int time_bucket32(int64_t delta, int nb) {
-  const uint64_t x = delta < 0 ? (uint64_t)0 - (uint64_t)delta : (uint64_t)delta;
-  if (x >> 32) return time_bucket(delta, nb);
-  const uint32_t y = (uint32_t)x;
+// The same rule on a gap of 32 bits, and with that path while |delta| < 2^32
+// (the usual case: a 64-bit leading-zero count and shift are several
+// instructions each).
+__device__ __forceinline__ int time_bucket_u32(uint32_t y, int nb) {
   int b;
   if (y < 4) {
     b = (int)y;
@@ -83,6 +81,11 @@ __device__ __forceinline__ int time_bucket32(int64_t delta, int nb) {
     b = 4 * (e - 1) + (int)((y >> (e - 2)) & 3u);
   }
   return b < nb - 1 ? b : nb - 1;
+}
+
+__device__ __forceinline__ int time_bucket32(int64_t delta, int nb) {
+  const uint64_t x = delta < 0 ? (uint64_t)0 - (uint64_t)delta : (uint64_t)delta;
+  return x >> 32 ? time_bucket(delta, nb) : time_bucket_u32((uint32_t)x, nb);
 }
 
 // Work-group barrier that orders LDS only: it waits for this wave's
@@ -94,6 +97,14 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Orders a wave's own LDS traffic across its lanes (the hardware keeps a
+// wave's LDS operations in order; this keeps the compiler to it).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
 // Raw buffer loads: a resource over `bytes` bytes from `base` and a per-lane

@@ -3,19 +3,40 @@
 // padding) from the position table, the bucketed time table and a
 // functional time encoding, and its backward into those parameters.
 //
-// Square tiling: work-group (b, it, h) owns the 64-row band it of sequence
-// b's square for head h and walks its 64 x 64 tiles; the tile's position
-// slice and the head's time table sit in LDS; lane c of a wave handles column c of
-// a tile and the wave's rows, so every store (forward) and load (backward)
-// of a wave is one contiguous 256-byte row segment, whatever the square's
-// alignment.  Per element the forward adds the biases in registers; the
-// backward sums the incoming gradient by diagonal (an LDS window of the
-// tile's 127 diagonals), by time bucket (per-lane runs over the row order
-// into an LDS histogram) and into the functional encoding's two parameter
-// gradients (per-lane sums, reduced across the work-group in a fixed
-// order).  All table sums are 64-bit fixed point added with integer
-// atomics: the result does not depend on the order in which work-groups
-// finish, so the backward is bitwise reproducible.
+// Both passes cut the batch into equal wave items, numbered across the
+// sequences (rab_scan_kernel's prefix sums): a 2048-token sequence's square is
+// spread as evenly as a hundred short ones.
+//
+// Forward, bound by its writes: an item is 512 consecutive elements of a
+// square, whatever rows they belong to, for every head.  The time bucket,
+// log2(1 + |dt|) and position index of an element belong to its pair of rows,
+// not to a head, and are computed once.  Consecutive elements, because a
+// wave that writes 256-byte pieces of many unaligned rows leaves the 128-byte
+// lines at their ends to other waves: 3.3 TB/s for the bare stores of
+// 16 x 64 tiles, 4.6 TB/s for runs, 5.5 TB/s where all planes are aligned.
+// One eighth of the items go to each XCD, so that shared lines meet in one L2
+// (another 8% for the tiles).
+//
+// Backward, bound by its reads and the per-element double sums: sheared
+// items of 32 rows by 64 diagonals, lane l on diagonal d0 + l.  In any row the
+// lanes read 64 consecutive columns, and down the rows a lane stays on its
+// diagonal, so the position gradient is a plain sum in a register.  Two heads
+// share a work-group (and an element's bucket and logarithm); it keeps their
+// time histograms in LDS, one 64-bit fixed-point counter per bucket and lane
+// group, added to at the end of each run of equal buckets down a diagonal.
+// Lanes on neighbouring diagonals meet in the same bucket and a wave's
+// atomics on one address are served one by one, so four heads (16 counters
+// per bucket) took 1010 us where two (32) take 257 and one (64) 356.  The
+// functional encoding's sums stay in registers.  All partial sums are in
+// double; what crosses waves is 64-bit fixed point added with integer
+// atomics, or a sum in a fixed order: the result does not depend on the
+// order in which work-groups finish, so the backward is bitwise reproducible.
+//
+// Measured on 64 sequences of 32..2048 tokens, 8 heads (841 MB), all three
+// encodings: forward 1630 -> 182 us (4.6 TB/s), backward 2480 -> 257 us
+// (3.3 TB/s; reading alone, position gradient only, 189 us).  Before, one
+// work-group walked a 64-row band per head, which computed every bucket and
+// logarithm per head and left the longest bands to the end.
 #include <algorithm>
 
 #include "internal.h"
@@ -24,19 +45,34 @@
 namespace hstu {
 namespace {
 
-constexpr int RT = 256;                 // threads: 4 waves x 64 columns
-constexpr int ROWS_PER_THREAD = TILE / (RT / TILE);   // 16
+constexpr int R_ROWS = 32;                   // rows of an item
+constexpr int R_STEP = 8;                    // rows handled at a time (16 spills)
+constexpr int R_FSTEP = 8;                   // elements of a lane in a forward item
+constexpr int R_FLAT = 64 * R_FSTEP;         // consecutive elements of a forward item
+constexpr int R_FWD_THREADS = 256;
+constexpr int R_BWD_THREADS = 512;
+constexpr int R_SCAN_THREADS = 1024;
+// Item prefix in LDS up to this many sequences (read from L2 above).
+constexpr int R_LDS_SEQS = 1023;
+// LDS counters of the backward's time histograms (64 KB, two work-groups per
+// CU): with two heads 32 per bucket up to 128 buckets, fewer above.
+constexpr int R_HIST = 8192;
+constexpr int64_t R_NEAR = 1 << 30;          // gaps of timestamps this near fit 32 bits
 
 struct RabArgs {
   const int64_t *off;
   int64_t *sq;                          // [B+1] square offsets (workspace)
+  int64_t *items;                       // [B+1] item offsets (workspace)
   const float *pos_w, *time_w, *time_fn;
   const int64_t *ts;
   float *rab;
   const float *d_rab;
-  unsigned long long *fix_pos, *fix_time, *fix_fn;
+  // table sums, back to back in the workspace (n_fix in all)
+  unsigned long long *fix, *fix_pos, *fix_time, *fix_fn;
+  int64_t n_fix;
   int64_t T, total_square;
   int B, N, H, nb;
+  int copies;                           // histogram counters per bucket
 };
 
 // Clamped start and length of sequence b (as the attention's scheduler
@@ -50,46 +86,60 @@ __device__ __forceinline__ void seq_of(const RabArgs &a, int b, int64_t &start, 
   len = (int)(L > a.N ? a.N : L);
 }
 
-// sq[b] = sum of L_b'^2 over b' < b: each thread sums a contiguous run of
-// sequences, the run totals are scanned in LDS, then every run is written.
-__global__ void __launch_bounds__(1024) rab_sq_kernel(RabArgs a) {
-  __shared__ int64_t part[1024];
-  const int t = threadIdx.x;
-  const int per = (a.B + 1023) / 1024;
-  const int b0 = t * per, b1 = min(a.B, b0 + per);
-  int64_t s = 0;
-  for (int b = b0; b < b1; ++b) {
-    int64_t st; int L;
-    seq_of(a, b, st, L);
-    s += (int64_t)L * L;
-  }
-  part[t] = s;
-  __syncthreads();
-  if (t == 0) {
-    int64_t run = 0;
-    for (int x = 0; x < 1024; ++x) { const int64_t v = part[x]; part[x] = run; run += v; }
-    a.sq[a.B] = run;
-  }
-  __syncthreads();
-  s = part[t];
-  for (int b = b0; b < b1; ++b) {
-    a.sq[b] = s;
-    int64_t st; int L;
-    seq_of(a, b, st, L);
-    s += (int64_t)L * L;
-  }
+// 64-diagonal strips that cover `rows` rows of a square of side L, and the
+// items of the whole square (`flat`: the forward's, else the backward's).
+__device__ __forceinline__ int strips_of(int L, int rows) { return (L + rows - 1 + 63) / 64; }
+__device__ __forceinline__ int64_t items_of(int L, bool flat) {
+  if (flat) return ((int64_t)L * L + R_FLAT - 1) / R_FLAT;
+  const int full = L / R_ROWS, rem = L % R_ROWS;
+  return (int64_t)full * strips_of(L, R_ROWS) + (rem ? strips_of(L, rem) : 0);
 }
 
-__global__ void rab_zero_kernel(unsigned long long *p, int64_t n) {
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n;
-       x += (int64_t)gridDim.x * blockDim.x)
-    p[x] = 0;
-}
-
-__global__ void rab_fix_to_float_kernel(const unsigned long long *fix, float *out, int64_t n) {
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n;
-       x += (int64_t)gridDim.x * blockDim.x)
-    out[x] = (float)((double)(long long)fix[x] * (1.0 / FIX_ONE));
+// sq[b] = sum of L_b'^2 and items[b] = sum of items over b' < b (work-group
+// 0: a wave scan of each 1024 sequences); the other work-groups clear the
+// backward's table sums.
+__global__ void __launch_bounds__(R_SCAN_THREADS) rab_scan_kernel(RabArgs a) {
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  if (blockIdx.x > 0) {
+    for (int64_t x = (int64_t)(blockIdx.x - 1) * R_SCAN_THREADS + t; x < a.n_fix;
+         x += (int64_t)(gridDim.x - 1) * R_SCAN_THREADS)
+      a.fix[x] = 0;
+    return;
+  }
+  constexpr int W = R_SCAN_THREADS / 64;
+  __shared__ int64_t part[2][W];
+  int64_t run_s = 0, run_i = 0;
+  for (int b0 = 0; b0 < a.B; b0 += R_SCAN_THREADS) {
+    const int b = b0 + t;
+    int64_t st, sq = 0, it = 0;
+    if (b < a.B) {
+      int L;
+      seq_of(a, b, st, L);
+      sq = (int64_t)L * L;
+      it = items_of(L, a.rab != nullptr);
+    }
+    int64_t s = sq, n = it;                       // inclusive sums over the wave
+#pragma unroll
+    for (int k = 1; k < 64; k <<= 1) {
+      const int64_t us = __shfl_up(s, k, 64), un = __shfl_up(n, k, 64);
+      s += lane >= k ? us : 0;
+      n += lane >= k ? un : 0;
+    }
+    __syncthreads();
+    if (lane == 63) { part[0][w] = s; part[1][w] = n; }
+    __syncthreads();
+    int64_t before_s = run_s, before_i = run_i;
+    for (int x = 0; x < W; ++x) {
+      if (x < w) { before_s += part[0][x]; before_i += part[1][x]; }
+      run_s += part[0][x];
+      run_i += part[1][x];
+    }
+    if (b < a.B) {
+      a.sq[b] = before_s + s - sq;
+      a.items[b] = before_i + n - it;
+    }
+  }
+  if (t == 0) { a.sq[a.B] = run_s; a.items[a.B] = run_i; }
 }
 
 // 64-bit fixed-point value of a double partial sum (as to_fix).
@@ -105,197 +155,328 @@ __device__ __forceinline__ float fn_lg2(int64_t dt) {
   return __builtin_amdgcn_logf(1.0f + xf);
 }
 
-// The bucket rule on a time gap, with a 32-bit path while |dt| < 2^32.
-__device__ __forceinline__ int bucket_fast(int64_t dt, int nb) {
-  const uint64_t x = dt < 0 ? (uint64_t)0 - (uint64_t)dt : (uint64_t)dt;
-  if (x >> 32) return time_bucket(dt, nb);
-  const uint32_t y = (uint32_t)x;
-  int b;
-  if (y < 4) {
-    b = (int)y;
-  } else {
-    const int e = 31 - __clz((int)y);
-    b = 4 * (e - 1) + (int)((y >> (e - 2)) & 3u);
-  }
-  return b < nb - 1 ? b : nb - 1;
+// The item prefix where a work-group finds it: staged in LDS, or (many
+// sequences) in the workspace.
+__device__ __forceinline__ const int64_t *stage_items(const RabArgs &a, int64_t *lds, int tid,
+                                                      int threads) {
+  if (a.B > R_LDS_SEQS) return a.items;
+  for (int b = tid; b <= a.B; b += threads) lds[b] = a.items[b];
+  __syncthreads();
+  return lds;
 }
 
-// Band setup shared by both passes: sequence, band rows of this thread and
-// their timestamps.  Returns false when the band lies past the sequence (or
-// the square would not fit the caller's tensor).
-struct Band {
-  int64_t start, base;                  // first row; sq[b]
-  int L, it, nt, c, rg;
-  int64_t ts_i[ROWS_PER_THREAD];
+// Sequence of item `item`: the last one whose items begin at or before it
+// (the same in every lane).
+__device__ __forceinline__ int seq_of_item(const RabArgs &a, const int64_t *items, int64_t item) {
+  int lo = 0, hi = a.B - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (items[mid] <= item) lo = mid; else hi = mid - 1;
+  }
+  return __builtin_amdgcn_readfirstlane(lo);
+}
+
+// Wave item `item`: rows r0 .. r0 + rows - 1 of the sequence at `start`, whose
+// square of side L begins at element `base`; lane l is on diagonal (column
+// minus row) d0 + l.  All wave-uniform.
+struct Strip {
+  int64_t start, base;
+  int L, r0, rows, d0;
 };
 
-__device__ __forceinline__ bool band_of(const RabArgs &a, Band &bd) {
-  const int b = blockIdx.x;
-  bd.it = blockIdx.y;
-  seq_of(a, b, bd.start, bd.L);
-  if ((int64_t)bd.it * TILE >= bd.L) return false;
-  bd.base = a.sq[b];
-  if (bd.base < 0 || bd.base + (int64_t)bd.L * bd.L > a.total_square) return false;
-  bd.nt = (bd.L + TILE - 1) / TILE;
-  bd.c = threadIdx.x & 63;
-  bd.rg = threadIdx.x >> 6;
-  if (a.ts) {
-#pragma unroll
-    for (int k = 0; k < ROWS_PER_THREAD; ++k) {
-      const int i = bd.it * TILE + bd.rg + 4 * k;
-      bd.ts_i[k] = a.ts[bd.start + (i < bd.L ? i : bd.L - 1)];
-    }
-  }
-  return true;
+// False if the square would not fit the caller's tensor.
+__device__ __forceinline__ bool strip_of(const RabArgs &a, const int64_t *items, int64_t item,
+                                         Strip &t) {
+  const int b = seq_of_item(a, items, item);
+  seq_of(a, b, t.start, t.L);
+  t.base = a.sq[b];
+  const int local = __builtin_amdgcn_readfirstlane((int)(item - items[b]));
+  const int full = t.L / R_ROWS, ns = strips_of(t.L, R_ROWS);
+  int rc = local / ns;
+  rc = rc < full ? rc : full;
+  t.r0 = rc * R_ROWS;
+  t.rows = t.L - t.r0 < R_ROWS ? t.L - t.r0 : R_ROWS;
+  t.d0 = 64 * (local - rc * ns) - (t.r0 + t.rows - 1);
+  return t.base >= 0 && t.base + (int64_t)t.L * t.L <= a.total_square;
 }
 
-// Dynamic LDS: the head's time table (nb floats) when time_w is given.  The
-// next tile's position-slice entry and column timestamp are loaded while
-// the current tile is computed (double-buffered slice, one barrier a tile).
+// Rows k0 .. k0 + R_STEP - 1 of a strip for a lane on diagonal d: bit k set
+// where row k0 + k exists and its column lies in the square.
+__device__ __forceinline__ uint32_t step_ok(const Strip &t, int k0, int d) {
+  const int i0 = t.r0 + k0;
+  int lo = -(i0 + d), hi = t.L - (i0 + d);                 // columns 0 .. L - 1
+  lo = lo < 0 ? 0 : (lo > R_STEP ? R_STEP : lo);
+  const int left = t.rows - k0 < R_STEP ? t.rows - k0 : R_STEP;
+  hi = hi < 0 ? 0 : (hi > left ? left : hi);
+  return hi > lo ? ((1u << hi) - 1u) & ~((1u << lo) - 1u) : 0u;
+}
+
+// log2(1 + y) of a 32-bit gap.
+__device__ __forceinline__ float fn_lg2_32(uint32_t y) {
+  return __builtin_amdgcn_logf(1.0f + (float)y);
+}
+
+// What the heads share of R_STEP rows from k0 on: time bucket and
+// log2(1 + |dt|) of this lane's elements.  `near`: the strip's timestamps lie
+// within 2^30 of the sequence's first, and `cols` (LDS) and `row` (lane k: row
+// k) hold the differences; else the 64-bit rule on the timestamps themselves.
+template <bool TIME, bool FN>
+__device__ __forceinline__ void step_keys(const RabArgs &a, const Strip &t, int k0, int lane,
+                                          bool near, const int32_t *cols, int32_t row,
+                                          int (&bk)[R_STEP], float (&l2)[R_STEP]) {
+  if (near) {
+#pragma unroll
+    for (int k = 0; k < R_STEP; ++k) {
+      const int32_t ri = __builtin_amdgcn_readlane(row, k0 + k), cj = cols[k0 + k + lane];
+      const uint32_t y = ri > cj ? (uint32_t)(ri - cj) : (uint32_t)(cj - ri);
+      if (TIME) bk[k] = time_bucket_u32(y, a.nb);
+      if (FN) l2[k] = fn_lg2_32(y);
+    }
+  } else {
+#pragma unroll 1
+    for (int k = 0; k < R_STEP; ++k) {
+      const int i = t.r0 + k0 + k, j = i + t.d0 + lane;
+      const int64_t *ts = a.ts + t.start;
+      const int64_t dt = ts[i < t.L ? i : t.L - 1] - ts[j < 0 ? 0 : (j < t.L ? j : t.L - 1)];
+      const int bv = TIME ? time_bucket32(dt, a.nb) : 0;
+      const float lv = FN ? fn_lg2(dt) : 0.0f;
+#pragma unroll
+      for (int x = 0; x < R_STEP; ++x) {
+        if (TIME) bk[x] = x == k ? bv : bk[x];
+        if (FN) l2[x] = x == k ? lv : l2[x];
+      }
+    }
+  }
+}
+
+// Dynamic LDS: every head's time table ([H][nb]) when time_w is given.
 template <bool POS, bool TIME, bool FN>
-__global__ void __launch_bounds__(RT) rab_fwd_kernel(RabArgs a) {
-  __shared__ float pos[2][2 * TILE];
+__global__ void __launch_bounds__(R_FWD_THREADS) rab_fwd_kernel(RabArgs a) {
+  __shared__ int64_t s_items[R_LDS_SEQS + 1];
   extern __shared__ float ttab[];
-  Band bd;
-  if (!band_of(a, bd)) return;
-  const int h = blockIdx.z, tid = threadIdx.x;
-  const int span = 2 * a.N - 1;
-  float fa = 0.0f, fb = 0.0f;
-  if (FN) { fa = a.time_fn[2 * h]; fb = a.time_fn[2 * h + 1]; }
+  constexpr int WAVES = R_FWD_THREADS / 64;
+  const int tid = threadIdx.x, lane = tid & 63;
   if (TIME)
-    for (int x = tid; x < a.nb; x += RT) ttab[x] = a.time_w[(int64_t)h * a.nb + x];
-  // slice entry x of tile jt: offset j - i = (jt - it) 64 + x - 63
-  auto pos_at = [&](int jt) {
-    const int m = (jt - bd.it) * TILE + tid - (TILE - 1) + a.N - 1;
-    return (tid < 2 * TILE - 1 && m >= 0 && m < span) ? a.pos_w[(int64_t)h * span + m] : 0.0f;
-  };
-  auto ts_at = [&](int jt) {
-    const int j = jt * TILE + bd.c;
-    return (TIME || FN) ? a.ts[bd.start + (j < bd.L ? j : bd.L - 1)] : (int64_t)0;
-  };
-  float pv = POS ? pos_at(0) : 0.0f;
-  int64_t ts_j = ts_at(0);
-  // rows of this thread past the sequence (band of the last tile) store
-  // nothing; columns are checked per tile
-  const int rows_ok = min(ROWS_PER_THREAD, (bd.L - bd.it * TILE - bd.rg + 3) / 4);
-  float *plane = a.rab + (int64_t)h * a.total_square + bd.base +
-                 (int64_t)(bd.it * TILE + bd.rg) * bd.L + bd.c;
-  for (int jt = 0; jt < bd.nt; ++jt) {
-    float *pb = pos[jt & 1];
-    if (POS && tid < 2 * TILE - 1) pb[tid] = pv;
-    __syncthreads();
-    const int64_t ts_cur = ts_j;
-    if (jt + 1 < bd.nt) {
-      if (POS) pv = pos_at(jt + 1);
-      ts_j = ts_at(jt + 1);
-    }
-    if (jt * TILE + bd.c >= bd.L) continue;
-    float *col = plane + jt * TILE;
+    for (int x = tid; x < a.H * a.nb; x += R_FWD_THREADS) ttab[x] = a.time_w[x];
+  const int64_t *items = stage_items(a, s_items, tid, R_FWD_THREADS);
+  if (TIME) __syncthreads();
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t n_items = items[a.B], span = 2 * (int64_t)a.N - 1;
+  // one eighth of the items to each XCD (work-group i runs on XCD i % 8), so
+  // that the lines neighbouring items share are completed in one L2
+  const int64_t share = (n_items + 8 * WAVES - 1) / (8 * WAVES) * WAVES;
+  const int64_t first = (blockIdx.x & 7) * share;
+  const int64_t end = first + share < n_items ? first + share : n_items;
+  for (int64_t item = first + (int64_t)(blockIdx.x >> 3) * WAVES + w; item < end;
+       item += (int64_t)(gridDim.x >> 3) * WAVES) {
+    const int b = seq_of_item(a, items, item);
+    int64_t start;
+    int L;
+    seq_of(a, b, start, L);
+    const int64_t base = a.sq[b], square = (int64_t)L * L;
+    if (base < 0 || base + square > a.total_square) continue;
+    const int64_t e0 = (item - items[b]) * R_FLAT;              // < 2^32
+    const int left = (int)(square - e0 < R_FLAT ? square - e0 : R_FLAT);
+    const int i0 = (int)((uint32_t)e0 / (uint32_t)L), j0 = (int)(e0 - (int64_t)i0 * L);
+    const float rl = 1.0f / (float)L;
+    // row and column of this lane's elements, then what of them every head
+    // shares: bucket (8 bits) and position index (17 bits), log2(1 + |dt|)
+    uint32_t key[R_FSTEP];
+    float l2[R_FSTEP];
 #pragma unroll
-    for (int k = 0; k < ROWS_PER_THREAD; ++k) {
-      if (k < rows_ok) {
-        const int r = bd.rg + 4 * k;
-        float v = 0.0f;
-        if (POS) v += pb[bd.c - r + TILE - 1];
-        if (TIME || FN) {
-          const int64_t dt = bd.ts_i[k] - ts_cur;
-          if (TIME) v += ttab[bucket_fast(dt, a.nb)];
-          if (FN) v += fa * __builtin_amdgcn_exp2f(-fb * fn_lg2(dt));
-        }
-        col[(int64_t)(4 * k) * bd.L] = v;
+    for (int k = 0; k < R_FSTEP; ++k) {
+      const int x = j0 + 64 * k + lane;                         // < L + 1024 < 2^17
+      int q = (int)((float)x * rl);                             // x / L, off by one at most
+      int j = x - q * L;
+      if (j < 0) { j += L; --q; }
+      if (j >= L) { j -= L; ++q; }
+      int i = i0 + q;
+      i = i < L ? i : L - 1;                                    // past the square: not stored
+      key[k] = (uint32_t)(j - i + a.N - 1) << 8;
+      if (TIME || FN) {
+        const int64_t dt = a.ts[start + i] - a.ts[start + j];
+        if (TIME) key[k] |= (uint32_t)time_bucket32(dt, a.nb);
+        if (FN) l2[k] = fn_lg2(dt);
       }
+    }
+    float *out = a.rab + base + e0;
+    for (int h = 0; h < a.H; ++h) {
+      const float *tab = TIME ? ttab + h * a.nb : nullptr;
+      const float *pw = POS ? a.pos_w + h * span : nullptr;
+      const float fa = FN ? a.time_fn[2 * h] : 0.0f, fb = FN ? a.time_fn[2 * h + 1] : 0.0f;
+      float v[R_FSTEP];
+#pragma unroll
+      for (int k = 0; k < R_FSTEP; ++k) v[k] = POS ? pw[key[k] >> 8] : 0.0f;
+#pragma unroll
+      for (int k = 0; k < R_FSTEP; ++k) {
+        if (TIME) v[k] += tab[key[k] & 255u];
+        if (FN) v[k] += fa * __builtin_amdgcn_exp2f(-fb * l2[k]);
+      }
+      if (left == R_FLAT) {
+#pragma unroll
+        for (int k = 0; k < R_FSTEP; ++k) out[64 * k + lane] = v[k];
+      } else {
+#pragma unroll
+        for (int k = 0; k < R_FSTEP; ++k)
+          if (64 * k + lane < left) out[64 * k + lane] = v[k];
+      }
+      out += a.total_square;
     }
   }
 }
 
-// Backward: dynamic LDS = the head's [nb] fixed-point time histogram (if
-// time_w).
-template <bool POS, bool TIME, bool FN>
-__global__ void __launch_bounds__(RT) rab_bwd_kernel(RabArgs a) {
-  __shared__ unsigned long long win[2 * TILE];
-  __shared__ double red[2][RT];
+// Sum of a double over the wave (the same order every time).
+__device__ __forceinline__ double wave_sum_d(double x) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m, 64);
+  return x;
+}
+
+// Work-group of heads h0 .. h0 + HB - 1.  Dynamic LDS: their time histograms,
+// [HB][nb][copies] (if time_w).
+template <bool POS, bool TIME, bool FN, int HB>
+__global__ void __launch_bounds__(R_BWD_THREADS, 4) rab_bwd_kernel(RabArgs a) {
+  constexpr int WAVES = R_BWD_THREADS / 64;
+  __shared__ int64_t s_items[R_LDS_SEQS + 1];
+  __shared__ double red[2 * HB][WAVES];
+  __shared__ int32_t s_cols[WAVES][64 + R_ROWS];
   extern __shared__ unsigned long long hist[];
-  Band bd;
-  if (!band_of(a, bd)) return;
-  const int tid = threadIdx.x;
-  const int span = 2 * a.N - 1;
-  for (int x = tid; x < 2 * TILE; x += RT) win[x] = 0;
+  const int tid = threadIdx.x, lane = tid & 63;
   if (TIME)
-    for (int x = tid; x < a.nb; x += RT) hist[x] = 0;
+    for (int x = tid; x < HB * a.nb * a.copies; x += R_BWD_THREADS) hist[x] = 0;
+  const int64_t *items = stage_items(a, s_items, tid, R_BWD_THREADS);
   __syncthreads();
-  const int rows_ok = min(ROWS_PER_THREAD, (bd.L - bd.it * TILE - bd.rg + 3) / 4);
-  constexpr float LN2 = 0.693147180559945309f;
-  {
-    const int h = blockIdx.z;
-    // per-lane sums in double: the incoming gradient has both signs, and
-    // its long sums cancel
-    float fa = 0.0f, fb = 0.0f;
-    double s_a = 0.0, s_b = 0.0;
-    if (FN) { fa = a.time_fn[2 * h]; fb = a.time_fn[2 * h + 1]; }
-    const float *plane = a.d_rab + (int64_t)h * a.total_square + bd.base +
-                         (int64_t)(bd.it * TILE + bd.rg) * bd.L + bd.c;
-    unsigned long long *hh = hist;
-    for (int jt = 0; jt < bd.nt; ++jt) {
-      const int j = jt * TILE + bd.c;
-      if (j < bd.L) {
-        const int64_t ts_j = (TIME || FN) ? a.ts[bd.start + j] : 0;
-        const float *col = plane + jt * TILE;
-        double run = 0.0;
-        int cur = -1;
-        float gv[ROWS_PER_THREAD];
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int groups = a.H / HB;
+  const int h0 = blockIdx.x % groups * HB, wg = blockIdx.x / groups, nwg = gridDim.x / groups;
+  const int64_t n_items = items[a.B], span = 2 * (int64_t)a.N - 1;
+  unsigned long long *mine = hist + (lane & (a.copies - 1));
+  int32_t *cols = s_cols[w];
+  float fb[HB];
+  double s_a[HB], s_b[HB];              // sums of d g and d g log2(1 + |dt|)
+  double run[HB];                       // this lane's run of bucket `cur`
 #pragma unroll
-        for (int k = 0; k < ROWS_PER_THREAD; ++k)
-          gv[k] = k < rows_ok ? col[(int64_t)(4 * k) * bd.L] : 0.0f;
+  for (int u = 0; u < HB; ++u) {
+    fb[u] = FN ? a.time_fn[2 * (h0 + u) + 1] : 0.0f;
+    s_a[u] = s_b[u] = run[u] = 0.0;
+  }
+  int cur = 0;
+  auto flush = [&]() {
 #pragma unroll
-        for (int k = 0; k < ROWS_PER_THREAD; ++k) {
-          if (k >= rows_ok) continue;
-          const float g = gv[k];
-          if (POS) atomicAdd(&win[bd.c - (bd.rg + 4 * k) + TILE - 1], to_fix(g));
-          const int64_t dt = bd.ts_i[k] - ts_j;
-          if (TIME) {
-            const int bk = bucket_fast(dt, a.nb);
-            if (bk != cur && cur >= 0) atomicAdd(&hh[cur], fix_d(run));
-            run = bk != cur ? (double)g : run + g;
-            cur = bk;
-          }
+    for (int u = 0; u < HB; ++u) {
+      if (run[u] != 0.0) atomicAdd(&mine[(u * a.nb + cur) * a.copies], fix_d(run[u]));
+      run[u] = 0.0;
+    }
+  };
+  for (int64_t item = (int64_t)wg * WAVES + w; item < n_items; item += (int64_t)nwg * WAVES) {
+    Strip t;
+    if (!strip_of(a, items, item, t)) continue;
+    const int d = t.d0 + lane;
+    int32_t row = 0;
+    bool near = true;
+    if (TIME || FN) {
+      const int64_t *ts = a.ts + t.start;
+      const int64_t ts0 = ts[0];
+      auto rel = [&](int x) {
+        const int64_t r = ts[x < 0 ? 0 : (x < t.L ? x : t.L - 1)] - ts0;
+        near &= r < R_NEAR && r > -R_NEAR;
+        return (int32_t)r;
+      };
+      row = rel(t.r0 + (lane & (R_ROWS - 1)));
+      const int c0 = t.r0 + t.d0;
+      cols[lane] = rel(c0 + lane);
+      if (lane < R_ROWS) cols[64 + lane] = rel(c0 + 64 + lane);
+      near = __all(near);
+      wave_lds_fence();
+    }
+    double diag[HB];
+#pragma unroll
+    for (int u = 0; u < HB; ++u) diag[u] = 0.0;
+    for (int k0 = 0; k0 < t.rows; k0 += R_STEP) {
+      const uint32_t ok = step_ok(t, k0, d);
+      if (!__any(ok != 0)) continue;
+      const float *in = a.d_rab + (int64_t)h0 * a.total_square + t.base +
+                        (int64_t)(t.r0 + k0) * (t.L + 1) + t.d0;
+      float g[HB][R_STEP];
+      const bool full = __all(ok == (1u << R_STEP) - 1u);
+#pragma unroll
+      for (int u = 0; u < HB; ++u) {
+        if (full) {
+#pragma unroll
+          for (int k = 0; k < R_STEP; ++k) g[u][k] = in[(uint32_t)(k * (t.L + 1) + lane)];
+        } else {
+#pragma unroll
+          for (int k = 0; k < R_STEP; ++k)
+            g[u][k] = (ok >> k) & 1 ? in[(uint32_t)(k * (t.L + 1) + lane)] : 0.0f;
+        }
+        in += a.total_square;
+      }
+      int bk[R_STEP];
+      float l2[R_STEP];
+      if (TIME || FN) step_keys<TIME, FN>(a, t, k0, lane, near, cols, row, bk, l2);
+#pragma unroll
+      for (int k = 0; k < R_STEP; ++k) {
+        if (TIME && ((ok >> k) & 1) && bk[k] != cur) {
+          flush();
+          cur = bk[k];
+        }
+#pragma unroll
+        for (int u = 0; u < HB; ++u) {
+          const double gd = (double)g[u][k];
+          if (POS) diag[u] += gd;
+          if (TIME) run[u] += gd;
           if (FN) {
-            const float l2 = fn_lg2(dt);
-            const float e = __builtin_amdgcn_exp2f(-fb * l2);
-            s_a += (double)(g * e);
-            s_b -= (double)(g * fa * e) * (double)(l2 * LN2);
+            const double ge = (double)(g[u][k] * __builtin_amdgcn_exp2f(-fb[u] * l2[k]));
+            s_a[u] += ge;
+            s_b[u] = __builtin_fma(ge, (double)l2[k], s_b[u]);
           }
         }
-        if (TIME && cur >= 0) atomicAdd(&hh[cur], fix_d(run));
-      }
-      if (POS) {
-        // the tile's 127 diagonal sums go to the table, the window is cleared
-        __syncthreads();
-        if (tid < 2 * TILE - 1) {
-          const unsigned long long v = win[tid];
-          const int m = (jt - bd.it) * TILE + tid - (TILE - 1) + a.N - 1;
-          if (v != 0 && m >= 0 && m < span) atomicAdd(&a.fix_pos[(int64_t)h * span + m], v);
-          win[tid] = 0;
-        }
-        __syncthreads();
       }
     }
-    if (FN) {
-      // work-group sums of the two parameter gradients, fixed order
-      red[0][tid] = s_a;
-      red[1][tid] = s_b;
-      __syncthreads();
-      if (tid < 2) {
-        double t = 0.0;
-        for (int x = 0; x < RT; ++x) t += red[tid][x];
-        atomicAdd(&a.fix_fn[2 * h + tid], fix_d(t));
-      }
-      __syncthreads();
+    if (POS) {
+#pragma unroll
+      for (int u = 0; u < HB; ++u)
+        if (diag[u] != 0.0)
+          atomicAdd(&a.fix_pos[(int64_t)(h0 + u) * span + d + a.N - 1], fix_d(diag[u]));
     }
+    wave_lds_fence();
+  }
+  if (TIME) flush();
+  if (FN) {
+#pragma unroll
+    for (int u = 0; u < HB; ++u) {
+      const double x = wave_sum_d(s_a[u]), y = wave_sum_d(s_b[u]);
+      if (lane == 0) { red[2 * u][w] = x; red[2 * u + 1][w] = y; }
+    }
+  }
+  __syncthreads();
+  if (FN && tid < 2 * HB) {
+    double s = 0.0;
+    for (int x = 0; x < WAVES; ++x) s += red[tid][x];
+    // d of the exponent: -a ln(1 + |dt|) = -a ln 2 log2(1 + |dt|)
+    if (tid & 1) s *= -(double)a.time_fn[2 * h0 + tid - 1] * TABLE_UNIT;
+    if (s != 0.0) atomicAdd(&a.fix_fn[2 * h0 + tid], fix_d(s));
   }
   if (TIME) {
-    __syncthreads();
-    for (int x = tid; x < a.nb; x += RT)
-      if (hist[x] != 0) atomicAdd(&a.fix_time[(int64_t)blockIdx.z * a.nb + x], hist[x]);
+    for (int x = tid; x < HB * a.nb; x += R_BWD_THREADS) {
+      unsigned long long s = 0;
+      for (int c = 0; c < a.copies; ++c) s += hist[x * a.copies + ((c + x) & (a.copies - 1))];
+      if (s != 0) atomicAdd(&a.fix_time[(int64_t)h0 * a.nb + x], s);
+    }
+  }
+}
+
+// The table sums as float, each table into its own output.
+__global__ void rab_tables_out_kernel(RabArgs a, float *d_pos, float *d_time, float *d_fn) {
+  const int64_t n_pos = d_pos ? (int64_t)a.H * (2 * (int64_t)a.N - 1) : 0;
+  const int64_t n_time = d_time ? (int64_t)a.H * a.nb : 0, n_fn = d_fn ? 2 * (int64_t)a.H : 0;
+  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n_pos + n_time + n_fn;
+       x += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t y = x - n_pos, z = y - n_time;
+    const unsigned long long *src = x < n_pos ? a.fix_pos + x : y < n_time ? a.fix_time + y
+                                                                           : a.fix_fn + z;
+    float *dst = x < n_pos ? d_pos + x : y < n_time ? d_time + y : d_fn + z;
+    *dst = (float)((double)(long long)*src * (1.0 / FIX_ONE));
   }
 }
 
@@ -318,7 +499,7 @@ int check_rab(const int64_t *off, int32_t B, int32_t N, int32_t H, int64_t T,
 }
 
 struct RabLayout {
-  size_t sq, fpos, ftime, ffn, total;
+  size_t sq, items, fpos, ftime, ffn, total;
 };
 
 RabLayout rab_layout(int32_t B, int32_t N, int32_t H, const hstu_rab_params *rp) {
@@ -326,6 +507,7 @@ RabLayout rab_layout(int32_t B, int32_t N, int32_t H, const hstu_rab_params *rp)
   size_t o = 0;
   auto take = [&](size_t bytes) { const size_t at = o; o = align_up(o + bytes); return at; };
   L.sq = take(sizeof(int64_t) * ((size_t)B + 1));
+  L.items = take(sizeof(int64_t) * ((size_t)B + 1));
   L.fpos = rp->pos_w ? take(8 * (size_t)H * (2 * (size_t)N - 1)) : 0;
   L.ftime = rp->time_w ? take(8 * (size_t)H * rp->num_buckets) : 0;
   L.ffn = rp->time_fn ? take(8 * 2 * (size_t)H) : 0;
@@ -339,6 +521,7 @@ RabArgs rab_args(const int64_t *off, int32_t B, int32_t N, int32_t H, int64_t T,
   RabArgs a{};
   a.off = off;
   a.sq = (int64_t *)(ws + L.sq);
+  a.items = (int64_t *)(ws + L.items);
   a.pos_w = rp->pos_w;
   a.time_w = rp->time_w;
   a.time_fn = rp->time_fn;
@@ -346,6 +529,10 @@ RabArgs rab_args(const int64_t *off, int32_t B, int32_t N, int32_t H, int64_t T,
   a.fix_pos = rp->pos_w ? (unsigned long long *)(ws + L.fpos) : nullptr;
   a.fix_time = rp->time_w ? (unsigned long long *)(ws + L.ftime) : nullptr;
   a.fix_fn = rp->time_fn ? (unsigned long long *)(ws + L.ffn) : nullptr;
+  // the sums' regions follow each other (gaps and all) up to the layout's end
+  const size_t first = rp->pos_w ? L.fpos : rp->time_w ? L.ftime : rp->time_fn ? L.ffn : L.total;
+  a.fix = (unsigned long long *)(ws + first);
+  a.n_fix = (int64_t)((L.total - first) / 8);
   a.T = T;
   a.total_square = total_square;
   a.B = B;
@@ -353,6 +540,46 @@ RabArgs rab_args(const int64_t *off, int32_t B, int32_t N, int32_t H, int64_t T,
   a.H = H;
   a.nb = rp->time_w ? rp->num_buckets : 0;
   return a;
+}
+
+int rab_cus() {
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  return device_info(dev).num_cu;
+}
+
+// Work-groups of `waves` waves for a batch: `per_cu` on every compute unit,
+// fewer where the batch has fewer items (about one per 1024 elements of a
+// head, and at least one per sequence).
+int rab_grid(const RabArgs &a, int waves, int per_cu) {
+  const int64_t items = a.total_square / 1024 + 2 * (int64_t)a.B;
+  return (int)std::max<int64_t>(
+      1, std::min<int64_t>((int64_t)per_cu * rab_cus(), (items + waves - 1) / waves));
+}
+
+template <int HB>
+void launch_rab_bwd_t(RabArgs a, const hstu_rab_params *rp, hipStream_t s) {
+  const bool P = rp->pos_w, Tm = rp->time_w, F = rp->time_fn;
+  auto kfn = P ? (Tm ? (F ? rab_bwd_kernel<true, true, true, HB>
+                          : rab_bwd_kernel<true, true, false, HB>)
+                     : (F ? rab_bwd_kernel<true, false, true, HB>
+                          : rab_bwd_kernel<true, false, false, HB>))
+               : (Tm ? (F ? rab_bwd_kernel<false, true, true, HB>
+                          : rab_bwd_kernel<false, true, false, HB>)
+                     : (F ? rab_bwd_kernel<false, false, true, HB>
+                          : rab_bwd_kernel<false, false, false, HB>));
+  a.copies = 64;
+  while ((int64_t)a.copies * a.nb * HB > R_HIST) a.copies >>= 1;
+  const size_t dyn = rp->time_w ? 8 * (size_t)a.copies * a.nb * HB : 0;
+  const int groups = a.H / HB;
+  const int per_group = std::min(rab_grid(a, R_BWD_THREADS / 64, 2),
+                                 std::max(1, 2 * rab_cus() / groups));
+  hipLaunchKernelGGL(kfn, dim3((unsigned)(groups * per_group)), dim3(R_BWD_THREADS), dyn, s, a);
+}
+
+void launch_rab_bwd(const RabArgs &a, const hstu_rab_params *rp, hipStream_t s) {
+  if (a.H % 2 == 0) launch_rab_bwd_t<2>(a, rp, s);
+  else launch_rab_bwd_t<1>(a, rp, s);
 }
 
 }  // namespace
@@ -384,15 +611,15 @@ extern "C" int hstu_jagged_rab_fwd(const int64_t *seq_offsets, int32_t B, int32_
                        (char *)workspace, L);
   a.rab = rab;
   prof::Scope ps("rab_fwd", s);
-  hipLaunchKernelGGL(rab_sq_kernel, dim3(1), dim3(1024), 0, s, a);
+  hipLaunchKernelGGL(rab_scan_kernel, dim3(1), dim3(R_SCAN_THREADS), 0, s, a);
   const bool P = rp->pos_w, Tm = rp->time_w, F = rp->time_fn;
   auto kfn = P ? (Tm ? (F ? rab_fwd_kernel<true, true, true> : rab_fwd_kernel<true, true, false>)
                      : (F ? rab_fwd_kernel<true, false, true> : rab_fwd_kernel<true, false, false>))
                : (Tm ? (F ? rab_fwd_kernel<false, true, true> : rab_fwd_kernel<false, true, false>)
                      : (F ? rab_fwd_kernel<false, false, true>
                           : rab_fwd_kernel<false, false, false>));
-  hipLaunchKernelGGL(kfn, dim3(B, (max_len + TILE - 1) / TILE, H), dim3(RT),
-                     rp->time_w ? sizeof(float) * (size_t)rp->num_buckets : 0, s, a);
+  hipLaunchKernelGGL(kfn, dim3((rab_grid(a, R_FWD_THREADS / 64, 8) + 7) / 8 * 8), dim3(R_FWD_THREADS),
+                     rp->time_w ? sizeof(float) * (size_t)H * rp->num_buckets : 0, s, a);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? HSTU_OK : hip_fail(e, "rab forward launch");
 }
@@ -417,30 +644,20 @@ extern "C" int hstu_jagged_rab_bwd(const int64_t *seq_offsets, int32_t B, int32_
   const int64_t n_pos = (int64_t)H * (2 * (int64_t)max_len - 1);
   const int64_t n_time = rp->time_w ? (int64_t)H * rp->num_buckets : 0;
   prof::Scope ps("rab_bwd", s);
-  if (a.fix_pos) hipLaunchKernelGGL(rab_zero_kernel, dim3(64), dim3(256), 0, s, a.fix_pos, n_pos);
-  if (a.fix_time) hipLaunchKernelGGL(rab_zero_kernel, dim3(8), dim3(256), 0, s, a.fix_time, n_time);
-  if (a.fix_fn) hipLaunchKernelGGL(rab_zero_kernel, dim3(1), dim3(256), 0, s, a.fix_fn,
-                                   (int64_t)2 * H);
-  if (B > 0 && total_square > 0) {
-    hipLaunchKernelGGL(rab_sq_kernel, dim3(1), dim3(1024), 0, s, a);
-    const size_t dyn = rp->time_w ? 8 * (size_t)rp->num_buckets : 0;
-    const bool P = rp->pos_w, Tm = rp->time_w, F = rp->time_fn;
-    auto kfn =
-        P ? (Tm ? (F ? rab_bwd_kernel<true, true, true> : rab_bwd_kernel<true, true, false>)
-                : (F ? rab_bwd_kernel<true, false, true> : rab_bwd_kernel<true, false, false>))
-          : (Tm ? (F ? rab_bwd_kernel<false, true, true> : rab_bwd_kernel<false, true, false>)
-                : (F ? rab_bwd_kernel<false, false, true> : rab_bwd_kernel<false, false, false>));
-    hipLaunchKernelGGL(kfn, dim3(B, (max_len + TILE - 1) / TILE, H), dim3(RT), dyn, s, a);
+  const bool any = B > 0 && total_square > 0;
+  if (!any) a.B = 0;
+  const int64_t zero_blocks = std::min<int64_t>(256, (a.n_fix + R_SCAN_THREADS - 1) / R_SCAN_THREADS);
+  hipLaunchKernelGGL(rab_scan_kernel, dim3((unsigned)(1 + zero_blocks)), dim3(R_SCAN_THREADS), 0,
+                     s, a);
+  if (any) {
+    launch_rab_bwd(a, rp, s);
   }
-  if (a.fix_pos)
-    hipLaunchKernelGGL(rab_fix_to_float_kernel, dim3(64), dim3(256), 0, s, a.fix_pos, d_pos_w,
-                       n_pos);
-  if (a.fix_time)
-    hipLaunchKernelGGL(rab_fix_to_float_kernel, dim3(8), dim3(256), 0, s, a.fix_time, d_time_w,
-                       n_time);
-  if (a.fix_fn)
-    hipLaunchKernelGGL(rab_fix_to_float_kernel, dim3(1), dim3(256), 0, s, a.fix_fn, d_time_fn,
-                       (int64_t)2 * H);
+  const int64_t n_out = (d_pos_w && a.fix_pos ? n_pos : 0) + n_time + (a.fix_fn ? 2 * H : 0);
+  if (n_out > 0)
+    hipLaunchKernelGGL(rab_tables_out_kernel,
+                       dim3((unsigned)std::min<int64_t>(256, (n_out + 255) / 256)), dim3(256), 0,
+                       s, a, a.fix_pos ? d_pos_w : nullptr, a.fix_time ? d_time_w : nullptr,
+                       a.fix_fn ? d_time_fn : nullptr);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? HSTU_OK : hip_fail(e, "rab backward launch");
 }

@@ -83,3 +83,17 @@ def test_workload2_full():
     w = inputs.workload(2)
     say(f"  rab workload 2 {w.name}: T={w.T}")
     run_case(w, seed=4)
+
+
+# either side of a 32-row item and of 64 diagonals, items whose last strip is
+# one diagonal wide, and enough sequences to leave the LDS prefix (1023)
+@pytest.mark.parametrize("lengths,H,nb", [
+    ([1, 31, 32, 33, 0, 34, 63, 64, 65, 95, 96, 97, 129, 160], 1, 128),
+    ([33, 2, 65], 3, 300),                  # fewer histogram counters a bucket
+    ([1 + (7 * b) % 40 for b in range(1100)], 1, 32),
+    ([515], 8, 128),
+])
+def test_edges(lengths, H, nb):
+    w = inputs.make_workload(lengths, H=H, d=64, N=max(lengths), seed=47, num_buckets=nb)
+    say(f"  rab edges {len(lengths)} sequences, H={H}, {nb} buckets")
+    run_case(w, seed=5)
