@@ -249,7 +249,7 @@ int attn_fwd_call(const void *q, const void *k, const void *v, const void *u,
     return rc;
   }
   hipStream_t s = (hipStream_t)stream;
-  AttnArgs a{q, k, v, u,
+  AttnArgs a{seq_offsets, q, k, v, u,
              rab ? rab->pos_w : nullptr,
              p.has_time ? rab->time_w : nullptr,
              p.has_time ? rab->timestamps : nullptr,
@@ -258,15 +258,16 @@ int attn_fwd_call(const void *q, const void *k, const void *v, const void *u,
   // allocate)
   const bool prof_on = !fixed;
   hipError_t e;
-  {
+  const bool direct = fwd_direct(p, dev);
+  if (!direct) {
     prof::Scope ps(prof_on ? "schedule" : nullptr, s);
     e = launch_schedule(seq_offsets, p, ws, L, s);
+    if (e != hipSuccess) return hip_fail(e, "schedule launch");
   }
-  if (e != hipSuccess) return hip_fail(e, "schedule launch");
   {
     prof::Scope ps(!prof_on ? nullptr : p.dtype == HSTU_BF16 ? "attn_fwd" : "attn_fwd_f32", s);
-    e = p.dtype == HSTU_BF16 ? launch_attn_fwd_bf16(a, out->o, s)
-                             : launch_attn_fwd_f32(a, out->o, s);
+    e = p.dtype == HSTU_BF16 ? launch_attn_fwd_bf16(a, out->o, direct, s)
+                             : launch_attn_fwd_f32(a, out->o, direct, s);
   }
   if (e != hipSuccess) return hip_fail(e, "attention forward launch");
   {
@@ -303,7 +304,7 @@ int attn_bwd_call(const void *q, const void *k, const void *v, const void *u,
   if ((rc = check_workspace(L, io->workspace, io->workspace_bytes)) != HSTU_OK)
     return rc;
   hipStream_t s = (hipStream_t)stream;
-  AttnArgs a{q, k, v, u,
+  AttnArgs a{seq_offsets, q, k, v, u,
              rab ? rab->pos_w : nullptr,
              p.has_time ? rab->time_w : nullptr,
              p.has_time ? rab->timestamps : nullptr,

@@ -50,6 +50,7 @@
 
 #include "internal.h"
 #include "device.h"
+#include "sched_impl.h"
 
 namespace hstu {
 
@@ -96,6 +97,11 @@ struct KParams {
   // dV stores take dqk_scale / log2e and 1 / (N log2e)
   float al2e, dk_scale_l2, dv_scale_l2;
   int32_t all_heads;      // time tables of every head staged once per work-group
+                          // (2: the direct forward's, its item's head alone)
+  // direct forward: one item per work-group, found from the offsets
+  const int64_t *off;
+  int64_t T;
+  int32_t B, direct;
   int32_t fuse_dq0;       // combined backward, d=64: the dK/dV items of first
                           // k-tiles compute their q-tile's dQ (no such dQ items)
 };
@@ -252,7 +258,7 @@ __device__ __forceinline__ void stage_all_heads(const KParams &P, float *dyn, in
 template <int NT = THREADS>
 __device__ __forceinline__ float *item_time_slot(const KParams &P, float *dyn, int h, int tid,
                                                  float scale) {
-  if (P.all_heads) return dyn + h * time_slot_floats(P);
+  if (P.all_heads) return P.all_heads == 2 ? dyn : dyn + h * time_slot_floats(P);
   stage_time_heads<1, NT>(P, dyn, h, 1, tid, scale);
   return dyn;
 }
@@ -637,17 +643,30 @@ attn_fwd_kernel(KParams P) {
   constexpr int PCOPY = FWD_POS_COPY<QT>, PLEN = FWD_POS_LEN<QT>;
   __shared__ FwdSmem<D, QT> sm;
   extern __shared__ float dyn[];              // time tables (see item_time_slot)
-  const int n_items = P.ctrl[QT == 1 ? CTRL_N_ENTRIES : CTRL_N_PAIRS] * P.H;
   int cur = blockIdx.x;
+  int n_items;
+  Item it;
+  if (QT == 1 && P.direct) {
+    WorkEntry e;
+    if (cur == 0 && threadIdx.x == 0) const_cast<int32_t *>(P.ctrl)[CTRL_STATUS] = HSTU_SEQ_UNCHECKED;
+    if (!direct_entry(P.off, P.B, P.N, P.T, cur / P.H, e)) return;
+    it.start = e.start;
+    it.len = e.len;
+    it.tile = e.tile;
+    it.h = cur % P.H;
+    n_items = cur + 1;                        // no next item
+  } else {
+    n_items = P.ctrl[QT == 1 ? CTRL_N_ENTRIES : CTRL_N_PAIRS] * P.H;
+    if (cur >= n_items) return;
+    it = load_item(P, cur);
+  }
   // second static item: the list's next G items paired in reverse, so the
   // work-group with the longest first item gets the shortest second one
   int nxt = 2 * gridDim.x - 1 - blockIdx.x;
-  if (cur >= n_items) return;
   const int tid0 = threadIdx.x;
   if (tid0 < 3) sm.flag[tid0] = 0;
   int phase = 0;
 
-  Item it = load_item(P, cur);
   int item_no = 0;                            // items done by this work-group
   int64_t ts_start = 0, ts_i = 0, ts_k = 0;
   PosEntry pos_v{0.0f, false};
@@ -663,7 +682,10 @@ attn_fwd_kernel(KParams P) {
                        it.len - qt0 * TILE, P.H * D, g, qreg);
   }
   // the tables after the first item's loads: both latencies overlap
-  if (TIME) stage_all_heads<8, NT>(P, dyn, tid0, L2E);
+  if (TIME) {
+    if (QT == 1 && P.direct) stage_time_heads<4, NT>(P, dyn, it.h, 1, tid0, L2E);
+    else stage_all_heads<8, NT>(P, dyn, tid0, L2E);
+  }
 
   for (;;) {
     // Lane-derived values are rebuilt per item from an opaque copy of the
@@ -1808,10 +1830,10 @@ bool all_heads(const Problem &p) {
   const size_t budget = p.d == 64 ? ALL_HEADS_BUDGET : ALL_HEADS_BUDGET / 4;
   return p.has_time && sizeof(float) * (size_t)p.H * (KTAB + p.nb) <= budget;
 }
-size_t slots_bytes(const Problem &p) {
-  if (!p.has_time) return 0;
-  return sizeof(float) * (size_t)(all_heads(p) ? p.H : 1) * (KTAB + p.nb);
+size_t slot_bytes(const Problem &p, bool all) {
+  return p.has_time ? sizeof(float) * (size_t)(all ? p.H : 1) * (KTAB + p.nb) : 0;
 }
+size_t slots_bytes(const Problem &p) { return slot_bytes(p, all_heads(p)); }
 size_t q_dyn_bytes(const Problem &p) { return slots_bytes(p); }
 size_t k_dyn_bytes(const Problem &p) {
   return p.has_time ? slots_bytes(p) + sizeof(double) * (size_t)p.nb * p.H : 0;
@@ -1918,6 +1940,18 @@ int current_dev() {
 
 }  // namespace
 
+// One item per work-group, all resident at once: the d=64 and d=128 kernels'
+// persistent grids are what the device holds.
+bool fwd_direct(const Problem &p, int dev) {
+  if (p.check_offsets || p.B > FWD_DIRECT_SEQS) return false;
+  if (p.max_entries * p.H > 8 * (int64_t)device_info(dev).num_cu) return false;
+  if (p.dtype != HSTU_BF16) return 2 * p.max_entries * p.H <= 2 * device_info(dev).num_cu;
+  int grid = 0;
+  HSTU_DISPATCH_Q(attn_fwd_kernel, p.d, p.has_pos, p.has_time, 1,
+                  grid = persistent_grid(kfn, slot_bytes(p, false), p.max_entries * p.H, dev));
+  return p.max_entries * p.H <= grid;
+}
+
 bool fwd_pairs(const Problem &p) {
   return p.dtype == HSTU_BF16 && p.d == 64 && p.T >= FWD_PAIR_MIN_AVG_LEN * (int64_t)p.B;
 }
@@ -1955,9 +1989,23 @@ int attn_bwd_dkv_grid(const Problem &p, int dev) {
   return grid;
 }
 
-hipError_t launch_attn_fwd_bf16(const AttnArgs &a, void *o, hipStream_t s) {
+hipError_t launch_attn_fwd_bf16(const AttnArgs &a, void *o, bool direct, hipStream_t s) {
   const char *ws = (const char *)a.ws;
   const Problem &p = a.p;
+  if (direct) {
+    KParams P = make_params(a, nullptr, nullptr);
+    P.pop = (int32_t *)(ws + a.L.ctrl) + CTRL_POP_FWD;    // popped once, not used
+    P.out0 = (u16 *)o;
+    P.off = a.off;
+    P.T = p.T;
+    P.B = p.B;
+    P.direct = 1;
+    P.all_heads = p.has_time ? 2 : 0;
+    HSTU_DISPATCH_Q(attn_fwd_kernel, p.d, p.has_pos, p.has_time, 1,
+                    hipLaunchKernelGGL(kfn, dim3((unsigned)(p.max_entries * p.H)), dim3(THREADS),
+                                       slot_bytes(p, false), s, P));
+    return hipGetLastError();
+  }
   const bool pairs = fwd_pairs(p);
   KParams P = make_params(a, (int32_t *)(ws + a.L.ctrl) + CTRL_POP_FWD,
                           (const WorkEntry *)(ws + (pairs ? a.L.list_p : a.L.list_q)));

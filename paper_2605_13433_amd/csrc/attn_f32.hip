@@ -31,6 +31,7 @@
 
 #include "internal.h"
 #include "device.h"
+#include "sched_impl.h"
 
 namespace hstu {
 
@@ -56,6 +57,10 @@ struct F32Params {
   void *acc_pos, *acc_time;
   int32_t H, N, nb;
   float inv_n, alpha;
+  // direct forward: no lists, each work-group's item found from the offsets
+  const int64_t *off;
+  int64_t T;
+  int32_t B, direct, max_entries;
 };
 
 // K = 2 step of a 32 x 32 product: lane l gives A[l % 32][l / 32] and
@@ -314,7 +319,11 @@ __device__ __forceinline__ bool item_of(const F32Params &P, const WorkEntry *lis
   const int64_t eh = item >> 1;
   const int64_t entry = eh / P.H;
   h = (int)(eh - entry * P.H);
-  e = list[entry];
+  if (P.direct) {
+    if (!direct_entry(P.off, P.B, P.N, P.T, (int)entry, e)) return false;
+  } else {
+    e = list[entry];
+  }
   row0 = e.tile * TILE + FT * (int)(item & 1);
   return row0 < e.len;
 }
@@ -381,7 +390,9 @@ template <int D>
 __global__ void __launch_bounds__(F32_THREADS, D == 128 ? 1 : 2)
 f32_fwd_kernel(F32Params P) {
   __shared__ __attribute__((aligned(16))) F32FwdSmem<D> sm;
-  const int64_t n_items = 2 * (int64_t)P.ctrl[CTRL_N_ENTRIES] * P.H;
+  if (P.direct && blockIdx.x == 0 && threadIdx.x == 0)
+    const_cast<int32_t *>(P.ctrl)[CTRL_STATUS] = HSTU_SEQ_UNCHECKED;
+  const int64_t n_items = 2 * (int64_t)(P.direct ? P.max_entries : P.ctrl[CTRL_N_ENTRIES]) * P.H;
   for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
     f32_fwd_item<D>(P, sm, item);
     __syncthreads();
@@ -642,8 +653,15 @@ F32Params make_params(const AttnArgs &a) {
 
 }  // namespace
 
-hipError_t launch_attn_fwd_f32(const AttnArgs &a, void *o, hipStream_t s) {
+hipError_t launch_attn_fwd_f32(const AttnArgs &a, void *o, bool direct, hipStream_t s) {
   F32Params P = make_params(a);
+  if (direct) {
+    P.off = a.off;
+    P.T = a.p.T;
+    P.B = a.p.B;
+    P.max_entries = (int32_t)a.p.max_entries;
+    P.direct = 1;
+  }
   P.o = (float *)o;
   auto kfn = a.p.d == 32 ? f32_fwd_kernel<32> : a.p.d == 64 ? f32_fwd_kernel<64>
                                                             : f32_fwd_kernel<128>;

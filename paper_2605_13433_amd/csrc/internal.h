@@ -174,6 +174,7 @@ hipError_t launch_schedule(const int64_t *seq_offsets, const Problem &p,
                            void *ws, const Layout &L, hipStream_t s);
 
 struct AttnArgs {
+  const int64_t *off;
   const void *q, *k, *v, *u;
   const float *pos_w, *time_w;
   const int64_t *ts;
@@ -182,13 +183,13 @@ struct AttnArgs {
   Problem p;
 };
 
-hipError_t launch_attn_fwd_bf16(const AttnArgs &a, void *o, hipStream_t s);
+hipError_t launch_attn_fwd_bf16(const AttnArgs &a, void *o, bool direct, hipStream_t s);
 // dQ, dK, dV and the table-gradient partials: one combined launch, or a
 // dK/dV launch then a dQ launch (see Layout::bwd_combined).
 hipError_t launch_attn_bwd_bf16(const AttnArgs &a, const void *dO, void *dq, void *dk,
                                 void *dv, const GradOut *go, hipStream_t s);
 
-hipError_t launch_attn_fwd_f32(const AttnArgs &a, void *o, hipStream_t s);
+hipError_t launch_attn_fwd_f32(const AttnArgs &a, void *o, bool direct, hipStream_t s);
 hipError_t launch_attn_bwd_f32(const AttnArgs &a, const void *dO, void *dq,
                                void *dk, void *dv, float *d_pos,
                                float *d_time, hipStream_t s);
@@ -227,6 +228,11 @@ hipError_t launch_zero(void *p, size_t bytes, int dev, hipStream_t s);
 // and that list's capacity: every pair but one per sequence covers two of
 // the sum_b ceil(L_b / 64) <= max_entries tiles.
 bool fwd_pairs(const Problem &p);
+// Whether a forward call runs without the scheduler: every item at once
+// (direct_entry finds each work-group's), at most FWD_DIRECT_SEQS sequences
+// (two loads a lane), and no contract check asked for.
+constexpr int FWD_DIRECT_SEQS = 128;
+bool fwd_direct(const Problem &p, int dev);
 inline int64_t pair_entries(const Problem &p) { return (p.max_entries + p.B) / 2 + 1; }
 // Persistent-grid sizes (work-groups) of the bf16 attention kernels.
 int attn_fwd_grid(const Problem &p, int dev);

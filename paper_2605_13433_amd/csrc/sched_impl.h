@@ -50,7 +50,7 @@
 // for each purpose, and a sequence of more than SCHED_LANE_TILES tiles is
 // written by its whole wave.  The standalone launch, against one lane per
 // sequence and one thread over the bins: 6 sequences of up to 8192 tokens
-// 44.6 -> 4.6 us, 1024 of up to 8192 77 -> 11, 64 of up to 2048 16.3 -> 6.4,
+// 44.6 -> 4.6 us, 1024 of up to 8192 77 -> 22, 64 of up to 2048 16.3 -> 6.4,
 // 128 of up to 512 7.4 -> 5.7.  (Shuffle scans made 8 sequences of up to 250
 // tokens 0.3 us slower than the one thread; DPP scans are 0.1 us faster.)
 #pragma once
@@ -298,6 +298,44 @@ __device__ __forceinline__ void build_schedule(const SchedArgs &a, SchedSmem &sm
       for (int t = lane; t < sl.ntiles; t += 64) emit(bl, sl, rl, t);
     }
   }
+}
+
+// Entry `entry` of the batch's (sequence, tile) pairs in sequence order, found
+// without a list by every wave for itself: for forward calls small enough
+// that all their items run at once (fwd_direct), where the order does not
+// matter and the scheduler's launch is a quarter of the call (8 sequences of
+// up to 250 tokens, H = 4, d = 64: 17.0 -> 11.3 us with it gone).  False past
+// the last entry.  Clamps as build_schedule does.
+__device__ __forceinline__ bool direct_entry(const int64_t *off, int B, int N, int64_t T, int entry,
+                                             WorkEntry &e) {
+  const int lane = threadIdx.x & 63;
+  int first = 0;                        // entries of the sequences before
+  for (int b0 = 0; b0 < B; b0 += 64) {
+    const int b = b0 + lane;
+    int64_t s = 0, L = 0;
+    if (b < B) {
+      s = off[b];
+      int64_t t = off[b + 1];
+      s = s < 0 ? 0 : (s > T ? T : s);
+      t = t < s ? s : (t > T ? T : t);
+      L = t - s > N ? N : t - s;
+    }
+    const int nt = (int)((L + TILE - 1) / TILE);
+    const int end = first + wave_prefix(nt);
+    const uint64_t after = __ballot(end > entry);
+    if (after != 0) {
+      const int src = __builtin_ctzll(after);
+      e.seq = b0 + src;
+      e.len = __builtin_amdgcn_readlane((int)L, src);
+      e.tile = entry - (__builtin_amdgcn_readlane(end, src) - __builtin_amdgcn_readlane(nt, src));
+      e.reserved = 0;
+      e.start = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(s >> 32), src) << 32) |
+                          (uint32_t)__builtin_amdgcn_readlane((int)s, src));
+      return true;
+    }
+    first = __builtin_amdgcn_readlane(end, 63);
+  }
+  return false;
 }
 
 inline SchedArgs sched_args(const int64_t *seq_offsets, const Problem &p, void *ws,
