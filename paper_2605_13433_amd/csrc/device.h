@@ -107,6 +107,18 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
+// Sum of x over this and the lower lanes: DPP shifts inside the rows of 16
+// lanes, then row broadcasts (a ds_bpermute per step costs an LDS round trip).
+__device__ __forceinline__ int32_t wave_prefix(int32_t x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);    // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);    // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);    // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);    // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);   // lane 15 of rows 0, 2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);   // lane 31
+  return x;
+}
+
 // Raw buffer loads: a resource over `bytes` bytes from `base` and a per-lane
 // byte offset; loads at or past `bytes` return 0.  The offset is a plain
 // 32-bit register, so a loop that moves the base keeps one register per load

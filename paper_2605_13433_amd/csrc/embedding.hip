@@ -11,17 +11,25 @@
 // ([T][F*D]) that a sequence model consumes, so no conversion pass follows.
 //
 // Backward: deterministic sparse gradient.  Each id becomes its global row
-// key (row_offsets[t] + id; invalid ids get a sentinel that sorts last); a
-// stable radix sort orders the positions by key; a head-flag scan numbers
-// the distinct rows; then fixed 32-position chunks of the sorted order sum
-// the output-gradient rows of each distinct key in position order, writing
-// rows that start and end inside a chunk directly and chunk-boundary pieces
-// as partials that a fix-up pass joins in chunk order.  Every sum has a
+// key (row_offsets[t] + id; invalid ids get a sentinel that sorts last; 32
+// bits while the rows fit, which halves what the sort moves); a stable radix
+// sort orders the positions by key; head counts per chunk number the distinct
+// rows; then fixed 32-position chunks of the sorted order sum the
+// output-gradient rows of each distinct key in position order, writing rows
+// that start and end inside a chunk directly and chunk-boundary pieces as
+// partials that are joined in chunk order (within a chunk work-group by
+// itself, across work-groups by a fix-up pass).  Every sum has a
 // fixed order, so the result is bitwise reproducible (no float atomics),
 // and a hot row that occurs thousands of times is summed by many chunks in
 // parallel instead of by one serial loop.
+//
+// Measured on 8 tables of 2^22 .. 2^7 rows, 77 971 ids each, D = 128, fp32:
+// backward 265 -> 215 us.  The chunk pass (131 us) reads 319 MB of gradients
+// just after the forward wrote as much: plain loads of those bytes take 66 us
+// from clean memory and 111-130 us behind 1 GiB of dirty lines, in sorted or
+// sequential order alike.  Sort passes 25 -> 15 us each, fix-up 29 -> 10 us, the
+// rows' numbering 17 -> 8 us.  Non-temporal forward stores changed nothing.
 #include <rocprim/device/device_radix_sort.hpp>
-#include <rocprim/device/device_scan.hpp>
 
 #include <algorithm>
 
@@ -38,6 +46,7 @@ constexpr int CHUNK = 32;           // sorted positions per backward chunk
 constexpr int MAX_TABLES = 1024;
 constexpr int BWD_UNROLL = 8;       // gradient rows in flight per thread
 constexpr int MAX_CPB = 16;         // backward chunks per work-group
+constexpr int FIX_UNROLL = 8;       // group pieces in flight per thread of the join
 
 // Threads per chunk and chunks per work-group of the backward chunk pass
 // for `cpr` 16-byte slices per row (host and device agree on this).
@@ -152,25 +161,41 @@ __global__ void __launch_bounds__(ET) emb_fwd_kernel(FwdArgs a) {
 }
 
 // ---------------------------------------------------------------- backward
+constexpr int HEAD_BLOCK = 4096;    // sorted positions per head-count block (128 chunks)
+// The blocks' head counts are summed by every chunk work-group for itself up
+// to this many (2 M positions), by a scan launch above.
+constexpr int HEAD_SUM_BLOCKS = 512;
+
+// State of a chunk, and of a group of chunks for the fix-up pass.
+enum : uint32_t {
+  CHUNK_INSIDE = 1,                 // all its positions belong to one row that began
+                                    // before it and goes on after it
+  CHUNK_STARTS = 2,                 // a row begins in it and goes on after it
+  CHUNK_HEAD = 4                    // its first row began before it
+};
+
+template <typename K>
 struct BwdArgs {
   const int64_t *ro, *io, *ids;
   const void *dout;
   float *grad;
   int64_t *unique_rows;
   int32_t *num_unique;
-  uint64_t *keys_in, *keys;
+  K *keys_in, *keys;
   uint32_t *pos_in, *pos;
-  uint32_t *flag, *runid;
-  uint32_t *run_start;               // [num_ids]: first sorted position of each row
-  uint32_t *last_valid;              // [1]: last sorted position with a valid key
-  float *part;                       // [nchunks][2][D]
-  uint64_t sentinel;                 // total_rows
+  uint32_t *chunk_heads;             // [nchunks]: distinct rows that begin in the chunk
+  uint32_t *block_heads;             // [nblocks]: in the block; scanned: before it
+  // per group of `cpb` chunks (a chunk work-group's)
+  uint32_t *state;                   // [ngroups]: CHUNK_* bits
+  float *part;                       // [ngroups][2][D]: first, last piece
+  K sentinel;                        // total_rows
   int64_t n, per_table;
-  int F, D, nchunks;
-  bool token;
+  int F, D, nchunks, nblocks, ngroups;
+  bool token, scanned;
 };
 
-__global__ void __launch_bounds__(ET) emb_keys_kernel(BwdArgs a) {
+template <typename K>
+__global__ void __launch_bounds__(ET) emb_keys_kernel(BwdArgs<K> a) {
   __shared__ int64_t s_io[MAX_TABLES + 1], s_ro[MAX_TABLES + 1];
   for (int i = threadIdx.x; i <= a.F; i += ET) {
     s_io[i] = a.io[i];
@@ -181,59 +206,152 @@ __global__ void __launch_bounds__(ET) emb_keys_kernel(BwdArgs a) {
   if (r >= a.n) return;
   const int t = table_at(a.token, s_io, a.F, r, a.per_table);
   const int64_t g = global_row(s_ro, t, a.ids[r], (int64_t)a.sentinel);
-  a.keys_in[r] = g >= 0 ? (uint64_t)g : a.sentinel;
+  a.keys_in[r] = g >= 0 ? (K)g : a.sentinel;
   a.pos_in[r] = (uint32_t)r;
 }
 
-__global__ void __launch_bounds__(ET) emb_heads_kernel(BwdArgs a) {
-  const int64_t p = (int64_t)blockIdx.x * ET + threadIdx.x;
-  if (p >= a.n) return;
-  const uint64_t k = a.keys[p];
-  a.flag[p] = (k != a.sentinel && (p == 0 || a.keys[p - 1] != k)) ? 1u : 0u;
-  if (k != a.sentinel && (p + 1 == a.n || a.keys[p + 1] == a.sentinel))
-    *a.last_valid = (uint32_t)p;
+// Whether a distinct row begins at sorted position p (< n).
+template <typename K>
+__device__ __forceinline__ bool head_at(const BwdArgs<K> &a, int64_t p) {
+  const K k = a.keys[p];
+  return k != a.sentinel && (p == 0 || a.keys[p - 1] != k);
+}
+
+// Rows that begin in each chunk and in each block of HEAD_BLOCK positions.
+template <typename K>
+__global__ void __launch_bounds__(ET) emb_heads_kernel(BwdArgs<K> a) {
+  constexpr int ROUNDS = HEAD_BLOCK / ET;
+  __shared__ uint32_t total;
+  const int lane = threadIdx.x & 63;
+  if (threadIdx.x == 0) total = 0;
+  __syncthreads();
+  const int64_t p0 = (int64_t)blockIdx.x * HEAD_BLOCK;
+  uint32_t mine = 0;
+#pragma unroll
+  for (int x = 0; x < ROUNDS; ++x) {
+    const int64_t p = p0 + x * ET + threadIdx.x;
+    const uint64_t heads = __ballot(p < a.n && head_at(a, p));
+    // a wave's 64 positions are two chunks
+    const uint32_t c = __popc((uint32_t)(lane < 32 ? heads : heads >> 32));
+    if ((lane & 31) == 0 && p < a.n) a.chunk_heads[p / CHUNK] = c;
+    mine += lane == 0 || lane == 32 ? c : 0u;
+  }
+  if (mine) atomicAdd(&total, mine);
+  __syncthreads();
+  if (threadIdx.x == 0) a.block_heads[blockIdx.x] = total;
+}
+
+// block_heads -> sums over the blocks before (many blocks only): one
+// work-group, a contiguous share of the blocks a thread.
+template <typename K>
+__global__ void __launch_bounds__(1024) emb_scan_kernel(BwdArgs<K> a) {
+  __shared__ uint32_t part[1024];
+  const int64_t per = (a.nblocks + 1023) / 1024, b0 = threadIdx.x * per;
+  const int64_t b1 = b0 + per < a.nblocks ? b0 + per : a.nblocks;
+  uint32_t s = 0;
+  for (int64_t b = b0; b < b1; ++b) s += a.block_heads[b];
+  part[threadIdx.x] = s;
+  __syncthreads();
+  uint32_t before = 0;
+  for (int x = 0; x < (int)threadIdx.x; ++x) before += part[x];
+  for (int64_t b = b0; b < b1; ++b) {
+    const uint32_t c = a.block_heads[b];
+    a.block_heads[b] = before;
+    before += c;
+  }
 }
 
 // Output-gradient element offset of chunk c of id position r.
-__device__ __forceinline__ int64_t dout_elem(const BwdArgs &a, uint32_t r, int c, int n_e) {
+template <typename K>
+__device__ __forceinline__ int64_t dout_elem(const BwdArgs<K> &a, uint32_t r, int c, int n_e) {
   if (!a.token) return (int64_t)r * a.D + c * n_e;
   const uint32_t t = r / (uint32_t)a.per_table;       // num_ids < 2^31
   return (int64_t)(r - t * (uint32_t)a.per_table) * ((int64_t)a.F * a.D) +
          (int64_t)t * a.D + c * n_e;
 }
 
+// NE floats to 16-byte aligned memory.
+template <int NE>
+__device__ __forceinline__ void store_slice(float *dst, const float (&acc)[NE]) {
+#pragma unroll
+  for (int e = 0; e < NE; e += 4)
+    *(float4 *)(dst + e) = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
+}
+
 // One chunk of CHUNK sorted positions per group of `tpc` threads; a thread
 // sums its 16-byte column slices over the chunk's pieces (runs of equal
-// key) in position order.
-template <typename T>
-__global__ void __launch_bounds__(ET) emb_chunk_kernel(BwdArgs a) {
+// key) in position order; the pieces that cross chunks are joined in chunk
+// order within the work-group, so that only what crosses work-groups is left
+// to the fix-up pass (a row of 15 891 positions: 62 pieces instead of 497).
+// Bound by the gradient rows' reads: everything the
+// loop needs besides them (keys, row offsets, the rows' ranks) is in LDS
+// before it, since a wait for any other load would also wait for the rows in
+// flight.
+template <typename T, typename K>
+__global__ void __launch_bounds__(ET) emb_chunk_kernel(BwdArgs<K> a) {
   constexpr int NE = Elt<T>::N;
   const int cpr = a.D / NE;
   const int tpc = chunk_tpc(cpr), cpb = chunk_cpb(cpr);
-  __shared__ uint64_t s_key[MAX_CPB * CHUNK];
-  __shared__ uint32_t s_pos[MAX_CPB * CHUNK];
-  const int g = threadIdx.x / tpc, lt = threadIdx.x % tpc;
-  const int64_t chunk = (int64_t)blockIdx.x * cpb + g;
+  __shared__ K s_key[MAX_CPB * CHUNK];
+  __shared__ int64_t s_row[MAX_CPB * CHUNK];           // element offset of the gradient row
+  __shared__ uint32_t s_rank[MAX_CPB * CHUNK];         // distinct rows up to the position
+  __shared__ uint32_t s_sum[ET / 64], s_wave[MAX_CPB * CHUNK / 64], s_state[MAX_CPB];
+  __shared__ float s_part[2][ET * NE];                 // cpb > 1: chunk g's pieces at g D
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int g = tid / tpc, lt = tid % tpc;
+  const int64_t chunk0 = (int64_t)blockIdx.x * cpb, chunk = chunk0 + g;
   const int64_t p0 = chunk * CHUNK;
-  // stage the keys and positions of this block's chunks
-  for (int i = threadIdx.x; i < cpb * CHUNK; i += ET) {
-    const int64_t p = (int64_t)blockIdx.x * cpb * CHUNK + i;
-    s_key[i] = p < a.n ? a.keys[p] : a.sentinel;
-    s_pos[i] = p < a.n ? a.pos[p] : 0u;
+  // stage the keys and rows of this block's chunks and number their heads
+  const int npos = cpb * CHUNK;                        // at most 2 a thread
+  for (int i = tid; i < (npos + 63) / 64 * 64; i += ET) {
+    const int64_t p = chunk0 * CHUNK + i;
+    const bool in = i < npos && p < a.n;
+    const bool head = in && head_at(a, p);
+    const uint64_t heads = __ballot(head);
+    if (i < npos) {
+      s_key[i] = in ? a.keys[p] : a.sentinel;
+      s_row[i] = in ? dout_elem(a, a.pos[p], 0, NE) : 0;
+      s_rank[i] = __popcll(heads & (~0ull >> (63 - lane)));      // heads up to this lane
+    }
+    if (lane == 0) s_wave[i / 64] = __popcll(heads);
   }
+  // distinct rows before the block's first position
+  const int64_t blk = chunk0 / (HEAD_BLOCK / CHUNK);
+  uint32_t before = 0;
+  if (a.scanned) before = tid == 0 ? a.block_heads[blk] : 0u;
+  else for (int64_t b = tid; b < blk; b += ET) before += a.block_heads[b];
+  for (int64_t c = blk * (HEAD_BLOCK / CHUNK) + tid; c < chunk0; c += ET)
+    before += a.chunk_heads[c];
+  before = (uint32_t)wave_prefix((int32_t)before);
+  if (lane == 63) s_sum[tid >> 6] = before;
   __syncthreads();
-  if (g >= cpb || chunk >= a.nchunks) return;
-  const uint64_t *key = s_key + g * CHUNK;
-  const uint32_t *pos = s_pos + g * CHUNK;
-  int pe = (int)std::min<int64_t>(CHUNK, a.n - p0);
+  uint32_t base = 0;
+#pragma unroll
+  for (int x = 0; x < ET / 64; ++x) base += s_sum[x];
+  if (blockIdx.x == gridDim.x - 1 && tid == 0 && a.num_unique) {
+    uint32_t all = base;
+    for (int x = 0; x < (npos + 63) / 64; ++x) all += s_wave[x];
+    *a.num_unique = (int32_t)all;
+  }
+  // heads in the waves' spans before this chunk's
+  for (int x = 0; x < g * CHUNK / 64 && g < cpb; ++x) base += s_wave[x];
+  const K *key = s_key + g * CHUNK;
+  const int64_t *row = s_row + g * CHUNK;
+  const uint32_t *rank = s_rank + g * CHUNK;
+  const int pe = g < cpb && chunk < a.nchunks ? (int)std::min<int64_t>(CHUNK, a.n - p0) : 0;
   // sorted: the sentinel keys (invalid ids) form the array's tail
   int valid = 0;
   while (valid < pe && key[valid] != a.sentinel) ++valid;
-  if (valid == 0) return;
+  const bool prev_same = valid > 0 && p0 > 0 && a.keys[p0 - 1] == key[0];
+  const bool next_same =
+      valid > 0 && valid == pe && p0 + pe < a.n && a.keys[p0 + pe] == key[pe - 1];
+  if (lt == 0 && g < cpb) {
+    const bool one = valid > 0 && key[0] == key[valid - 1];
+    s_state[g] = (prev_same ? CHUNK_HEAD : 0u) |
+                 (next_same ? (one && prev_same ? CHUNK_INSIDE : CHUNK_STARTS) : 0u);
+  }
   const T *G = (const T *)a.dout;
-  const bool prev_same = p0 > 0 && a.keys[p0 - 1] == key[0];
-  const bool next_same = valid == pe && p0 + pe < a.n && a.keys[p0 + pe] == key[pe - 1];
-  for (int c = lt; c < cpr; c += tpc) {
+  for (int c = lt; c < cpr && valid > 0; c += tpc) {
     float acc[NE];
 #pragma unroll
     for (int e = 0; e < NE; ++e) acc[e] = 0.0f;
@@ -242,66 +360,104 @@ __global__ void __launch_bounds__(ET) emb_chunk_kernel(BwdArgs a) {
       uint4 v[BWD_UNROLL];
 #pragma unroll
       for (int u = 0; u < BWD_UNROLL; ++u)
-        v[u] = q0 + u < valid ? *(const uint4 *)(G + dout_elem(a, pos[q0 + u], c, NE))
+        v[u] = q0 + u < valid ? *(const uint4 *)(G + row[q0 + u] + c * NE)
                               : make_uint4(0, 0, 0, 0);
 #pragma unroll
       for (int u = 0; u < BWD_UNROLL; ++u) {
         const int q = q0 + u;
         if (q >= valid) break;
         add_chunk(acc, v[u], T{});
-        const uint64_t k = key[q];
+        const K k = key[q];
         if (q + 1 < valid && key[q + 1] == k) continue;
         // piece [start, q] of key k ends here
         const bool first = start > 0 || !prev_same;
         const bool last = q + 1 < valid || !next_same;
-        float *dst;
-        if (first && last) dst = a.grad + k * (uint64_t)a.D;
-        else if (!first) dst = a.part + (chunk * 2 + 0) * a.D;
-        else dst = a.part + (chunk * 2 + 1) * a.D;
-#pragma unroll
-        for (int e = 0; e < NE; e += 4)
-          *(float4 *)(dst + c * NE + e) = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
-        if (first && c == 0) {
-          const uint32_t u = a.runid[p0 + start] - 1;
-          a.run_start[u] = (uint32_t)(p0 + start);
-          if (a.unique_rows) a.unique_rows[u] = (int64_t)k;
-        }
+        const int slot = first ? 1 : 0;
+        if (first && last) store_slice<NE>(a.grad + (uint64_t)k * (uint64_t)a.D + c * NE, acc);
+        else if (cpb > 1) store_slice<NE>(s_part[slot] + g * a.D + c * NE, acc);
+        else store_slice<NE>(a.part + (chunk * 2 + slot) * a.D + c * NE, acc);
+        if (first && c == 0 && a.unique_rows)
+          a.unique_rows[base + rank[start] - 1] = (int64_t)k;
 #pragma unroll
         for (int e = 0; e < NE; ++e) acc[e] = 0.0f;
         start = q + 1;
       }
     }
   }
+  __syncthreads();
+  if (cpb == 1) {
+    if (tid == 0) a.state[blockIdx.x] = s_state[0];
+    return;
+  }
+  // join: the group of the chunk a row starts in (or of the work-group's first
+  // chunk, for a row that began before) adds the pieces of the chunks after
+  // it; slices of one thread each (cpb > 1: cpr = tpc).  What does not end in
+  // the work-group is its first (slot 0) or last (slot 1) piece.
+  const int chunks = (int)std::min<int64_t>(cpb, a.nchunks - chunk0);
+  if (g < chunks) {
+    const uint32_t st = s_state[g];
+#pragma unroll
+    for (int slot = 0; slot < 2; ++slot) {
+      if (slot == 0 ? !(g == 0 && (st & CHUNK_HEAD)) : !(st & CHUNK_STARTS)) continue;
+      float acc[NE];
+#pragma unroll
+      for (int e = 0; e < NE; ++e) acc[e] = s_part[slot][g * a.D + lt * NE + e];
+      bool open = slot == 1 || (st & CHUNK_INSIDE);
+      for (int j = g + 1; j < chunks && open; ++j) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) acc[e] += s_part[0][j * a.D + lt * NE + e];
+        open = s_state[j] & CHUNK_INSIDE;
+      }
+      if (slot == 1 && !open) {
+        const K k = key[CHUNK - 1];
+        store_slice<NE>(a.grad + (uint64_t)k * (uint64_t)a.D + lt * NE, acc);
+      } else {
+        store_slice<NE>(a.part + ((int64_t)blockIdx.x * 2 + slot) * a.D + lt * NE, acc);
+      }
+    }
+  }
+  if (tid == 0) {
+    // the work-group as one chunk: its last chunk that is not all inside one
+    // row decides
+    uint32_t st = s_state[0] & CHUNK_HEAD;
+    int j = chunks - 1;
+    while (j >= 0 && (s_state[j] & CHUNK_INSIDE)) --j;
+    if (j < 0) st |= CHUNK_INSIDE;
+    else if (s_state[j] & CHUNK_STARTS) st |= CHUNK_STARTS;
+    a.state[blockIdx.x] = st;
+  }
 }
 
-// Joins the pieces of rows that cross chunk boundaries.  Work-group b
-// serves the row (if any) whose first position lies in chunk b and whose
-// last lies in a later chunk: it finds that later chunk by binary search on
-// the sorted keys, splits the chunks in between into one contiguous range
-// per thread group, sums each range in chunk order, and adds the group sums
-// to chunk b's own piece in group order -- a fixed order for a given batch,
-// with a hot row's thousands of chunks shared by the whole work-group.
-// Work-group 0 also publishes the distinct-row count.
-template <typename T>
-__global__ void __launch_bounds__(ET) emb_fixup_kernel(BwdArgs a) {
+// Joins the pieces of rows that cross the chunk groups.  Work-group b serves
+// the row (if any) that begins in group b and goes on after it: it finds the
+// group it ends in (the first that is not all inside it), splits the groups in
+// between into one contiguous range per thread group, sums each range in
+// order, and adds the sums to group b's own piece in order -- a fixed order for
+// a given batch, with a hot row's groups shared by the whole work-group.
+template <typename T, typename K>
+__global__ void __launch_bounds__(ET) emb_fixup_kernel(BwdArgs<K> a) {
   constexpr int NE = Elt<T>::N;
+  const int64_t chunk = blockIdx.x;
+  if (!(a.state[chunk] & CHUNK_STARTS)) return;
   const int cpr = a.D / NE;
   const int tpc = chunk_tpc(cpr), groups = ET / tpc;
   __shared__ float s_sum[ET * NE];
-  if (blockIdx.x == 0 && threadIdx.x == 0 && a.num_unique)
-    *a.num_unique = a.n > 0 ? (int32_t)a.runid[a.n - 1] : 0;
-  const int64_t chunk = blockIdx.x;
-  const int64_t p0 = chunk * CHUNK;
-  const int64_t pl = std::min<int64_t>(p0 + CHUNK, a.n) - 1;
-  const uint64_t k = a.keys[pl];
-  if (k == a.sentinel || pl + 1 >= a.n || a.keys[pl + 1] != k) return;
-  if (p0 > 0 && a.keys[p0 - 1] == k && a.keys[p0] == k) return;   // starts earlier
-  // last position of key k: just before the next row's first position
-  const uint32_t u = a.runid[pl];                   // 1-based: this row is u-1
-  const uint32_t nruns = a.runid[a.n - 1];
-  const int64_t last = u < nruns ? (int64_t)a.run_start[u] - 1 : (int64_t)*a.last_valid;
-  const int64_t c_end = last / CHUNK;               // last chunk holding key k
-  const int64_t nparts = c_end - chunk;             // chunks chunk+1 .. c_end
+  __shared__ int32_t s_end;
+  const K k = a.keys[(chunk + 1) * chunk_cpb(cpr) * CHUNK - 1];   // its last position's
+  int64_t c_end = chunk;                            // last group holding key k
+  for (;;) {
+    if (threadIdx.x == 0) s_end = ET;
+    __syncthreads();
+    const int64_t c = c_end + 1 + threadIdx.x;
+    // (the group after one whose row goes on exists)
+    if (c < a.ngroups && !(a.state[c] & CHUNK_INSIDE)) atomicMin(&s_end, (int32_t)threadIdx.x);
+    __syncthreads();
+    const int e = s_end;
+    __syncthreads();
+    c_end += e < ET ? e + 1 : ET;
+    if (e < ET || c_end + 1 >= a.ngroups) break;
+  }
+  const int64_t nparts = c_end - chunk;             // groups chunk+1 .. c_end
   const int g = threadIdx.x / tpc, lt = threadIdx.x % tpc;
   const int64_t per = (nparts + groups - 1) / groups;
   const int64_t c_lo = chunk + 1 + g * per;
@@ -315,18 +471,18 @@ __global__ void __launch_bounds__(ET) emb_fixup_kernel(BwdArgs a) {
 #pragma unroll
     for (int e = 0; e < NE; ++e) acc[e] = 0.0f;
     if (mine) {
-      // loads of 4 chunks in flight, added in chunk order
-      for (int64_t c0 = c_lo; c0 < c_hi; c0 += 4) {
-        float4 x[4][NE / 4];
+      // FIX_UNROLL groups' loads in flight, added in order
+      for (int64_t c0 = c_lo; c0 < c_hi; c0 += FIX_UNROLL) {
+        float4 x[FIX_UNROLL][NE / 4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < FIX_UNROLL; ++j)
 #pragma unroll
           for (int e = 0; e < NE / 4; ++e)
             x[j][e] = c0 + j < c_hi
                           ? *(const float4 *)(a.part + ((c0 + j) * 2 + 0) * a.D + c * NE + 4 * e)
                           : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < FIX_UNROLL; ++j) {
           if (c0 + j >= c_hi) break;
 #pragma unroll
           for (int e = 0; e < NE / 4; ++e) {
@@ -349,7 +505,7 @@ __global__ void __launch_bounds__(ET) emb_fixup_kernel(BwdArgs a) {
       for (int gi = 0; gi < groups; ++gi)
 #pragma unroll
         for (int e = 0; e < NE; ++e) acc[e] += s_sum[(gi * tpc + lt) * NE + e];
-      float *dst = a.grad + k * (uint64_t)a.D + c * NE;
+      float *dst = a.grad + (uint64_t)k * (uint64_t)a.D + c * NE;
 #pragma unroll
       for (int e = 0; e < NE; e += 4)
         *(float4 *)(dst + e) = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
@@ -387,26 +543,28 @@ int check_desc(const hstu_emb_desc *d) {
 
 int elt_n(const hstu_emb_desc *d) { return d->dtype == HSTU_F32 ? 4 : 8; }
 
+// Key bytes: 32 bits while the rows and the sentinel fit.
+bool small_keys(const hstu_emb_desc *d) { return d->total_rows < (int64_t)0xffffffff; }
+
 struct BwdLayout {
-  size_t keys_in, keys, pos_in, pos, flag, runid, run_start, last_valid, part, tmp, tmp_bytes,
-      total;
+  size_t keys_in, keys, pos_in, pos, chunk_heads, block_heads, state, part, tmp, tmp_bytes, total;
 };
 
 BwdLayout bwd_layout(const hstu_emb_desc *d, size_t tmp_bytes) {
-  const size_t n = (size_t)d->num_ids;
-  const size_t nch = (n + CHUNK - 1) / CHUNK;
+  const size_t n = (size_t)d->num_ids, kb = small_keys(d) ? 4 : 8;
+  const size_t nch = (n + CHUNK - 1) / CHUNK, cpb = chunk_cpb(d->dim / elt_n(d));
+  const size_t groups = (nch + cpb - 1) / cpb;
   BwdLayout L{};
   size_t o = 0;
   auto take = [&](size_t bytes) { const size_t at = o; o = align_up(o + bytes); return at; };
-  L.keys_in = take(8 * n);
-  L.keys = take(8 * n);
+  L.keys_in = take(kb * n);
+  L.keys = take(kb * n);
   L.pos_in = take(4 * n);
   L.pos = take(4 * n);
-  L.flag = take(4 * n);
-  L.runid = take(4 * n);
-  L.run_start = take(4 * n);
-  L.last_valid = take(4);
-  L.part = take(sizeof(float) * 2 * nch * d->dim);
+  L.chunk_heads = take(4 * nch);
+  L.block_heads = take(4 * ((n + HEAD_BLOCK - 1) / HEAD_BLOCK));
+  L.state = take(4 * groups);
+  L.part = take(sizeof(float) * 2 * groups * d->dim);
   L.tmp = take(tmp_bytes);
   L.tmp_bytes = tmp_bytes;
   L.total = o;
@@ -415,9 +573,17 @@ BwdLayout bwd_layout(const hstu_emb_desc *d, size_t tmp_bytes) {
 
 // The sort runs the onesweep radix algorithm at every size above a single
 // block (its merge-sort path for mid-size inputs is some twenty small
-// launches, latency-bound at the batch sizes here).
-using SortConfig = rocprim::radix_sort_config<rocprim::default_config, rocprim::default_config,
-                                              rocprim::default_config, 0>;
+// launches, latency-bound at the batch sizes here), in blocks of 4096 pairs:
+// a pass is as long as the chain of blocks that wait for their predecessors'
+// counts, and 1024 threads of 4 pairs take a block's share of it fastest (624
+// k pairs, three passes and the rest of the call: 347 us; 256 x 12: 360, 256 x
+// 6: 384, the library's choice 388).
+using SortConfig = rocprim::radix_sort_config<
+    rocprim::default_config, rocprim::default_config,
+    rocprim::radix_sort_onesweep_config<rocprim::kernel_config<256, 12>,
+                                        rocprim::kernel_config<1024, 4>, 8,
+                                        rocprim::block_radix_rank_algorithm::match>,
+    0>;
 
 unsigned key_bits(int64_t total_rows) {
   unsigned b = 1;
@@ -425,20 +591,72 @@ unsigned key_bits(int64_t total_rows) {
   return b;                          // keys (and the sentinel) are < 2^b
 }
 
-// Temporary bytes of the sort and the scan (the larger of the two; they
-// run one after the other on the stream).
-hipError_t lib_tmp_bytes(int64_t n, int64_t total_rows, size_t *bytes) {
-  size_t s1 = 0, s2 = 0;
-  hipError_t e = rocprim::radix_sort_pairs<SortConfig>(nullptr, s1, (uint64_t *)nullptr,
-                                           (uint64_t *)nullptr, (uint32_t *)nullptr,
-                                           (uint32_t *)nullptr, (unsigned)n, 0,
-                                           key_bits(total_rows));
-  if (e != hipSuccess) return e;
-  e = rocprim::inclusive_scan(nullptr, s2, (uint32_t *)nullptr, (uint32_t *)nullptr,
-                              (size_t)n, rocprim::plus<uint32_t>());
-  if (e != hipSuccess) return e;
-  *bytes = std::max(s1, s2);
-  return hipSuccess;
+// Temporary bytes of the sort.
+template <typename K>
+hipError_t sort_tmp_bytes(int64_t n, int64_t total_rows, size_t *bytes) {
+  return rocprim::radix_sort_pairs<SortConfig>(nullptr, *bytes, (K *)nullptr, (K *)nullptr,
+                                               (uint32_t *)nullptr, (uint32_t *)nullptr,
+                                               (unsigned)n, 0, key_bits(total_rows));
+}
+hipError_t lib_tmp_bytes(const hstu_emb_desc *d, size_t *bytes) {
+  return small_keys(d) ? sort_tmp_bytes<uint32_t>(d->num_ids, d->total_rows, bytes)
+                       : sort_tmp_bytes<uint64_t>(d->num_ids, d->total_rows, bytes);
+}
+
+template <typename K>
+int bwd_launch(const hstu_emb_desc *desc, const int64_t *ids, const void *dout,
+               float *grad_weights, int64_t *unique_rows, int32_t *num_unique, char *ws,
+               const BwdLayout &L, hipStream_t s) {
+  const int64_t n = desc->num_ids;
+  BwdArgs<K> a{};
+  a.ro = desc->row_offsets;
+  a.io = desc->id_offsets;
+  a.ids = ids;
+  a.dout = dout;
+  a.grad = grad_weights;
+  a.unique_rows = unique_rows;
+  a.num_unique = num_unique;
+  a.keys_in = (K *)(ws + L.keys_in);
+  a.keys = (K *)(ws + L.keys);
+  a.pos_in = (uint32_t *)(ws + L.pos_in);
+  a.pos = (uint32_t *)(ws + L.pos);
+  a.chunk_heads = (uint32_t *)(ws + L.chunk_heads);
+  a.block_heads = (uint32_t *)(ws + L.block_heads);
+  a.state = (uint32_t *)(ws + L.state);
+  a.part = (float *)(ws + L.part);
+  a.sentinel = (K)desc->total_rows;
+  a.n = n;
+  a.F = desc->num_tables;
+  a.D = desc->dim;
+  a.token = desc->layout == HSTU_EMB_TOKEN;
+  a.per_table = a.token ? n / a.F : 0;
+  a.nchunks = (int)((n + CHUNK - 1) / CHUNK);
+  a.nblocks = (int)((n + HEAD_BLOCK - 1) / HEAD_BLOCK);
+  a.scanned = a.nblocks > HEAD_SUM_BLOCKS;
+  const int cpr = a.D / elt_n(desc);
+  const int cpb = chunk_cpb(cpr);
+  a.ngroups = (a.nchunks + cpb - 1) / cpb;
+  hipError_t e;
+  prof::Scope ps("emb_bwd", s);
+  hipLaunchKernelGGL(emb_keys_kernel<K>, dim3((unsigned)((n + ET - 1) / ET)), dim3(ET), 0, s, a);
+  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "embedding key launch");
+  size_t tb = L.tmp_bytes;
+  e = rocprim::radix_sort_pairs<SortConfig>(ws + L.tmp, tb, a.keys_in, a.keys, a.pos_in, a.pos,
+                                (unsigned)n, 0, key_bits(desc->total_rows), s);
+  if (e != hipSuccess) return hip_fail(e, "embedding key sort");
+  hipLaunchKernelGGL(emb_heads_kernel<K>, dim3((unsigned)a.nblocks), dim3(ET), 0, s, a);
+  if (a.scanned) hipLaunchKernelGGL(emb_scan_kernel<K>, dim3(1), dim3(1024), 0, s, a);
+  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "embedding head launch");
+  const unsigned grid_c = (unsigned)a.ngroups, grid_f = grid_c;
+  if (desc->dtype == HSTU_F32) {
+    hipLaunchKernelGGL((emb_chunk_kernel<float, K>), dim3(grid_c), dim3(ET), 0, s, a);
+    hipLaunchKernelGGL((emb_fixup_kernel<float, K>), dim3(grid_f), dim3(ET), 0, s, a);
+  } else {
+    hipLaunchKernelGGL((emb_chunk_kernel<u16, K>), dim3(grid_c), dim3(ET), 0, s, a);
+    hipLaunchKernelGGL((emb_fixup_kernel<u16, K>), dim3(grid_f), dim3(ET), 0, s, a);
+  }
+  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "embedding chunk launch");
+  return HSTU_OK;
 }
 
 }  // namespace
@@ -486,9 +704,9 @@ extern "C" size_t hstu_jagged_embedding_bwd_workspace_bytes(const hstu_emb_desc 
   clear_last_error();
   if (check_desc(desc)) return 0;
   size_t tmp = 0;
-  const hipError_t e = lib_tmp_bytes(desc->num_ids, desc->total_rows, &tmp);
+  const hipError_t e = lib_tmp_bytes(desc, &tmp);
   if (e != hipSuccess) {
-    hip_fail(e, "sort/scan workspace query");
+    hip_fail(e, "sort workspace query");
     return 0;
   }
   return bwd_layout(desc, tmp).total;
@@ -515,61 +733,14 @@ extern "C" int hstu_jagged_embedding_bwd(const hstu_emb_desc *desc, const int64_
   if (!ids || !dout || !grad_weights)
     return fail(HSTU_EINVAL, "ids, dout and grad_weights must be non-null");
   size_t tmp = 0;
-  hipError_t e = lib_tmp_bytes(n, desc->total_rows, &tmp);
-  if (e != hipSuccess) return hip_fail(e, "sort/scan workspace query");
+  hipError_t e = lib_tmp_bytes(desc, &tmp);
+  if (e != hipSuccess) return hip_fail(e, "sort workspace query");
   const BwdLayout L = bwd_layout(desc, tmp);
   rc = check_workspace_bytes(L.total, workspace, workspace_bytes);
   if (rc) return rc;
-  char *ws = (char *)workspace;
-  BwdArgs a{};
-  a.ro = desc->row_offsets;
-  a.io = desc->id_offsets;
-  a.ids = ids;
-  a.dout = dout;
-  a.grad = grad_weights;
-  a.unique_rows = unique_rows;
-  a.num_unique = num_unique;
-  a.keys_in = (uint64_t *)(ws + L.keys_in);
-  a.keys = (uint64_t *)(ws + L.keys);
-  a.pos_in = (uint32_t *)(ws + L.pos_in);
-  a.pos = (uint32_t *)(ws + L.pos);
-  a.flag = (uint32_t *)(ws + L.flag);
-  a.runid = (uint32_t *)(ws + L.runid);
-  a.run_start = (uint32_t *)(ws + L.run_start);
-  a.last_valid = (uint32_t *)(ws + L.last_valid);
-  a.part = (float *)(ws + L.part);
-  a.sentinel = (uint64_t)desc->total_rows;
-  a.n = n;
-  a.F = desc->num_tables;
-  a.D = desc->dim;
-  a.token = desc->layout == HSTU_EMB_TOKEN;
-  a.per_table = a.token ? n / a.F : 0;
-  a.nchunks = (int)((n + CHUNK - 1) / CHUNK);
-  const int cpr = a.D / elt_n(desc);
-  const int cpb = chunk_cpb(cpr);
-  const unsigned grid_n = (unsigned)((n + ET - 1) / ET);
-  prof::Scope ps("emb_bwd", s);
-  hipLaunchKernelGGL(emb_keys_kernel, dim3(grid_n), dim3(ET), 0, s, a);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "embedding key launch");
-  size_t tb = L.tmp_bytes;
-  e = rocprim::radix_sort_pairs<SortConfig>(ws + L.tmp, tb, a.keys_in, a.keys, a.pos_in, a.pos,
-                                (unsigned)n, 0, key_bits(desc->total_rows), s);
-  if (e != hipSuccess) return hip_fail(e, "embedding key sort");
-  hipLaunchKernelGGL(emb_heads_kernel, dim3(grid_n), dim3(ET), 0, s, a);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "embedding head launch");
-  tb = L.tmp_bytes;
-  e = rocprim::inclusive_scan(ws + L.tmp, tb, a.flag, a.runid, (size_t)n,
-                              rocprim::plus<uint32_t>(), s);
-  if (e != hipSuccess) return hip_fail(e, "embedding head scan");
-  const unsigned grid_c = (unsigned)((a.nchunks + cpb - 1) / cpb);
-  const unsigned grid_f = (unsigned)a.nchunks;
-  if (desc->dtype == HSTU_F32) {
-    hipLaunchKernelGGL(emb_chunk_kernel<float>, dim3(grid_c), dim3(ET), 0, s, a);
-    hipLaunchKernelGGL(emb_fixup_kernel<float>, dim3(grid_f), dim3(ET), 0, s, a);
-  } else {
-    hipLaunchKernelGGL(emb_chunk_kernel<u16>, dim3(grid_c), dim3(ET), 0, s, a);
-    hipLaunchKernelGGL(emb_fixup_kernel<u16>, dim3(grid_f), dim3(ET), 0, s, a);
-  }
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "embedding chunk launch");
-  return HSTU_OK;
+  return small_keys(desc)
+             ? bwd_launch<uint32_t>(desc, ids, dout, grad_weights, unique_rows, num_unique,
+                                    (char *)workspace, L, s)
+             : bwd_launch<uint64_t>(desc, ids, dout, grad_weights, unique_rows, num_unique,
+                                    (char *)workspace, L, s);
 }

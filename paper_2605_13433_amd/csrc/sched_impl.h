@@ -99,18 +99,6 @@ struct SchedArgs {
   int32_t n_zero;
 };
 
-// Sum of x over this and the lower lanes: DPP shifts inside the rows of 16
-// lanes, then row broadcasts (a ds_bpermute per step costs an LDS round trip).
-__device__ __forceinline__ int32_t wave_prefix(int32_t x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);    // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);    // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);    // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);    // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);   // lane 15 of rows 0, 2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);   // lane 31
-  return x;
-}
-
 // Runs in one work-group of NT threads.
 template <int NT>
 __device__ __forceinline__ void build_schedule(const SchedArgs &a, SchedSmem &sm, int tid) {

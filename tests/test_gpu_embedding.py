@@ -101,6 +101,47 @@ def test_runs_across_chunk_boundaries():
         compare(b)
 
 
+# chunk groups of 256 positions (fp32, D = 128: 8 chunks of 32), 512 (D = 8)
+# and 32 (D >= 1024, one chunk, several slices a thread): runs that end one
+# short of, at and one past a group's end, cover whole groups, and cross three
+@pytest.mark.parametrize("D,dtype", [(128, torch.float32), (128, torch.bfloat16),
+                                     (8, torch.float32), (40, torch.bfloat16),
+                                     (1024, torch.float32), (2048, torch.float32)])
+def test_runs_across_chunk_groups(D, dtype):
+    runs = [255, 257, 1, 256, 31, 33, 767, 2, 510, 1500, 1, 1, 62, 512, 3]
+    ids = np.repeat(np.arange(len(runs)) * 3 % 64, runs)
+    ids = np.random.default_rng(5).permutation(ids)
+    b = emb_inputs.make_batch((64,), (len(ids),), D, dtype, seed=11, ids=list(ids),
+                              name="group_runs")
+    compare(b)
+
+
+def test_many_positions_scan():
+    """More head-count blocks than a chunk work-group sums for itself."""
+    n = 512 * 4096 + 4097
+    ids = np.random.default_rng(6).integers(-1, 3000, size=n)
+    b = emb_inputs.make_batch((3000,), (n,), 8, torch.float32, seed=12, ids=ids,
+                              name="many_positions")
+    compare(b)
+
+
+def test_wide_keys():
+    """64-bit keys (2^32 rows and more) give the bits that 32-bit keys give;
+    the ids stay in the rows that exist."""
+    b = emb_inputs.make_batch((1 << 10, 16), (20000, 20000), 64, torch.float32, seed=13,
+                              alpha=1.2, name="wide")
+    _, g1, u1, c1, p, (W, ids, dout) = run(b)
+    wide = emb.plan(W, p.row_offsets, p.id_offsets, 1 << 33, b.n)
+    g2 = torch.full_like(g1, float("nan"), device="cuda")
+    u2 = torch.full((b.n,), -7, dtype=torch.int64, device="cuda")
+    c2 = torch.full((1,), -7, dtype=torch.int32, device="cuda")
+    emb.lookup_backward(wide, ids, dout.contiguous().cuda(), g2, u2, c2)
+    torch.cuda.synchronize()
+    assert int(c2.item()) == c1 and torch.equal(u2.cpu()[:c1], u1[:c1])
+    rows = u1[:c1]
+    assert torch.equal(g1[rows].view(torch.int32), g2.cpu()[rows].view(torch.int32))
+
+
 def test_backward_is_deterministic():
     b = emb_inputs.make_batch((1 << 10, 16), (20000, 20000), 128, torch.float32, seed=9,
                               alpha=1.2, name="det")
