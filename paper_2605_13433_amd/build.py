@@ -17,10 +17,10 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libhstu_jagged.so")
 ARCH = "gfx950"
-SOURCES = ["api.cpp", "sched.hip", "attn_bf16.hip", "attn_f32.hip", "norm.hip",
+SOURCES = ["api.cpp", "sched.hip", "attn_bf16.hip", "attn_short.hip", "attn_f32.hip", "norm.hip",
            "layer.cpp", "layer_kernels.hip", "noalloc.hip", "embedding.hip", "rab.hip",
            "gemm.hip"]
-HEADERS = ["device.h", "internal.h", "sched_impl.h"]
+HEADERS = ["device.h", "internal.h", "sched_impl.h", "attn_common.h"]
 
 CFLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -258,7 +258,8 @@ int attn_fwd_call(const void *q, const void *k, const void *v, const void *u,
   // allocate)
   const bool prof_on = !fixed;
   hipError_t e;
-  const bool direct = fwd_direct(p, dev);
+  const bool small = fwd_short(p, dev);
+  const bool direct = small ? p.B <= FWD_DIRECT_SEQS && !p.check_offsets : fwd_direct(p, dev);
   if (!direct) {
     prof::Scope ps(prof_on ? "schedule" : nullptr, s);
     e = launch_schedule(seq_offsets, p, ws, L, s);
@@ -266,8 +267,9 @@ int attn_fwd_call(const void *q, const void *k, const void *v, const void *u,
   }
   {
     prof::Scope ps(!prof_on ? nullptr : p.dtype == HSTU_BF16 ? "attn_fwd" : "attn_fwd_f32", s);
-    e = p.dtype == HSTU_BF16 ? launch_attn_fwd_bf16(a, out->o, direct, s)
-                             : launch_attn_fwd_f32(a, out->o, direct, s);
+    e = small                    ? launch_attn_fwd_short(a, out->o, direct, s)
+        : p.dtype == HSTU_BF16 ? launch_attn_fwd_bf16(a, out->o, direct, s)
+                               : launch_attn_fwd_f32(a, out->o, direct, s);
   }
   if (e != hipSuccess) return hip_fail(e, "attention forward launch");
   {
@@ -327,7 +329,12 @@ int attn_bwd_call(const void *q, const void *k, const void *v, const void *u,
     if (e != hipSuccess) return hip_fail(e, "schedule launch");
   }
   if (p.dtype == HSTU_BF16) {
-    e = launch_attn_bwd_bf16(a, ws + L.dO, io->dq, io->dk, io->dv, go, s);
+    if (bwd_short(p, dev)) {
+      prof::Scope ps("attn_bwd_short", s);
+      e = launch_attn_bwd_short(a, ws + L.dO, io->dq, io->dk, io->dv, go, s);
+    } else {
+      e = launch_attn_bwd_bf16(a, ws + L.dO, io->dq, io->dk, io->dv, go, s);
+    }
     if (e != hipSuccess) return hip_fail(e, "attention backward launch");
     {
       prof::Scope ps("finalize_tables", s);

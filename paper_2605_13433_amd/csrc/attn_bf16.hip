@@ -50,6 +50,7 @@
 
 #include "internal.h"
 #include "device.h"
+#include "attn_common.h"
 #include "sched_impl.h"
 
 namespace hstu {
@@ -64,13 +65,6 @@ constexpr int DS_STRIDE = TILE + RM_PAD;   // backward: staged dS^T tile
 // read phase, whose 4-entry windows start at 16 consecutive entries, fall on
 // 16 distinct 4-bank groups of the 64 banks.
 constexpr int POS_COPY = 144;
-constexpr int KTAB = 608;        // float-exponent time index 0..603 (+pad)
-constexpr int32_t NEAR = 1 << 23;  // |ts - ts_start| < NEAR -> float-exponent path
-constexpr float L2E = 1.44269504088896341f;      // log2(e)
-
-typedef short v4i16 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
-
 struct KParams {
   const u16 *q, *k, *v;
   const u16 *dO;
@@ -97,11 +91,9 @@ struct KParams {
   // dV stores take dqk_scale / log2e and 1 / (N log2e)
   float al2e, dk_scale_l2, dv_scale_l2;
   int32_t all_heads;      // time tables of every head staged once per work-group
-                          // (2: the direct forward's, its item's head alone)
-  // direct forward: one item per work-group, found from the offsets
-  const int64_t *off;
+  const int64_t *off;     // direct forward
   int64_t T;
-  int32_t B, direct;
+  int32_t B;
   int32_t fuse_dq0;       // combined backward, d=64: the dK/dV items of first
                           // k-tiles compute their q-tile's dQ (no such dQ items)
 };
@@ -178,29 +170,6 @@ __device__ __forceinline__ const float *pos_lane(const float *pos, int x0) {
   return pos + s * COPY + (x0 - s);
 }
 
-// Float-exponent index of a time difference held exactly in a float
-// (|delta| < 2^24; see file comment).  The sign bit is not in the field.
-__device__ __forceinline__ int time_index(float delta) {
-  return (int)__builtin_amdgcn_ubfe(__float_as_uint(delta), 21u, 10u);
-}
-
-// Bucket of float-exponent index k (k = 0 <-> 0; 508, 512, 514 <-> 1, 2, 3;
-// k >= 516 <-> k - 512), clamped to nb-1.  Indices no integer reaches map
-// to some valid bucket.
-__device__ __forceinline__ int bucket_of_index(int k, int nb) {
-  int b = k >= 516 ? k - 512 : (k >= 514 ? 3 : (k >= 512 ? 2 : (k >= 508 ? 1 : 0)));
-  return b < nb - 1 ? b : nb - 1;
-}
-
-// Scores are handled in the base-2 domain x' = x log2(e): the MFMA result is
-// scaled once and the bias tables are staged pre-scaled, so that e^-x is a
-// single exp2 of -x'.
-//   silu(x) / N = x' / (N log2e (1 + 2^-x'));  nl = N log2e
-__device__ __forceinline__ float silu2_over_n(float xs, float nl) {
-  const float t = __builtin_amdgcn_exp2f(-xs);
-  return xs * __builtin_amdgcn_rcpf(__builtin_fmaf(nl, t, nl));
-}
-
 // d_time is accumulated in LDS in double precision: the gfx950 LDS f64 add
 // atomic runs at a few cycles per wave instruction on distinct addresses,
 // while the f32 one costs hundreds.
@@ -258,7 +227,7 @@ __device__ __forceinline__ void stage_all_heads(const KParams &P, float *dyn, in
 template <int NT = THREADS>
 __device__ __forceinline__ float *item_time_slot(const KParams &P, float *dyn, int h, int tid,
                                                  float scale) {
-  if (P.all_heads) return P.all_heads == 2 ? dyn : dyn + h * time_slot_floats(P);
+  if (P.all_heads) return dyn + h * time_slot_floats(P);
   stage_time_heads<1, NT>(P, dyn, h, 1, tid, scale);
   return dyn;
 }
@@ -636,9 +605,11 @@ __device__ __forceinline__ void fwd_store_o(float *red, const f32x16 (&acc)[D / 
 // issued one step before an item's last, and an
 // item's last tile streams the next item's first key tile, query rows, bias
 // slice and timestamps, so no item starts with an exposed memory latency.
-template <int D, bool POS, bool TIME, int QT>
+// DIRECT: one item per work-group, found from the offsets (fwd_direct).
+template <int D, bool POS, bool TIME, int QT, bool DIRECT = false>
 __global__ void __launch_bounds__(THREADS * QT, QT == 1 ? 2 : 1)
 attn_fwd_kernel(KParams P) {
+  static_assert(QT == 1 || !DIRECT, "direct items are one query tile");
   constexpr int NT = THREADS * QT, NW = 4 * QT;
   constexpr int PCOPY = FWD_POS_COPY<QT>, PLEN = FWD_POS_LEN<QT>;
   __shared__ FwdSmem<D, QT> sm;
@@ -646,7 +617,7 @@ attn_fwd_kernel(KParams P) {
   int cur = blockIdx.x;
   int n_items;
   Item it;
-  if (QT == 1 && P.direct) {
+  if constexpr (DIRECT) {
     WorkEntry e;
     if (cur == 0 && threadIdx.x == 0) const_cast<int32_t *>(P.ctrl)[CTRL_STATUS] = HSTU_SEQ_UNCHECKED;
     if (!direct_entry(P.off, P.B, P.N, P.T, cur / P.H, e)) return;
@@ -683,7 +654,7 @@ attn_fwd_kernel(KParams P) {
   }
   // the tables after the first item's loads: both latencies overlap
   if (TIME) {
-    if (QT == 1 && P.direct) stage_time_heads<4, NT>(P, dyn, it.h, 1, tid0, L2E);
+    if (DIRECT) stage_time_heads<4, NT>(P, dyn, it.h, 1, tid0, L2E);
     else stage_all_heads<8, NT>(P, dyn, tid0, L2E);
   }
 
@@ -748,7 +719,7 @@ attn_fwd_kernel(KParams P) {
       const int64_t rel = ts_i - ts_start;
       ts_i32 = (float)(int32_t)rel;
       q_far = rel >= NEAR || rel <= -NEAR;
-      ktab = item_time_slot<NT>(P, dyn, h, tid, L2E);
+      if (!DIRECT) ktab = item_time_slot<NT>(P, dyn, h, tid, L2E);   // (staged at the start)
     }
     const int64_t ts_i_item = ts_i, ts_start_item = ts_start;
     // the item's K and V rows of head h: one source each for its tiles
@@ -972,22 +943,6 @@ __device__ __forceinline__ bf16x8 read_rm(const u16 *lds, int stride, int row, i
   return *(const bf16x8 *)(lds + row * stride + col);
 }
 
-// Operand holding, for lane l, column ncol + (l & 31) of rows krow .. krow+3
-// and krow+8 .. krow+11 of a row-major LDS tile (krow already includes this
-// lane's 4*(l/32)), via two LDS transpose loads.  Within a 16-lane group,
-// lane c addresses row (c>>2), columns 4*(c&3)..+3 of its group's 16-column
-// slab; the transpose hands lane i the column slab+i of the four rows.
-__device__ __forceinline__ bf16x8 read_tr(const u16 *lds, int stride, int krow,
-                                          int ncol, int lane) {
-  const int c = lane & 15;
-  const u16 *p = lds + (krow + (c >> 2)) * stride + ncol + ((lane >> 4) & 1) * 16 + 4 * (c & 3);
-  const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)p);
-  const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16 *)(p + 8 * stride));
-  typedef short v8i16 __attribute__((ext_vector_type(8)));
-  const v8i16 x = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  return __builtin_bit_cast(bf16x8, x);
-}
-
 template <int D>
 struct StreamSmem {
   union {
@@ -1005,53 +960,9 @@ struct StreamSmem {
   int item;
 };
 
-// Per-lane running sum of d_time contributions (dS multiplied by log2e, as
-// the dK/dV items carry it; the table partials keep that factor, which the
-// finalize pass divides out) over one float-exponent time index (the lane's
-// pairs visit non-decreasing indices when timestamps are ordered, so a run
-// ends only when its index changes); a finished run goes to its bucket of
-// the work-group's histogram `hist`.  A run is opened by
-// the first index of the item's first tile (start), so adding needs no test
-// for an empty run.
-template <typename A>
-struct TimeRun {
-  typedef typename A::L L;
-  float sum = 0.0f;
-  int cur = -1;
-  __device__ __forceinline__ void start(int k) { cur = cur < 0 ? k : cur; }
-  __device__ __forceinline__ void add(L *hist, int nb, int k, float v) {
-    const bool change = k != cur;
-    if (change) atomicAdd(&hist[bucket_of_index(cur, nb)], A::lds(sum));
-    sum = change ? v : sum + v;
-    cur = k;
-  }
-  __device__ __forceinline__ void flush(L *hist, int nb) {
-    if (cur >= 0) atomicAdd(&hist[bucket_of_index(cur, nb)], A::lds(sum));
-    cur = -1;
-    sum = 0.0f;
-  }
-};
-
-
 // The backward kernels work with N dS and N A (the 1/N of both is applied
 // once, to the accumulated dQ, dK, dV tiles at their store and to the table
 // gradients when they are finalized).
-
-// Table-gradient accumulation types: LDS sums in double and global partials
-// in float, or (deterministic mode) both as 64-bit fixed point, whose
-// integer additions give the same result in any order.
-template <bool DET> struct TabAcc {
-  typedef double L;
-  typedef float G;
-  static __device__ __forceinline__ L lds(float v) { return (double)v; }
-  static __device__ __forceinline__ G glob(L v) { return (float)v; }
-};
-template <> struct TabAcc<true> {
-  typedef unsigned long long L;
-  typedef unsigned long long G;
-  static __device__ __forceinline__ L lds(float v) { return to_fix(v); }
-  static __device__ __forceinline__ G glob(L v) { return v; }
-};
 
 // The backward kernels' persistent loop: a work-group's first item is
 // static (its block index in the longest-first list) and every item pops the
@@ -1883,6 +1794,9 @@ KParams make_params(const AttnArgs &a, int32_t *pop, const WorkEntry *list) {
     }                                                                         \
   } while (0)
 
+template <int D, bool POS, bool TIME>
+constexpr auto attn_fwd_direct = attn_fwd_kernel<D, POS, TIME, 1, true>;
+
 // As HSTU_DISPATCH, with a fourth template argument QT (forward items of QT
 // query tiles).
 #define HSTU_DISPATCH_Q(KERNEL, D, POS, TIME, QT, ...)                              \
@@ -1947,8 +1861,8 @@ bool fwd_direct(const Problem &p, int dev) {
   if (p.max_entries * p.H > 8 * (int64_t)device_info(dev).num_cu) return false;
   if (p.dtype != HSTU_BF16) return 2 * p.max_entries * p.H <= 2 * device_info(dev).num_cu;
   int grid = 0;
-  HSTU_DISPATCH_Q(attn_fwd_kernel, p.d, p.has_pos, p.has_time, 1,
-                  grid = persistent_grid(kfn, slot_bytes(p, false), p.max_entries * p.H, dev));
+  HSTU_DISPATCH(attn_fwd_direct, p.d, p.has_pos, p.has_time,
+                grid = persistent_grid(kfn, slot_bytes(p, false), p.max_entries * p.H, dev));
   return p.max_entries * p.H <= grid;
 }
 
@@ -1999,11 +1913,9 @@ hipError_t launch_attn_fwd_bf16(const AttnArgs &a, void *o, bool direct, hipStre
     P.off = a.off;
     P.T = p.T;
     P.B = p.B;
-    P.direct = 1;
-    P.all_heads = p.has_time ? 2 : 0;
-    HSTU_DISPATCH_Q(attn_fwd_kernel, p.d, p.has_pos, p.has_time, 1,
-                    hipLaunchKernelGGL(kfn, dim3((unsigned)(p.max_entries * p.H)), dim3(THREADS),
-                                       slot_bytes(p, false), s, P));
+    HSTU_DISPATCH(attn_fwd_direct, p.d, p.has_pos, p.has_time,
+                  hipLaunchKernelGGL(kfn, dim3((unsigned)(p.max_entries * p.H)), dim3(THREADS),
+                                     slot_bytes(p, false), s, P));
     return hipGetLastError();
   }
   const bool pairs = fwd_pairs(p);

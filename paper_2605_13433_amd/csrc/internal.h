@@ -189,6 +189,13 @@ hipError_t launch_attn_fwd_bf16(const AttnArgs &a, void *o, bool direct, hipStre
 hipError_t launch_attn_bwd_bf16(const AttnArgs &a, const void *dO, void *dq, void *dk,
                                 void *dv, const GradOut *go, hipStream_t s);
 
+// The same for short batches (attn_short.hip) and the rules that choose it.
+bool fwd_short(const Problem &p, int dev);
+bool bwd_short(const Problem &p, int dev);
+hipError_t launch_attn_fwd_short(const AttnArgs &a, void *o, bool direct, hipStream_t s);
+hipError_t launch_attn_bwd_short(const AttnArgs &a, const void *dO, void *dq, void *dk, void *dv,
+                                 const GradOut *go, hipStream_t s);
+
 hipError_t launch_attn_fwd_f32(const AttnArgs &a, void *o, bool direct, hipStream_t s);
 hipError_t launch_attn_bwd_f32(const AttnArgs &a, const void *dO, void *dq,
                                void *dk, void *dv, float *d_pos,

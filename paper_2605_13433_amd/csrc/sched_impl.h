@@ -47,12 +47,15 @@
 // The chain of steps bounds it, so none of them is serial in the batch: the
 // sequences are dealt to the waves in turn (a small batch occupies every
 // wave), the sums over the tile-count bins are scans of 64 bins by one wave
-// for each purpose, and a sequence of more than SCHED_LANE_TILES tiles is
-// written by its whole wave.  The standalone launch, against one lane per
+// for each purpose, and a wave writes its sequences' entries 64 at a time
+// whatever their lengths.  The standalone launch, against one lane per
 // sequence and one thread over the bins: 6 sequences of up to 8192 tokens
-// 44.6 -> 4.6 us, 1024 of up to 8192 77 -> 22, 64 of up to 2048 16.3 -> 6.4,
-// 128 of up to 512 7.4 -> 5.7.  (Shuffle scans made 8 sequences of up to 250
-// tokens 0.3 us slower than the one thread; DPP scans are 0.1 us faster.)
+// 44.6 -> 4.7 us, 1024 of up to 8192 77 -> 21, 64 of up to 2048 16.3 -> 5.2,
+// 128 of up to 512 7.4 -> 4.7 (and the LayerNorm-backward launch that carries
+// it 14.2 -> 10.3).  Tried on the way: shuffle scans made 8 sequences of up to
+// 250 tokens 0.3 us slower than the one thread (DPP scans 0.1 us faster), and
+// whole waves writing the long sequences one after another made 927 sequences
+// of up to 1805 tokens 3 us slower than one lane each.
 #pragma once
 
 #include "internal.h"
@@ -65,10 +68,6 @@ constexpr int SCHED_MAX_BINS = 65536 / TILE + 2;   // max_len <= 65536
 // The sequence-major order needs this many times the longest item's cost of
 // work per work-group (in 64 x 64 tile pairs).
 constexpr int SCHED_SEQ_MAJOR_SLACK = 4;
-
-// A sequence of up to this many tiles is written by one lane (64 at once),
-// a longer one by all 64 lanes of its wave.
-constexpr int SCHED_LANE_TILES = 4;
 
 struct SchedSmem {
   int32_t count[SCHED_MAX_BINS];      // # sequences with ntiles == n
@@ -272,18 +271,24 @@ __device__ __forceinline__ void build_schedule(const SchedArgs &a, SchedSmem &sm
     const int nt = si.ntiles;
     int r = 0;                                     // rank, by tile count
     if (nt > 0) r = sm.rank0[nt] + atomicAdd(&sm.fill[nt], 1);
-    if (nt <= SCHED_LANE_TILES)
-      for (int t = 0; t < nt; ++t) emit(b, si, r, t);
-    for (uint64_t long_ = __ballot(nt > SCHED_LANE_TILES); long_ != 0; long_ &= long_ - 1) {
-      const int src = __builtin_ctzll(long_);
-      SeqInfo sl;
-      sl.start = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(
-                                (int)((uint64_t)si.start >> 32), src) << 32) |
-                           (uint32_t)__builtin_amdgcn_readlane((int)si.start, src));
-      sl.len = __builtin_amdgcn_readlane(si.len, src);
-      sl.ntiles = __builtin_amdgcn_readlane(nt, src);
-      const int rl = __builtin_amdgcn_readlane(r, src), bl = __builtin_amdgcn_readlane(b, src);
-      for (int t = lane; t < sl.ntiles; t += 64) emit(bl, sl, rl, t);
+    // the wave's entries 64 at a time, each lane on the sequence (lane) that
+    // its entry belongs to
+    const int end = wave_prefix(nt);
+    const int total = __builtin_amdgcn_readlane(end, 63);
+    for (int x0 = 0; x0 < total; x0 += 64) {
+      const int x = x0 + lane < total ? x0 + lane : total - 1;
+      int src = 0;                                 // first lane whose end lies past x
+#pragma unroll
+      for (int step = 32; step >= 1; step >>= 1)
+        src += __shfl(end, src + step - 1, 64) <= x ? step : 0;
+      SeqInfo so;
+      so.start = (int64_t)(((uint64_t)(uint32_t)__shfl((int)((uint64_t)si.start >> 32), src, 64)
+                            << 32) | (uint32_t)__shfl((int)si.start, src, 64));
+      so.len = __shfl(si.len, src, 64);
+      so.ntiles = __shfl(nt, src, 64);
+      const int ro = __shfl(r, src, 64), bo = __shfl(b, src, 64);
+      const int t = x - (__shfl(end, src, 64) - so.ntiles);
+      if (x0 + lane < total) emit(bo, so, ro, t);
     }
   }
 }
