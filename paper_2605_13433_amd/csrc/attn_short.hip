@@ -683,14 +683,16 @@ auto pick_bwd(bool pos, bool time) {
 
 }  // namespace
 
-// The line: the batch's work-groups all run at once, at most two on a compute
-// unit at d = 64 and one at d = 128 (the forward has one work-group per 32-row
-// item, the backward two).  Then a call is as long as its longest chain, and
+// The line: the batch's work-groups all run at once (the forward has one
+// work-group per 32-row item and room for three on a compute unit at d = 64,
+// the backward two per item and room for two; one at d = 128, where a second
+// gains nothing).  Then a call is as long as its longest chain, and
 // the chain here is the shorter one.  Beyond it the items queue, each with its
 // exposed start, where the tile kernels' persistent work-groups hide theirs.
 // Tile kernels / these, both biases, H = 4 where not said (us):
 //   forward d = 64:  B=1 L=502 20.3 / 16.7, B=1 L=812 26.0 / 19.7, B=1 L=8022 H=2
-//     148 / 109, B=12 L<=250 16.3 / 15.6; past it B=12 L<=1000 34.5 / 40.5
+//     148 / 109, B=12 L<=250 16.3 / 15.6, B=4 L<=1630 43.8 / 37.1; past it B=12
+//     L<=1000 34.5 / 40.5
 //   forward d = 128: B=1 L=502 25.3 / 22.5, B=4 L<=512 23.7 / 21.3; past it B=12
 //     L<=250 19.5 / 20.5
 //   backward d = 64: B=1 L=90 27.7 / 20.8, B=1 L=812 62.5 / 40.5, B=4 L<=512 45.2 /
@@ -701,7 +703,7 @@ static int64_t short_items(const Problem &p) { return 2 * p.max_entries * p.H; }
 
 bool fwd_short(const Problem &p, int dev) {
   return p.dtype == HSTU_BF16 &&
-         short_items(p) <= (p.d == 64 ? 2 : 1) * (int64_t)device_info(dev).num_cu;
+         short_items(p) <= (p.d == 64 ? 3 : 1) * (int64_t)device_info(dev).num_cu;
 }
 bool bwd_short(const Problem &p, int dev) {
   return p.dtype == HSTU_BF16 &&
