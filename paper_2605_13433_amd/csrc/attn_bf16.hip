@@ -90,6 +90,7 @@ struct KParams {
   // the dK/dV items carry A and dS multiplied by log2e: their dK, dQ and
   // dV stores take dqk_scale / log2e and 1 / (N log2e)
   float al2e, dk_scale_l2, dv_scale_l2;
+  int32_t time_cs;        // log2 of the d_time histogram's counters per bucket
   int32_t all_heads;      // time tables of every head staged once per work-group
   const int64_t *off;     // direct forward
   int64_t T;
@@ -1320,7 +1321,7 @@ __device__ __forceinline__ void dkv_item(const KParams &P, DkvSmem<D, POS, DET> 
       ktab = item_time_slot(P, dyn, h, tid, P.inv_alpha);
     }
     TimeRun<A> run;                           // fast path: by float-exponent index
-    typename A::L *my_t = TIME ? tacc + h * P.nb : nullptr;
+    typename A::L *my_t = TIME ? tacc + (lane & ((1 << P.time_cs) - 1)) : nullptr;
     typename A::G *dp_item = POS ? (typename A::G *)P.dpos_part + si.start * P.H + h : nullptr;
 
     // At d=128 (SPLIT) a wave's dK and dV accumulators together would take
@@ -1524,7 +1525,7 @@ __device__ __forceinline__ void dkv_item(const KParams &P, DkvSmem<D, POS, DET> 
           if (!slow) {
             if (hh == 0) run.start(tk[0]);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) run.add(my_t, P.nb, tk[e], dsv[e]);
+            for (int e = 0; e < 8; ++e) run.add(my_t, P.nb, P.time_cs, tk[e], dsv[e]);
           } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -1532,7 +1533,7 @@ __device__ __forceinline__ void dkv_item(const KParams &P, DkvSmem<D, POS, DET> 
               // conversion would keep the doubles live across this branch
               float v = dsv[e];
               asm volatile("" : "+v"(v));
-              if (v != 0.0f) atomicAdd(&my_t[tk[e]], A::lds(v));
+              if (v != 0.0f) atomicAdd(&my_t[tk[e] << P.time_cs], A::lds(v));
             }
           }
         }
@@ -1583,8 +1584,24 @@ __device__ __forceinline__ void dkv_item(const KParams &P, DkvSmem<D, POS, DET> 
     }
 
     // close the d_time runs; sum the two query halves, store dK, dV (bf16)
-    if (TIME) run.flush(my_t, P.nb);
+    if (TIME) run.flush(my_t, P.nb, P.time_cs);
     lds_barrier();
+    if (TIME) {
+      // the item's d_time sums go to one of DTIME_BINS partials; cleared for the
+      // next item (whose first step's barriers order it).  One head's
+      // histogram instead of all of them: at d=128 with 8 heads and 128
+      // buckets two work-groups fit a CU's LDS again.
+      typename A::GT *part =
+          (typename A::GT *)P.dtime_part + ((int64_t)(blockIdx.x % DTIME_BINS) * P.H + h) * P.nb;
+      for (int x = tid; x < P.nb; x += THREADS) {
+        typename A::L v = 0;
+        for (int c = 0; c < 1 << P.time_cs; ++c) {
+          v += tacc[(x << P.time_cs) + c];
+          tacc[(x << P.time_cs) + c] = 0;
+        }
+        if (v != 0) atomicAdd(&part[x], (typename A::GT)v);
+      }
+    }
     if constexpr (POS) {   // every diagonal of the last window is final
       if (tid < 2 * TILE - 1)
         dpos_retire<A>(smx.pwin[(phase - 1) & 1], smx.pwin[phase & 1], tid,
@@ -1617,7 +1634,7 @@ __device__ __forceinline__ void dkv_kernel_init(const KParams &P, DkvSmem<D, POS
                                                 typename TabAcc<DET>::L *tacc, float *dyn,
                                                 int tid0) {
   if (TIME) {
-    for (int x = tid0; x < P.H * P.nb; x += THREADS) tacc[x] = 0;
+    for (int x = tid0; x < P.nb << P.time_cs; x += THREADS) tacc[x] = 0;
   }
   if (tid0 < 2) smx.s.flag[tid0] = 0;
   if constexpr (POS)
@@ -1626,21 +1643,11 @@ __device__ __forceinline__ void dkv_kernel_init(const KParams &P, DkvSmem<D, POS
 
 // Work-group end: the last deferred d_pos sum (a finished diagonal is sent
 // one tile later, after the next wait for the prefetched tiles, because that
-// wait also counts atomics), then this work-group's d_time histogram folded
-// into one of DTIME_BINS partials.
-template <int D, bool POS, bool TIME, bool DET>
-__device__ __forceinline__ void dkv_kernel_fini(const KParams &P, typename TabAcc<DET>::L *tacc,
-                                                int tid0, typename TabAcc<DET>::G *pend_p,
+// wait also counts atomics).
+template <bool POS, bool DET>
+__device__ __forceinline__ void dkv_kernel_fini(typename TabAcc<DET>::G *pend_p,
                                                 typename TabAcc<DET>::G pend_v) {
-  typedef TabAcc<DET> A;
   if (POS && pend_p) atomicAdd(pend_p, pend_v);
-  if (TIME) {
-    lds_barrier();
-    typename A::G *part =
-        (typename A::G *)P.dtime_part + (int64_t)(blockIdx.x % DTIME_BINS) * P.H * P.nb;
-    for (int x = tid0; x < P.H * P.nb; x += THREADS)
-      if (tacc[x] != 0) atomicAdd(&part[x], A::glob(tacc[x]));
-  }
 }
 
 // Backward, both item kinds in one launch over the combined list, whose
@@ -1654,10 +1661,10 @@ attn_bwd_kernel(KParams P) {
   // dS^T of a first tile pair (d=64, see dkv_item)
   __shared__ __attribute__((aligned(16))) u16 dsb[D == 64 ? TILE * DS_STRIDE : 8];
   StreamSmem<D> &sm = smx.s;
-  // dynamic LDS: [H][nb] d_time (double), then the time tables
+  // dynamic LDS: the item's d_time histogram (double), then the time tables
   extern __shared__ double dyn_k[];
   typename A::L *tacc = (typename A::L *)dyn_k;
-  float *dyn = (float *)(dyn_k + P.H * P.nb);
+  float *dyn = (float *)(dyn_k + (TIME ? P.nb << P.time_cs : 0));
   const int tid0 = threadIdx.x;
   const int n_items = P.ctrl[CTRL_N_BWD] * P.H;
   dkv_kernel_init<D, POS, TIME, DET>(P, smx, tacc, dyn, tid0);
@@ -1677,7 +1684,7 @@ attn_bwd_kernel(KParams P) {
                                            nxt, P.fuse_dq0 ? dsb : nullptr);
     }
   }
-  dkv_kernel_fini<D, POS, TIME, DET>(P, tacc, tid0, pend_p, pend_v);
+  dkv_kernel_fini<POS, DET>(pend_p, pend_v);
 }
 
 // Backward, dQ: persistent work-groups pop q-tile items longest first.
@@ -1706,7 +1713,7 @@ attn_bwd_dkv_kernel(KParams P) {
   StreamSmem<D> &sm = smx.s;
   extern __shared__ double dyn_k[];
   typename A::L *tacc = (typename A::L *)dyn_k;
-  float *dyn = (float *)(dyn_k + P.H * P.nb);
+  float *dyn = (float *)(dyn_k + (TIME ? P.nb << P.time_cs : 0));
   const int tid0 = threadIdx.x;
   const int n_items = P.ctrl[CTRL_N_ENTRIES] * P.H;
   dkv_kernel_init<D, POS, TIME, DET>(P, smx, tacc, dyn, tid0);
@@ -1720,7 +1727,7 @@ attn_bwd_dkv_kernel(KParams P) {
     // 5-10% slower on the Zipf batch of 1024 sequences)
     dkv_item<D, POS, TIME, DET, D == 64>(P, smx, dyn, tacc, tid0, P.list[item / P.H],
                                          item % P.H, phase, pend_p, pend_v, nxt);
-  dkv_kernel_fini<D, POS, TIME, DET>(P, tacc, tid0, pend_p, pend_v);
+  dkv_kernel_fini<POS, DET>(pend_p, pend_v);
 }
 
 // ------------------------------------------------------------- launchers
@@ -1747,7 +1754,8 @@ size_t slot_bytes(const Problem &p, bool all) {
 size_t slots_bytes(const Problem &p) { return slot_bytes(p, all_heads(p)); }
 size_t q_dyn_bytes(const Problem &p) { return slots_bytes(p); }
 size_t k_dyn_bytes(const Problem &p) {
-  return p.has_time ? slots_bytes(p) + sizeof(double) * (size_t)p.nb * p.H : 0;
+  return p.has_time ? slots_bytes(p) + (sizeof(double) * (size_t)p.nb << hist_copies_log2(p.nb))
+                    : 0;
 }
 
 KParams make_params(const AttnArgs &a, int32_t *pop, const WorkEntry *list) {
@@ -1774,6 +1782,7 @@ KParams make_params(const AttnArgs &a, int32_t *pop, const WorkEntry *list) {
   P.al2e = a.p.alpha * L2E;
   P.dk_scale_l2 = P.dqk_scale / L2E;
   P.dv_scale_l2 = P.inv_n / L2E;
+  P.time_cs = hist_copies_log2(P.nb);
   P.all_heads = all_heads(a.p) ? 1 : 0;
   P.out_stride = a.p.H * a.p.d;
   return P;

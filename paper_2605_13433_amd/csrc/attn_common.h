@@ -55,17 +55,20 @@ __device__ __forceinline__ bf16x8 read_tr(const u16 *lds, int stride, int krow,
 }
 
 // Table-gradient accumulation types: LDS sums in double and global partials
-// in float, or (deterministic mode) both as 64-bit fixed point, whose
-// integer additions give the same result in any order.
+// in float (d_pos: one per sequence and diagonal) or double (d_time: one per
+// item), or (deterministic mode) all as 64-bit fixed point, whose integer
+// additions give the same result in any order.
 template <bool DET> struct TabAcc {
   typedef double L;
   typedef float G;
+  typedef double GT;
   static __device__ __forceinline__ L lds(float v) { return (double)v; }
   static __device__ __forceinline__ G glob(L v) { return (float)v; }
 };
 template <> struct TabAcc<true> {
   typedef unsigned long long L;
   typedef unsigned long long G;
+  typedef unsigned long long GT;
   static __device__ __forceinline__ L lds(float v) { return to_fix(v); }
   static __device__ __forceinline__ G glob(L v) { return v; }
 };
@@ -75,7 +78,8 @@ template <> struct TabAcc<true> {
 // finalize pass divides out) over one float-exponent time index (the lane's
 // pairs visit non-decreasing indices when timestamps are ordered, so a run
 // ends only when its index changes); a finished run goes to its bucket of
-// the work-group's histogram `hist`.  A run is opened by
+// the item's histogram `hist` (2^cs counters a bucket, see hist_copies).  A run is
+// opened by
 // the first index of the item's first tile (start), so adding needs no test
 // for an empty run.
 template <typename A>
@@ -84,17 +88,27 @@ struct TimeRun {
   float sum = 0.0f;
   int cur = -1;
   __device__ __forceinline__ void start(int k) { cur = cur < 0 ? k : cur; }
-  __device__ __forceinline__ void add(L *hist, int nb, int k, float v) {
+  __device__ __forceinline__ void add(L *hist, int nb, int cs, int k, float v) {
     const bool change = k != cur;
-    if (change) atomicAdd(&hist[bucket_of_index(cur, nb)], A::lds(sum));
+    if (change) atomicAdd(&hist[bucket_of_index(cur, nb) << cs], A::lds(sum));
     sum = change ? v : sum + v;
     cur = k;
   }
-  __device__ __forceinline__ void flush(L *hist, int nb) {
-    if (cur >= 0) atomicAdd(&hist[bucket_of_index(cur, nb)], A::lds(sum));
+  __device__ __forceinline__ void flush(L *hist, int nb, int cs) {
+    if (cur >= 0) atomicAdd(&hist[bucket_of_index(cur, nb) << cs], A::lds(sum));
     cur = -1;
     sum = 0.0f;
   }
 };
+
+// log2 of the counters per bucket of an item's d_time histogram: lanes are
+// spread over them, because neighbouring keys meet in the same bucket and a
+// wave's LDS atomics on one address are served one by one (44 clocks for four
+// lanes, 8 for none).  Up to eight, in at most 4 KB.
+inline int hist_copies_log2(int nb) {
+  int cs = 3;
+  while (cs > 0 && ((int64_t)nb << cs) * 8 > 4096) --cs;
+  return cs;
+}
 
 }  // namespace hstu

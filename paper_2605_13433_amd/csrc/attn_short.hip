@@ -45,7 +45,7 @@ struct SParams {
   u16 *o, *dq, *dk, *dv;
   const u16 *h_dq, *h_dk, *h_dv;             // silu' factors of the gradients (or null)
   int32_t out_stride;                        // row stride of the gradients (elements)
-  void *dpos_part, *dtime_part;              // float, or fixed point (deterministic)
+  void *dpos_part, *dtime_part;              // see TabAcc
   int64_t T;
   int32_t B, H, N, nb, direct, copies;
   float alpha, inv_alpha, neg_al2e, al2e, dqk_scale, dk_scale_l2, dv_scale_l2;
@@ -618,12 +618,12 @@ __device__ __forceinline__ void short_dkv(const SParams &P, ShortBwdSmem<D, DET>
   short_store<D>(&sm.red[0][0], dv, tid, P.dv + at, P.out_stride, e.len - j0, P.dv_scale_l2,
                  P.h_dv ? P.h_dv + at : nullptr);
   if (TIME) {
-    typename A::G *part = (typename A::G *)P.dtime_part +
+    typename A::GT *part = (typename A::GT *)P.dtime_part +
                           ((int64_t)(item % DTIME_BINS) * P.H + h) * P.nb;
     for (int x = tid; x < P.nb; x += S_THREADS) {
       typename A::L v = 0;
       for (int c = 0; c < P.copies; ++c) v += hist[x * P.copies + c];
-      if (v != 0) atomicAdd(&part[x], A::glob(v));
+      if (v != 0) atomicAdd(&part[x], (typename A::GT)v);
     }
   }
 }
@@ -657,8 +657,7 @@ SParams make_params(const AttnArgs &a) {
   P.N = a.p.N;
   P.nb = a.p.has_time ? a.p.nb : 0;
   P.out_stride = a.p.H * a.p.d;
-  P.copies = 8;
-  while (P.copies > 1 && P.copies * P.nb > 1024) P.copies >>= 1;
+  P.copies = 1 << hist_copies_log2(P.nb);
   P.alpha = a.p.alpha;
   P.inv_alpha = 1.0f / a.p.alpha;
   P.neg_al2e = -a.p.alpha * L2E;

@@ -276,8 +276,8 @@ ln_bwd_kernel(const T *__restrict__ dy, const T *__restrict__ u,
 //     offset m = N-1-x sums the per-sequence partials of every sequence
 //     longer than m.  Block = (h, 64 consecutive m); lane = m, waves stride
 //     over the sequences, then a cross-wave sum in LDS.
-//   d_time[h, k]: sum of the DTIME_BINS partial histograms the dK/dV
-//     work-groups folded theirs into.  Block = 64 consecutive (h, k)
+//   d_time[h, k]: sum of the DTIME_BINS partial histograms (double) the dK/dV
+//     items added theirs to.  Block = 64 consecutive (h, k)
 //     columns; waves stride over the bins.
 // Summation order is fixed, so the result is deterministic given the
 // partials.  `scale` multiplies every entry (ln 2 / N: the backward kernel
@@ -290,7 +290,10 @@ constexpr int FIN_WAVES = FIN_THREADS / 64;
 
 template <bool DET> struct FinAcc { typedef float T; };
 template <> struct FinAcc<true> { typedef unsigned long long T; };
+template <bool DET> struct FinTime { typedef double T; };
+template <> struct FinTime<true> { typedef unsigned long long T; };
 __device__ __forceinline__ float fin_value(float x) { return x; }
+__device__ __forceinline__ float fin_value(double x) { return (float)x; }
 __device__ __forceinline__ float fin_value(unsigned long long x) {
   return (float)((double)(long long)x * (1.0 / FIX_ONE));
 }
@@ -304,8 +307,10 @@ finalize_tables_kernel(const SeqInfo *__restrict__ info, int B,
                        int width, float *__restrict__ d_time, float scale) {
   typedef typename FinAcc<DET>::T A;
   const A *pos_part = (const A *)pos_part_v;
-  const A *time_part = (const A *)time_part_v;
+  typedef typename FinTime<DET>::T AT;
+  const AT *time_part = (const AT *)time_part_v;
   __shared__ A red[FIN_WAVES][64];
+  __shared__ AT red_t[FIN_WAVES][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   A acc = 0;
   if ((int)blockIdx.x < pos_blocks) {
@@ -346,13 +351,14 @@ finalize_tables_kernel(const SeqInfo *__restrict__ info, int B,
     }
   } else {
     const int c = ((int)blockIdx.x - pos_blocks) * 64 + lane;
+    AT acc_t = 0;
     if (c < width)
-      for (int g = wv; g < n_parts; g += FIN_WAVES) acc += time_part[(int64_t)g * width + c];
-    red[wv][lane] = acc;
+      for (int g = wv; g < n_parts; g += FIN_WAVES) acc_t += time_part[(int64_t)g * width + c];
+    red_t[wv][lane] = acc_t;
     __syncthreads();
     if (wv == 0 && c < width) {
-      A s = 0;
-      for (int x = 0; x < FIN_WAVES; ++x) s += red[x][lane];
+      AT s = 0;
+      for (int x = 0; x < FIN_WAVES; ++x) s += red_t[x][lane];
       d_time[c] = scale * fin_value(s);
     }
   }
