@@ -1742,10 +1742,16 @@ int persistent_grid(K kernel, size_t dyn, int64_t items, int dev, int block = TH
 }
 
 // Time tables: one slot of KTAB + nb floats per head when all heads fit in
-// this budget (staged once per work-group), else a single per-item slot.
+// this budget (staged once per work-group), else a single per-item slot.  At
+// d=64 the forward holds half as much: 8 heads of 128 buckets (23 KB) would
+// leave its third work-group no room on a CU (128 power-law sequences 60.6 ->
+// 56.5 us with per-item slots), while the backward, at two, prefers them all
+// (400 sequences of up to 300 tokens 407 us against 424).
 constexpr size_t ALL_HEADS_BUDGET = 32 * 1024;
-bool all_heads(const Problem &p) {
-  const size_t budget = p.d == 64 ? ALL_HEADS_BUDGET : ALL_HEADS_BUDGET / 4;
+bool all_heads(const Problem &p, bool fwd = false) {
+  const size_t budget = p.d != 64 ? ALL_HEADS_BUDGET / 4
+                        : fwd     ? ALL_HEADS_BUDGET / 2
+                                  : ALL_HEADS_BUDGET;
   return p.has_time && sizeof(float) * (size_t)p.H * (KTAB + p.nb) <= budget;
 }
 size_t slot_bytes(const Problem &p, bool all) {
@@ -1753,6 +1759,7 @@ size_t slot_bytes(const Problem &p, bool all) {
 }
 size_t slots_bytes(const Problem &p) { return slot_bytes(p, all_heads(p)); }
 size_t q_dyn_bytes(const Problem &p) { return slots_bytes(p); }
+size_t fwd_dyn_bytes(const Problem &p) { return slot_bytes(p, all_heads(p, true)); }
 size_t k_dyn_bytes(const Problem &p) {
   return p.has_time ? slots_bytes(p) + (sizeof(double) * (size_t)p.nb << hist_copies_log2(p.nb))
                     : 0;
@@ -1883,11 +1890,11 @@ int attn_fwd_grid(const Problem &p, int dev) {
   int grid = 1;
   if (fwd_pairs(p))
     HSTU_DISPATCH_Q(attn_fwd_kernel, p.d, p.has_pos, p.has_time, 2,
-                    grid = persistent_grid(kfn, q_dyn_bytes(p), p.max_entries * p.H, dev,
+                    grid = persistent_grid(kfn, fwd_dyn_bytes(p), p.max_entries * p.H, dev,
                                            2 * THREADS));
   else
     HSTU_DISPATCH_Q(attn_fwd_kernel, p.d, p.has_pos, p.has_time, 1,
-                    grid = persistent_grid(kfn, q_dyn_bytes(p), p.max_entries * p.H, dev));
+                    grid = persistent_grid(kfn, fwd_dyn_bytes(p), p.max_entries * p.H, dev));
   return grid;
 }
 
@@ -1931,13 +1938,14 @@ hipError_t launch_attn_fwd_bf16(const AttnArgs &a, void *o, bool direct, hipStre
   KParams P = make_params(a, (int32_t *)(ws + a.L.ctrl) + CTRL_POP_FWD,
                           (const WorkEntry *)(ws + (pairs ? a.L.list_p : a.L.list_q)));
   P.out0 = (u16 *)o;
+  P.all_heads = all_heads(p, true) ? 1 : 0;
   const int grid = attn_fwd_grid(p, current_dev());
   if (pairs)
     HSTU_DISPATCH_Q(attn_fwd_kernel, p.d, p.has_pos, p.has_time, 2,
-                    hipLaunchKernelGGL(kfn, dim3(grid), dim3(2 * THREADS), q_dyn_bytes(p), s, P));
+                    hipLaunchKernelGGL(kfn, dim3(grid), dim3(2 * THREADS), fwd_dyn_bytes(p), s, P));
   else
     HSTU_DISPATCH_Q(attn_fwd_kernel, p.d, p.has_pos, p.has_time, 1,
-                    hipLaunchKernelGGL(kfn, dim3(grid), dim3(THREADS), q_dyn_bytes(p), s, P));
+                    hipLaunchKernelGGL(kfn, dim3(grid), dim3(THREADS), fwd_dyn_bytes(p), s, P));
   return hipGetLastError();
 }
 

@@ -31,6 +31,7 @@
 
 #include "internal.h"
 #include "device.h"
+#include "attn_common.h"
 #include "sched_impl.h"
 
 namespace hstu {
@@ -40,9 +41,10 @@ namespace {
 constexpr int F32_THREADS = 256;           // 4 waves
 constexpr int F32_WAVES = F32_THREADS / 64;
 constexpr int FT = 32;                     // rows of an item and of a streamed tile
-// A work-group's d_time histogram sits in LDS up to this many buckets (16
-// KB); above it every finished run goes straight to the table.
-constexpr int F32_LDS_BUCKETS = 2048;
+// A work-group's d_time histogram sits in LDS (hist_copies_log2 counters a
+// bucket) up to this many buckets; above it every finished run goes straight
+// to the table.
+constexpr int F32_LDS_BUCKETS = 512;
 
 struct F32Params {
   const float *q, *k, *v, *dO;
@@ -61,6 +63,7 @@ struct F32Params {
   const int64_t *off;
   int64_t T;
   int32_t B, direct, max_entries;
+  int32_t time_cs;                // log2 of the histogram's counters per bucket
 };
 
 // K = 2 step of a 32 x 32 product: lane l gives A[l % 32][l / 32] and
@@ -505,7 +508,15 @@ __device__ __forceinline__ void f32_dkv_item(const F32Params &P, F32BwdSmem<D, D
                           : nullptr;
   for (int x = lane; x < 4 * FT; x += 64) (&sm.win[w][0][0])[x] = 0;
   if (time_g && in_lds)
-    for (int x = tid; x < P.nb; x += F32_THREADS) hist[x] = 0;
+    for (int x = tid; x < P.nb << P.time_cs; x += F32_THREADS) hist[x] = 0;
+  // runs of equal buckets down this lane's queries, also from tile to tile
+  // (ordered timestamps change bucket rarely), summed like the table
+  typename A::T run = 0;
+  int cur = -1;
+  auto flush = [&]() {
+    if (in_lds) atomicAdd(&hist[(cur << P.time_cs) + (lane & ((1 << P.time_cs) - 1))], run);
+    else atomicAdd(&gt[cur], run);
+  };
   __syncthreads();
   f32x16 dk[D / 32], dv[D / 32];
 #pragma unroll
@@ -557,34 +568,32 @@ __device__ __forceinline__ void f32_dkv_item(const F32Params &P, F32BwdSmem<D, D
       if (v != 0 && m >= 0 && m < e.len) atomicAdd(&gp[P.N - 1 - m], v);
     }
     if (time_g) {
-      // runs of equal buckets down this lane's queries (ordered timestamps
-      // change bucket rarely), summed like the table
-      typename A::T run = 0;
-      int cur = bk.at(0);
+      cur = cur < 0 ? bk.at(0) : cur;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         if (bk.at(r) != cur) {
-          if (in_lds) atomicAdd(&hist[cur], run);
-          else atomicAdd(&gt[cur], run);
+          flush();
           run = 0;
           cur = bk.at(r);
         }
         run += A::of(ds[r]);
       }
-      if (in_lds) atomicAdd(&hist[cur], run);
-      else atomicAdd(&gt[cur], run);
     }
     tile_accumulate<D>(os, a, edge, ok, l32, g, dv);
     tile_accumulate<D>(qs, ds, edge, ok, l32, g, dk);
     wave_lds_fence();
   }
+  if (time_g && cur >= 0) flush();
   sum_store<D>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dk, tid,
                P.dk + ((e.start + j0) * P.H + h) * D, P.H * D, e.len - j0, P.alpha);
   sum_store<D>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dv, tid,
                P.dv + ((e.start + j0) * P.H + h) * D, P.H * D, e.len - j0, 1.0f);
   if (time_g && in_lds)
-    for (int x = tid; x < P.nb; x += F32_THREADS)
-      if (hist[x] != 0) atomicAdd(&gt[x], hist[x]);
+    for (int x = tid; x < P.nb; x += F32_THREADS) {
+      typename A::T v = 0;
+      for (int c = 0; c < 1 << P.time_cs; ++c) v += hist[(x << P.time_cs) + c];
+      if (v != 0) atomicAdd(&gt[x], v);
+    }
 }
 
 // Both item kinds of the backward in one launch, a dK/dV and a dQ item in
@@ -697,7 +706,9 @@ hipError_t launch_attn_bwd_f32(const AttnArgs &a, const void *dO, void *dq,
     P.dv = (float *)dv;
     P.acc_pos = st_pos;
     P.acc_time = st_time;
-    const size_t dyn = d_time && p.nb <= F32_LDS_BUCKETS ? sizeof(double) * (size_t)p.nb : 0;
+    P.time_cs = hist_copies_log2(p.nb);
+    const size_t dyn =
+        d_time && p.nb <= F32_LDS_BUCKETS ? sizeof(double) * (size_t)p.nb << P.time_cs : 0;
     auto kfn = p.deterministic
                    ? (p.d == 32 ? f32_bwd_kernel<32, true>
                                 : p.d == 64 ? f32_bwd_kernel<64, true> : f32_bwd_kernel<128, true>)
