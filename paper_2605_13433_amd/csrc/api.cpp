@@ -201,11 +201,10 @@ Layout make_layout(const Problem &p, bool for_bwd, int dev) {
   // each kind runs at its own occupancy.
   L.bwd_combined = bf16_bwd && p.max_entries * p.H < (int64_t)BWD_COMBINED_ITEMS_PER_WG *
                                                       std::max(L.bwd_grid_both, 1);
-  // Table-gradient partials: 8 bytes per entry, which the deterministic
-  // backward uses as 64-bit fixed point and the default one as float (in
-  // the first half).  bf16: per-sequence diagonal partials and DTIME_BINS
-  // histograms; fp32: one table-shaped fixed-point staging buffer each
-  // (used by the deterministic mode only).
+  // Table-gradient partials: 8 bytes per entry, 64-bit fixed point in the
+  // deterministic backward; in the default one double, but the per-sequence
+  // diagonal partials float (in the first half).  bf16: per-sequence diagonal
+  // partials and DTIME_BINS histograms; fp32: one table-shaped buffer each.
   const bool f32_bwd = for_bwd && p.dtype == HSTU_F32;
   const size_t span = 2 * (size_t)p.N - 1;
   L.dpos_part = !p.has_pos ? 0

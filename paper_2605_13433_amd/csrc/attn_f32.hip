@@ -6,12 +6,13 @@
 // float64 or 64-bit fixed point).
 //
 // An item is a 32-row half of one 64-row work-list tile of one head: 32
-// queries for the forward and dQ, 32 keys for dK/dV.  The four waves of a
-// work-group take every fourth 32-row tile of the item's streamed side, each
-// on its own -- a wave stages its tile in its own part of the LDS, so the
-// loop has no barrier; each operand's loads are in flight under the product
-// before it, through one set of registers -- and their partial sums are added through LDS in wave order at
-// the end (the result does not depend on timing).
+// queries for the forward and dQ, 32 keys for dK/dV.  The four waves (NW; two
+// for batches of many short sequences, two_waves) of a work-group take every
+// fourth 32-row tile of the item's streamed side, each on its own -- a wave
+// stages its tile in its own part of the LDS, so the loop has no barrier; each
+// operand's loads are in flight under the product before it, through one set of
+// registers -- and their partial sums are added through LDS in wave order at the
+// end (the result does not depend on timing).
 //
 // What bounds it: a 32 x 32 tile is D/2 matrix instructions of 64 cycles for
 // every product, and a batch of short sequences is as long as its longest
@@ -24,7 +25,7 @@
 // rows c_row(r, 0) and c_row(r, 1).
 // Measured against one thread per row on the vector ALUs (48 power-law
 // sequences of 16..512 tokens, H = 4, d = 64, both biases): forward 582 ->
-// 32 us, backward 7796 -> 107 us (6886 of them were one double atomic on a
+// 32 us, backward 7796 -> 103 us (6886 of them were one double atomic on a
 // table entry per pair), error against 64 bits 4.3e-7 -> 3.6e-7; four
 // sequences of up to 64 tokens, H = 2, d = 32: forward 27 -> 6.4 us.
 #include <algorithm>
@@ -38,8 +39,6 @@ namespace hstu {
 
 namespace {
 
-constexpr int F32_THREADS = 256;           // 4 waves
-constexpr int F32_WAVES = F32_THREADS / 64;
 constexpr int FT = 32;                     // rows of an item and of a streamed tile
 // A work-group's d_time histogram sits in LDS (hist_copies_log2 counters a
 // bucket) up to this many buckets; above it every finished run goes straight
@@ -196,10 +195,10 @@ __device__ __forceinline__ void tile_accumulate(float *lds, const float (&p)[16]
       acc[db] = mfma2(lds[c_row(r, g) * F32_ROW<D> + 32 * db + l32], p[r], acc[db]);
 }
 
-// Sum of the four waves' accumulators (each through its own LDS part, in
+// Sum of the NW waves' accumulators (each through its own LDS part, in
 // wave order) and the store of the item's rows (those below `valid`) times
 // `scale`.
-template <int D>
+template <int D, int NW>
 __device__ __forceinline__ void sum_store(float *lds0, int part, const f32x16 (&acc)[D / 32],
                                           int tid, float *out, int row_stride, int valid,
                                           float scale) {
@@ -214,12 +213,12 @@ __device__ __forceinline__ void sum_store(float *lds0, int part, const f32x16 (&
           make_float4(acc[db][4 * q], acc[db][4 * q + 1], acc[db][4 * q + 2], acc[db][4 * q + 3]);
   __syncthreads();
 #pragma unroll
-  for (int x = 0; x < FT * D / 4 / F32_THREADS; ++x) {
-    const int ch = tid + F32_THREADS * x, row = ch / (D / 4), col = ch % (D / 4);
+  for (int x = 0; x < FT * D / 4 / (64 * NW); ++x) {
+    const int ch = tid + 64 * NW * x, row = ch / (D / 4), col = ch % (D / 4);
     if (row >= valid) continue;
     float4 s = *(const float4 *)(lds0 + row * F32_ROW<D> + 4 * col);
 #pragma unroll
-    for (int w = 1; w < F32_WAVES; ++w) {
+    for (int w = 1; w < NW; ++w) {
       const float4 t = *(const float4 *)(lds0 + w * part + row * F32_ROW<D> + 4 * col);
       s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
     }
@@ -331,14 +330,15 @@ __device__ __forceinline__ bool item_of(const F32Params &P, const WorkEntry *lis
   return row0 < e.len;
 }
 
-template <int D>
+template <int D, int NW>
 struct F32FwdSmem {
-  float tile[F32_WAVES][2][FT * F32_ROW<D>];     // K, V of each wave's tile
-  int64_t ts[F32_WAVES][FT];
+  float tile[NW][2][FT * F32_ROW<D>];     // K, V of each wave's tile
+  int64_t ts[NW][FT];
 };
 
-template <int D>
-__device__ __forceinline__ void f32_fwd_item(const F32Params &P, F32FwdSmem<D> &sm, int64_t item) {
+template <int D, int NW>
+__device__ __forceinline__ void f32_fwd_item(const F32Params &P, F32FwdSmem<D, NW> &sm,
+                                             int64_t item) {
   WorkEntry e;
   int h, i0;
   if (!item_of(P, P.list_q, item, e, h, i0)) return;
@@ -360,7 +360,7 @@ __device__ __forceinline__ void f32_fwd_item(const F32Params &P, F32FwdSmem<D> &
     for (int r = 0; r < 16; ++r) acc[db][r] = 0.0f;
 
   const int last = i0 / FT;
-  for (int kt = w; kt <= last; kt += F32_WAVES) {
+  for (int kt = w; kt <= last; kt += NW) {
     const int j0 = FT * kt;
     t.store(ks, lane);
     stage_ts(P, e, j0, sm.ts[w], lane);
@@ -369,7 +369,7 @@ __device__ __forceinline__ void f32_fwd_item(const F32Params &P, F32FwdSmem<D> &
     f32x16 s = tile_scores<D>(ks, qreg, l32, g);
     t.store(vs, lane);
     wave_lds_fence();
-    t.load(P, rk, j0 + FT * F32_WAVES, lane);
+    t.load(P, rk, j0 + FT * NW, lane);
     Buckets bk;
     add_bias(P, bias, s, j0 - i, 1, sm.ts[w], g, bk);
     const bool edge = kt == last;
@@ -385,19 +385,19 @@ __device__ __forceinline__ void f32_fwd_item(const F32Params &P, F32FwdSmem<D> &
     tile_accumulate<D>(vs, a, edge, ok, l32, g, acc);
     wave_lds_fence();
   }
-  sum_store<D>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, acc, tid,
+  sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, acc, tid,
                P.o + ((e.start + i0) * P.H + h) * D, P.H * D, e.len - i0, 1.0f);
 }
 
-template <int D>
-__global__ void __launch_bounds__(F32_THREADS, D == 128 ? 1 : 2)
+template <int D, int NW>
+__global__ void __launch_bounds__(64 * NW, D == 128 ? 1 : 2)
 f32_fwd_kernel(F32Params P) {
-  __shared__ __attribute__((aligned(16))) F32FwdSmem<D> sm;
+  __shared__ __attribute__((aligned(16))) F32FwdSmem<D, NW> sm;
   if (P.direct && blockIdx.x == 0 && threadIdx.x == 0)
     const_cast<int32_t *>(P.ctrl)[CTRL_STATUS] = HSTU_SEQ_UNCHECKED;
   const int64_t n_items = 2 * (int64_t)(P.direct ? P.max_entries : P.ctrl[CTRL_N_ENTRIES]) * P.H;
   for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-    f32_fwd_item<D>(P, sm, item);
+    f32_fwd_item<D, NW>(P, sm, item);
     __syncthreads();
   }
 }
@@ -415,17 +415,17 @@ template <> struct F32Tab<true> {
   static __device__ __forceinline__ T of(float v) { return to_fix(v); }
 };
 
-template <int D, bool DET>
+template <int D, bool DET, int NW>
 struct F32BwdSmem {
-  float tile[F32_WAVES][2][FT * F32_ROW<D>];     // K, V or Q, dO of each wave's tile
-  int64_t ts[F32_WAVES][FT];
+  float tile[NW][2][FT * F32_ROW<D>];     // K, V or Q, dO of each wave's tile
+  int64_t ts[NW][FT];
   // diagonal sums of each wave's tile, one copy per lane group (the lanes of
   // an atomic hit distinct slots)
-  typename F32Tab<DET>::T win[F32_WAVES][2][2 * FT];
+  typename F32Tab<DET>::T win[NW][2][2 * FT];
 };
 
-template <int D, bool DET>
-__device__ __forceinline__ void f32_dq_item(const F32Params &P, F32BwdSmem<D, DET> &sm,
+template <int D, bool DET, int NW>
+__device__ __forceinline__ void f32_dq_item(const F32Params &P, F32BwdSmem<D, DET, NW> &sm,
                                             int64_t item) {
   WorkEntry e;
   int h, i0;
@@ -448,7 +448,7 @@ __device__ __forceinline__ void f32_dq_item(const F32Params &P, F32BwdSmem<D, DE
     for (int r = 0; r < 16; ++r) acc[db][r] = 0.0f;
 
   const int last = i0 / FT;
-  for (int kt = w; kt <= last; kt += F32_WAVES) {
+  for (int kt = w; kt <= last; kt += NW) {
     const int j0 = FT * kt;
     t.store(ks, lane);
     stage_ts(P, e, j0, sm.ts[w], lane);
@@ -457,7 +457,7 @@ __device__ __forceinline__ void f32_dq_item(const F32Params &P, F32BwdSmem<D, DE
     f32x16 s = tile_scores<D>(ks, qreg, l32, g);
     t.store(vs, lane);
     wave_lds_fence();
-    t.load(P, rk, j0 + FT * F32_WAVES, lane);
+    t.load(P, rk, j0 + FT * NW, lane);
     const f32x16 da = tile_scores<D>(vs, oreg, l32, g);
     Buckets bk;
     add_bias(P, bias, s, j0 - i, 1, sm.ts[w], g, bk);
@@ -477,12 +477,12 @@ __device__ __forceinline__ void f32_dq_item(const F32Params &P, F32BwdSmem<D, DE
     tile_accumulate<D>(ks, ds, edge, ok, l32, g, acc);
     wave_lds_fence();
   }
-  sum_store<D>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, acc, tid,
+  sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, acc, tid,
                P.dq + ((e.start + i0) * P.H + h) * D, P.H * D, e.len - i0, P.alpha);
 }
 
-template <int D, bool DET>
-__device__ __forceinline__ void f32_dkv_item(const F32Params &P, F32BwdSmem<D, DET> &sm,
+template <int D, bool DET, int NW>
+__device__ __forceinline__ void f32_dkv_item(const F32Params &P, F32BwdSmem<D, DET, NW> &sm,
                                              typename F32Tab<DET>::T *hist, int64_t item) {
   typedef F32Tab<DET> A;
   WorkEntry e;
@@ -508,7 +508,7 @@ __device__ __forceinline__ void f32_dkv_item(const F32Params &P, F32BwdSmem<D, D
                           : nullptr;
   for (int x = lane; x < 4 * FT; x += 64) (&sm.win[w][0][0])[x] = 0;
   if (time_g && in_lds)
-    for (int x = tid; x < P.nb << P.time_cs; x += F32_THREADS) hist[x] = 0;
+    for (int x = tid; x < P.nb << P.time_cs; x += 64 * NW) hist[x] = 0;
   // runs of equal buckets down this lane's queries, also from tile to tile
   // (ordered timestamps change bucket rarely), summed like the table
   typename A::T run = 0;
@@ -524,7 +524,7 @@ __device__ __forceinline__ void f32_dkv_item(const F32Params &P, F32BwdSmem<D, D
 #pragma unroll
     for (int r = 0; r < 16; ++r) { dk[db][r] = 0.0f; dv[db][r] = 0.0f; }
 
-  for (int qt = first + w; qt < tiles; qt += F32_WAVES) {
+  for (int qt = first + w; qt < tiles; qt += NW) {
     const int i0 = FT * qt;
     t.store(qs, lane);
     stage_ts(P, e, i0, sm.ts[w], lane);
@@ -533,7 +533,7 @@ __device__ __forceinline__ void f32_dkv_item(const F32Params &P, F32BwdSmem<D, D
     f32x16 s = tile_scores<D>(qs, kreg, l32, g);
     t.store(os, lane);
     wave_lds_fence();
-    t.load(P, rq, i0 + FT * F32_WAVES, lane);
+    t.load(P, rq, i0 + FT * NW, lane);
     const f32x16 da = tile_scores<D>(os, vreg, l32, g);
     Buckets bk;
     add_bias(P, bias, s, j - i0, -1, sm.ts[w], g, bk);
@@ -584,12 +584,12 @@ __device__ __forceinline__ void f32_dkv_item(const F32Params &P, F32BwdSmem<D, D
     wave_lds_fence();
   }
   if (time_g && cur >= 0) flush();
-  sum_store<D>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dk, tid,
+  sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dk, tid,
                P.dk + ((e.start + j0) * P.H + h) * D, P.H * D, e.len - j0, P.alpha);
-  sum_store<D>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dv, tid,
+  sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dv, tid,
                P.dv + ((e.start + j0) * P.H + h) * D, P.H * D, e.len - j0, 1.0f);
   if (time_g && in_lds)
-    for (int x = tid; x < P.nb; x += F32_THREADS) {
+    for (int x = tid; x < P.nb; x += 64 * NW) {
       typename A::T v = 0;
       for (int c = 0; c < 1 << P.time_cs; ++c) v += hist[(x << P.time_cs) + c];
       if (v != 0) atomicAdd(&gt[x], v);
@@ -598,15 +598,15 @@ __device__ __forceinline__ void f32_dkv_item(const F32Params &P, F32BwdSmem<D, D
 
 // Both item kinds of the backward in one launch, a dK/dV and a dQ item in
 // turn down the longest-first lists, so that neither kind's tail is alone.
-template <int D, bool DET>
-__global__ void __launch_bounds__(F32_THREADS, D == 128 ? 1 : 2)
+template <int D, bool DET, int NW>
+__global__ void __launch_bounds__(64 * NW, D == 128 ? 1 : 2)
 f32_bwd_kernel(F32Params P) {
-  __shared__ __attribute__((aligned(16))) F32BwdSmem<D, DET> sm;
+  __shared__ __attribute__((aligned(16))) F32BwdSmem<D, DET, NW> sm;
   extern __shared__ double dyn_f32[];              // d_time histogram of the item's head
   const int64_t n_items = 4 * (int64_t)P.ctrl[CTRL_N_ENTRIES] * P.H;
   for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-    if (item & 1) f32_dq_item<D, DET>(P, sm, item >> 1);
-    else f32_dkv_item<D, DET>(P, sm, (typename F32Tab<DET>::T *)dyn_f32, item >> 1);
+    if (item & 1) f32_dq_item<D, DET, NW>(P, sm, item >> 1);
+    else f32_dkv_item<D, DET, NW>(P, sm, (typename F32Tab<DET>::T *)dyn_f32, item >> 1);
     __syncthreads();
   }
 }
@@ -638,6 +638,34 @@ __global__ void f32_tables_out_kernel(const void *pos, int64_t n_pos, const void
 dim3 f32_grid(const Problem &p, int per) {
   return dim3((unsigned)std::max<int64_t>(
       1, std::min<int64_t>((int64_t)1 << 20, per * p.max_entries * p.H)));
+}
+
+// Two waves a work-group instead of four where sequences have at most four
+// 32-row tiles and the work-groups (`per` to a list entry and head) queue for
+// the device: the third and fourth wave of most items would have no tile, and
+// only hold their place.  Forward / backward (us), four waves and two: 300
+// sequences of up to 100 tokens, 8 heads of 64, 149 / 547 and 104 / 425; 200 of
+// up to 110, 8 heads of 128, 272 / 954 and 182 / 599; just above the line, 24 of
+// 100..128, 4 heads of 64, 16 / 54 and 16 / 49; but 4 of up to 700, 4 heads of 64,
+// 37 / 83 and 60 / 130, where the chain of tiles doubles.  Resident to a compute
+// unit with four waves: one at d = 128, three of the d = 32 forward (48 of
+// 100..128, 4 heads, which all fit: 20.0 with four and 21.2 with two), else two.
+bool two_waves(const Problem &p, int per) {
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  const int resident = p.d == 128 ? 1 : p.d == 32 && per == 2 ? 3 : 2;
+  return p.N <= 4 * FT && per * p.max_entries * p.H > resident * (int64_t)device_info(dev).num_cu;
+}
+
+template <int NW>
+auto pick_fwd(int d) {
+  return d == 32 ? f32_fwd_kernel<32, NW> : d == 64 ? f32_fwd_kernel<64, NW>
+                                                    : f32_fwd_kernel<128, NW>;
+}
+template <bool DET, int NW>
+auto pick_bwd(int d) {
+  return d == 32 ? f32_bwd_kernel<32, DET, NW> : d == 64 ? f32_bwd_kernel<64, DET, NW>
+                                                         : f32_bwd_kernel<128, DET, NW>;
 }
 
 F32Params make_params(const AttnArgs &a) {
@@ -672,9 +700,9 @@ hipError_t launch_attn_fwd_f32(const AttnArgs &a, void *o, bool direct, hipStrea
     P.direct = 1;
   }
   P.o = (float *)o;
-  auto kfn = a.p.d == 32 ? f32_fwd_kernel<32> : a.p.d == 64 ? f32_fwd_kernel<64>
-                                                            : f32_fwd_kernel<128>;
-  hipLaunchKernelGGL(kfn, f32_grid(a.p, 2), dim3(F32_THREADS), 0, s, P);
+  const bool two = two_waves(a.p, 2);
+  auto kfn = two ? pick_fwd<2>(a.p.d) : pick_fwd<4>(a.p.d);
+  hipLaunchKernelGGL(kfn, f32_grid(a.p, 2), dim3(two ? 128 : 256), 0, s, P);
   return hipGetLastError();
 }
 
@@ -709,13 +737,10 @@ hipError_t launch_attn_bwd_f32(const AttnArgs &a, const void *dO, void *dq,
     P.time_cs = hist_copies_log2(p.nb);
     const size_t dyn =
         d_time && p.nb <= F32_LDS_BUCKETS ? sizeof(double) * (size_t)p.nb << P.time_cs : 0;
-    auto kfn = p.deterministic
-                   ? (p.d == 32 ? f32_bwd_kernel<32, true>
-                                : p.d == 64 ? f32_bwd_kernel<64, true> : f32_bwd_kernel<128, true>)
-                   : (p.d == 32 ? f32_bwd_kernel<32, false>
-                                : p.d == 64 ? f32_bwd_kernel<64, false>
-                                            : f32_bwd_kernel<128, false>);
-    hipLaunchKernelGGL(kfn, f32_grid(p, 4), dim3(F32_THREADS), dyn, s, P);
+    const bool two = two_waves(p, 4);
+    auto kfn = p.deterministic ? (two ? pick_bwd<true, 2>(p.d) : pick_bwd<true, 4>(p.d))
+                               : (two ? pick_bwd<false, 2>(p.d) : pick_bwd<false, 4>(p.d));
+    hipLaunchKernelGGL(kfn, f32_grid(p, 4), dim3(two ? 128 : 256), dyn, s, P);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (tables) {

@@ -14,9 +14,9 @@ namespace hstu {
 // the work lists the scheduler builds.
 constexpr int TILE = 64;
 
-// The dK/dV work-groups fold their d_time histograms into this many partial
-// tables (work-group index mod DTIME_BINS) with float atomics; the finalize
-// kernel sums the bins in a fixed order.
+// The dK/dV items fold their head's d_time histogram into this many partial
+// tables (work-group index mod DTIME_BINS) with double (or fixed-point) atomics;
+// the finalize kernel sums the bins in a fixed order.
 constexpr int DTIME_BINS = 16;
 
 // Fixed-point unit of the deterministic backward's table-gradient partials:

@@ -42,6 +42,20 @@ def test_edges(d, pos, time, nb):
 
 
 @pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("N", [128, 129])
+def test_many_short_sequences(d, N):
+    """Either side of the line (max_len 128) where work-groups of two waves
+    take over from four, with more items than run at once."""
+    rng = np.random.default_rng(930 + d)
+    lengths = [1, 32, 33, 64, 97, 127, 128] + [int(x) for x in rng.integers(0, 129, size=70)]
+    w = inputs.make_workload(lengths, H=4, d=d, N=N, dtype=torch.float32, seed=930 + d)
+    got = run_gpu(w)
+    ref = dict(oracle.fwd_workload(w), **oracle.bwd_workload(w))
+    for n in ("o", "y", "dq", "dk", "dv", "du", "d_pos", "d_time"):
+        check(n, got[n], ref[n], TOL[w.dtype])
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
 def test_nonfinite_rows_stay_causal(d):
     """An infinite v (or k) row at position p leaves o (and dq) of the rows
     before p as they are, and an infinite dy row the dk and dv of the keys
