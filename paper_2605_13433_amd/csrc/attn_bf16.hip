@@ -91,6 +91,8 @@ struct KParams {
   // dV stores take dqk_scale / log2e and 1 / (N log2e)
   float al2e, dk_scale_l2, dv_scale_l2;
   int32_t time_cs;        // log2 of the d_time histogram's counters per bucket
+  int32_t time_hs;        // its counters per head; 0: the item's head only
+  int32_t time_n;         // its counters in all
   int32_t all_heads;      // time tables of every head staged once per work-group
   const int64_t *off;     // direct forward
   int64_t T;
@@ -1238,6 +1240,24 @@ __device__ __forceinline__ f32x16 dq0_block(const u16 *dsb, const u16 *kst, int 
   return dq;
 }
 
+// d_time sums of `heads` heads from `h0` on, out of the LDS histogram into one of
+// DTIME_BINS partial tables; the counters are cleared.
+template <bool DET>
+__device__ __forceinline__ void time_fold(const KParams &P, typename TabAcc<DET>::L *tacc,
+                                          int tid, int h0, int heads) {
+  typedef TabAcc<DET> A;
+  typename A::GT *part =
+      (typename A::GT *)P.dtime_part + ((int64_t)(blockIdx.x % DTIME_BINS) * P.H + h0) * P.nb;
+  for (int x = tid; x < heads * P.nb; x += THREADS) {
+    typename A::L v = 0;
+    for (int c = 0; c < 1 << P.time_cs; ++c) {
+      v += tacc[(x << P.time_cs) + c];
+      tacc[(x << P.time_cs) + c] = 0;
+    }
+    if (v != 0) atomicAdd(&part[x], (typename A::GT)v);
+  }
+}
+
 // One k-stationary item: dV_j, dK_j for a 64-row key tile of one head over
 // its query tiles, with the table gradients (d_pos through the sheared tile
 // and the rolling diagonal window, d_time through per-lane index runs).
@@ -1321,7 +1341,7 @@ __device__ __forceinline__ void dkv_item(const KParams &P, DkvSmem<D, POS, DET> 
       ktab = item_time_slot(P, dyn, h, tid, P.inv_alpha);
     }
     TimeRun<A> run;                           // fast path: by float-exponent index
-    typename A::L *my_t = TIME ? tacc + (lane & ((1 << P.time_cs) - 1)) : nullptr;
+    typename A::L *my_t = TIME ? tacc + h * P.time_hs + (lane & ((1 << P.time_cs) - 1)) : nullptr;
     typename A::G *dp_item = POS ? (typename A::G *)P.dpos_part + si.start * P.H + h : nullptr;
 
     // At d=128 (SPLIT) a wave's dK and dV accumulators together would take
@@ -1586,22 +1606,9 @@ __device__ __forceinline__ void dkv_item(const KParams &P, DkvSmem<D, POS, DET> 
     // close the d_time runs; sum the two query halves, store dK, dV (bf16)
     if (TIME) run.flush(my_t, P.nb, P.time_cs);
     lds_barrier();
-    if (TIME) {
-      // the item's d_time sums go to one of DTIME_BINS partials; cleared for the
-      // next item (whose first step's barriers order it).  One head's
-      // histogram instead of all of them: at d=128 with 8 heads and 128
-      // buckets two work-groups fit a CU's LDS again.
-      typename A::GT *part =
-          (typename A::GT *)P.dtime_part + ((int64_t)(blockIdx.x % DTIME_BINS) * P.H + h) * P.nb;
-      for (int x = tid; x < P.nb; x += THREADS) {
-        typename A::L v = 0;
-        for (int c = 0; c < 1 << P.time_cs; ++c) {
-          v += tacc[(x << P.time_cs) + c];
-          tacc[(x << P.time_cs) + c] = 0;
-        }
-        if (v != 0) atomicAdd(&part[x], (typename A::GT)v);
-      }
-    }
+    // one head's sums leave with the item (its next step's barriers order the
+    // clearing); all heads' stay for the work-group's end
+    if (TIME && P.time_hs == 0) time_fold<DET>(P, tacc, tid, h, 1);
     if constexpr (POS) {   // every diagonal of the last window is final
       if (tid < 2 * TILE - 1)
         dpos_retire<A>(smx.pwin[(phase - 1) & 1], smx.pwin[phase & 1], tid,
@@ -1634,7 +1641,7 @@ __device__ __forceinline__ void dkv_kernel_init(const KParams &P, DkvSmem<D, POS
                                                 typename TabAcc<DET>::L *tacc, float *dyn,
                                                 int tid0) {
   if (TIME) {
-    for (int x = tid0; x < P.nb << P.time_cs; x += THREADS) tacc[x] = 0;
+    for (int x = tid0; x < P.time_n; x += THREADS) tacc[x] = 0;
   }
   if (tid0 < 2) smx.s.flag[tid0] = 0;
   if constexpr (POS)
@@ -1643,11 +1650,17 @@ __device__ __forceinline__ void dkv_kernel_init(const KParams &P, DkvSmem<D, POS
 
 // Work-group end: the last deferred d_pos sum (a finished diagonal is sent
 // one tile later, after the next wait for the prefetched tiles, because that
-// wait also counts atomics).
-template <bool POS, bool DET>
-__device__ __forceinline__ void dkv_kernel_fini(typename TabAcc<DET>::G *pend_p,
+// wait also counts atomics), then the d_time sums of all heads where the
+// work-group kept them.
+template <bool POS, bool TIME, bool DET>
+__device__ __forceinline__ void dkv_kernel_fini(const KParams &P, typename TabAcc<DET>::L *tacc,
+                                                int tid0, typename TabAcc<DET>::G *pend_p,
                                                 typename TabAcc<DET>::G pend_v) {
   if (POS && pend_p) atomicAdd(pend_p, pend_v);
+  if (TIME && P.time_hs != 0) {
+    lds_barrier();
+    time_fold<DET>(P, tacc, tid0, 0, P.H);
+  }
 }
 
 // Backward, both item kinds in one launch over the combined list, whose
@@ -1664,7 +1677,7 @@ attn_bwd_kernel(KParams P) {
   // dynamic LDS: the item's d_time histogram (double), then the time tables
   extern __shared__ double dyn_k[];
   typename A::L *tacc = (typename A::L *)dyn_k;
-  float *dyn = (float *)(dyn_k + (TIME ? P.nb << P.time_cs : 0));
+  float *dyn = (float *)(dyn_k + (TIME ? P.time_n : 0));
   const int tid0 = threadIdx.x;
   const int n_items = P.ctrl[CTRL_N_BWD] * P.H;
   dkv_kernel_init<D, POS, TIME, DET>(P, smx, tacc, dyn, tid0);
@@ -1684,7 +1697,7 @@ attn_bwd_kernel(KParams P) {
                                            nxt, P.fuse_dq0 ? dsb : nullptr);
     }
   }
-  dkv_kernel_fini<POS, DET>(pend_p, pend_v);
+  dkv_kernel_fini<POS, TIME, DET>(P, tacc, tid0, pend_p, pend_v);
 }
 
 // Backward, dQ: persistent work-groups pop q-tile items longest first.
@@ -1713,7 +1726,7 @@ attn_bwd_dkv_kernel(KParams P) {
   StreamSmem<D> &sm = smx.s;
   extern __shared__ double dyn_k[];
   typename A::L *tacc = (typename A::L *)dyn_k;
-  float *dyn = (float *)(dyn_k + (TIME ? P.nb << P.time_cs : 0));
+  float *dyn = (float *)(dyn_k + (TIME ? P.time_n : 0));
   const int tid0 = threadIdx.x;
   const int n_items = P.ctrl[CTRL_N_ENTRIES] * P.H;
   dkv_kernel_init<D, POS, TIME, DET>(P, smx, tacc, dyn, tid0);
@@ -1727,7 +1740,7 @@ attn_bwd_dkv_kernel(KParams P) {
     // 5-10% slower on the Zipf batch of 1024 sequences)
     dkv_item<D, POS, TIME, DET, D == 64>(P, smx, dyn, tacc, tid0, P.list[item / P.H],
                                          item % P.H, phase, pend_p, pend_v, nxt);
-  dkv_kernel_fini<POS, DET>(pend_p, pend_v);
+  dkv_kernel_fini<POS, TIME, DET>(P, tacc, tid0, pend_p, pend_v);
 }
 
 // ------------------------------------------------------------- launchers
@@ -1747,22 +1760,48 @@ int persistent_grid(K kernel, size_t dyn, int64_t items, int dev, int block = TH
 // leave its third work-group no room on a CU (128 power-law sequences 60.6 ->
 // 56.5 us with per-item slots), while the backward, at two, prefers them all
 // (400 sequences of up to 300 tokens 407 us against 424).
+// The dK/dV items at d=128 fill a CU with two work-groups and DKV128_ROOM bytes
+// each beside their tiles: one slot and the d_time histogram.
+enum class Pass { FWD, DQ, DKV };
 constexpr size_t ALL_HEADS_BUDGET = 32 * 1024;
-bool all_heads(const Problem &p, bool fwd = false) {
-  const size_t budget = p.d != 64 ? ALL_HEADS_BUDGET / 4
-                        : fwd     ? ALL_HEADS_BUDGET / 2
-                                  : ALL_HEADS_BUDGET;
+constexpr int64_t DKV128_ROOM = 80 * 1024 - 74784;
+bool all_heads(const Problem &p, Pass pass) {
+  const size_t budget = p.d != 64          ? ALL_HEADS_BUDGET / 4
+                        : pass == Pass::FWD ? ALL_HEADS_BUDGET / 2
+                                            : ALL_HEADS_BUDGET;
+  if (p.d != 64 && pass == Pass::DKV && p.H > 1) return false;
   return p.has_time && sizeof(float) * (size_t)p.H * (KTAB + p.nb) <= budget;
 }
 size_t slot_bytes(const Problem &p, bool all) {
   return p.has_time ? sizeof(float) * (size_t)(all ? p.H : 1) * (KTAB + p.nb) : 0;
 }
-size_t slots_bytes(const Problem &p) { return slot_bytes(p, all_heads(p)); }
-size_t q_dyn_bytes(const Problem &p) { return slots_bytes(p); }
-size_t fwd_dyn_bytes(const Problem &p) { return slot_bytes(p, all_heads(p, true)); }
+size_t slots_bytes(const Problem &p, Pass pass) { return slot_bytes(p, all_heads(p, pass)); }
+size_t q_dyn_bytes(const Problem &p) { return slots_bytes(p, Pass::DQ); }
+size_t fwd_dyn_bytes(const Problem &p) { return slots_bytes(p, Pass::FWD); }
+// The dK/dV work-group's d_time histogram: every head's, folded once at the
+// work-group's end, where those take at most KEEP_BYTES (so that they still have
+// two or more counters a bucket), else the item's head's with more counters,
+// folded at the item's end.  Backward (us), kept and per item: 150 sequences of
+// 15..615 tokens, 4 heads of 128, 128 buckets (4 KB) 331 and 325; 400 of up to
+// 300, 2 heads of 64, 64 buckets (1 KB) 122.4 and 124.3; 2 heads of 128, 32
+// buckets 334.8 and 337.0.  At d=128 the counters fit DKV128_ROOM: 309 sequences
+// of 15..615, 2 heads, took 445 with one work-group a CU, 335 with two.
+struct TimeHist { int cs, hs, n; };
+constexpr int64_t KEEP_BYTES = 2048;
+TimeHist time_hist(const Problem &p) {
+  int64_t room = HIST_BYTES;
+  if (p.d != 64)
+    room = std::min(room, DKV128_ROOM - (int64_t)slots_bytes(p, Pass::DKV));
+  const bool keep = p.H * (int64_t)p.nb * 8 <= std::min(room, KEEP_BYTES);
+  TimeHist t;
+  t.n = keep ? p.H * p.nb : p.nb;
+  t.cs = hist_copies_log2(t.n, room);
+  t.hs = keep ? p.nb << t.cs : 0;
+  t.n <<= t.cs;
+  return t;
+}
 size_t k_dyn_bytes(const Problem &p) {
-  return p.has_time ? slots_bytes(p) + (sizeof(double) * (size_t)p.nb << hist_copies_log2(p.nb))
-                    : 0;
+  return p.has_time ? slots_bytes(p, Pass::DKV) + sizeof(double) * (size_t)time_hist(p).n : 0;
 }
 
 KParams make_params(const AttnArgs &a, int32_t *pop, const WorkEntry *list) {
@@ -1789,8 +1828,9 @@ KParams make_params(const AttnArgs &a, int32_t *pop, const WorkEntry *list) {
   P.al2e = a.p.alpha * L2E;
   P.dk_scale_l2 = P.dqk_scale / L2E;
   P.dv_scale_l2 = P.inv_n / L2E;
-  P.time_cs = hist_copies_log2(P.nb);
-  P.all_heads = all_heads(a.p) ? 1 : 0;
+  const TimeHist th = time_hist(a.p);
+  P.all_heads = 0;
+  P.time_cs = th.cs, P.time_hs = th.hs, P.time_n = th.n;
   P.out_stride = a.p.H * a.p.d;
   return P;
 }
@@ -1938,7 +1978,7 @@ hipError_t launch_attn_fwd_bf16(const AttnArgs &a, void *o, bool direct, hipStre
   KParams P = make_params(a, (int32_t *)(ws + a.L.ctrl) + CTRL_POP_FWD,
                           (const WorkEntry *)(ws + (pairs ? a.L.list_p : a.L.list_q)));
   P.out0 = (u16 *)o;
-  P.all_heads = all_heads(p, true) ? 1 : 0;
+  P.all_heads = all_heads(p, Pass::FWD) ? 1 : 0;
   const int grid = attn_fwd_grid(p, current_dev());
   if (pairs)
     HSTU_DISPATCH_Q(attn_fwd_kernel, p.d, p.has_pos, p.has_time, 2,
@@ -1972,6 +2012,7 @@ hipError_t launch_attn_bwd_bf16(const AttnArgs &a, const void *dO, void *dq, voi
     outputs(P);
     P.dpos_part = a.L.dpos_part ? (void *)(ws + a.L.dpos_part) : nullptr;
     P.dtime_part = a.L.dtime_part ? (void *)(ws + a.L.dtime_part) : nullptr;
+    P.all_heads = all_heads(p, Pass::DKV) ? 1 : 0;
     // must match the scheduler's choice (sched_args)
     P.fuse_dq0 = p.d == 64 ? 1 : 0;
     HSTU_DISPATCH_TAB(attn_bwd_kernel, p.d, p.has_pos, p.has_time, p.deterministic,
@@ -1986,6 +2027,7 @@ hipError_t launch_attn_bwd_bf16(const AttnArgs &a, const void *dO, void *dq, voi
     outputs(P);
     P.dpos_part = a.L.dpos_part ? (void *)(ws + a.L.dpos_part) : nullptr;
     P.dtime_part = a.L.dtime_part ? (void *)(ws + a.L.dtime_part) : nullptr;
+    P.all_heads = all_heads(p, Pass::DKV) ? 1 : 0;
     HSTU_DISPATCH_TAB(attn_bwd_dkv_kernel, p.d, p.has_pos, p.has_time, p.deterministic,
                       hipLaunchKernelGGL(kfn, dim3(a.L.bwd_grid_dkv), dim3(THREADS),
                                          k_dyn_bytes(p), s, P));
@@ -1996,6 +2038,7 @@ hipError_t launch_attn_bwd_bf16(const AttnArgs &a, const void *dO, void *dq, voi
   KParams P = make_params(a, (int32_t *)(ws + a.L.ctrl) + CTRL_POP_DQ,
                           (const WorkEntry *)(ws + a.L.list_q));
   outputs(P);
+  P.all_heads = all_heads(p, Pass::DQ) ? 1 : 0;
   HSTU_DISPATCH(attn_bwd_dq_kernel, p.d, p.has_pos, p.has_time,
                 hipLaunchKernelGGL(kfn, dim3(a.L.bwd_grid_dq), dim3(THREADS), q_dyn_bytes(p),
                                    s, P));

@@ -104,10 +104,11 @@ struct TimeRun {
 // log2 of the counters per bucket of an item's d_time histogram: lanes are
 // spread over them, because neighbouring keys meet in the same bucket and a
 // wave's LDS atomics on one address are served one by one (44 clocks for four
-// lanes, 8 for none).  Up to eight, in at most 4 KB.
-inline int hist_copies_log2(int nb) {
+// lanes, 8 for none).  Up to eight, in at most `bytes`.
+constexpr int64_t HIST_BYTES = 4096;
+inline int hist_copies_log2(int nb, int64_t bytes = HIST_BYTES) {
   int cs = 3;
-  while (cs > 0 && ((int64_t)nb << cs) * 8 > 4096) --cs;
+  while (cs > 0 && ((int64_t)nb << cs) * 8 > bytes) --cs;
   return cs;
 }
 

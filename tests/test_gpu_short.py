@@ -55,6 +55,21 @@ def test_edges(d, pos, time, filler):
     against_oracle(w, gpu(w))
 
 
+@pytest.mark.parametrize("det", [False, True])
+@pytest.mark.parametrize("H,nb", [(1, 256), (1, 512), (2, 128), (2, 129), (4, 64), (4, 128)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_tile_time_histograms(d, H, nb, det):
+    """The tile kernels' d_time histogram on both sides of its lines: all heads'
+    to the work-group's end or the item's head's, one to eight counters.
+    (The batch is filled past the short kernels with 40-token sequences: with
+    one head the LayerNorm makes a one-token sequence's dO orthogonal to its o,
+    a multiple of v, so its dS = <dO, v> is a cancellation; 700 of them sum |dS|
+    to 20 times the largest table entry, and rounding o and dO to bf16 alone
+    moves the diagonal's sum by 1% of it at d=128, half the tolerance.)"""
+    w = inputs.make_workload(LENGTHS + [40] * 300, H=H, d=d, N=200, num_buckets=nb, seed=850 + d)
+    against_oracle(w, gpu(w, det=det))
+
+
 @pytest.mark.parametrize("d,N,nb", [(64, 200, 32), (128, 200, 2048), (64, 3, 1)])
 def test_scale_deterministic_far(d, N, nb):
     """A score scale, fixed-point tables that repeat bit for bit, bucket
