@@ -38,6 +38,21 @@ __device__ __forceinline__ float silu2_over_n(float xs, float nl) {
   return xs * __builtin_amdgcn_rcpf(__builtin_fmaf(nl, t, nl));
 }
 
+// The forward's score of a pair in that domain, s alpha log2(e) + time bias'.
+// Rounded once at d = 64 with a position bias and twice elsewhere, by name: the
+// compiler fuses the product into the sum in one instantiation and not in the
+// next, and a sequence's bits must not depend on which kernel its batch took.
+template <int D, bool POS>
+__device__ __forceinline__ float time_score(float s, float al2e, float tb) {
+  if constexpr (D == 64 && POS) {
+    return __builtin_fmaf(s, al2e, tb);
+  } else {
+#pragma clang fp contract(off)
+    const float x = s * al2e;
+    return x + tb;
+  }
+}
+
 // Operand holding, for lane l, column ncol + (l & 31) of rows krow .. krow+3
 // and krow+8 .. krow+11 of a row-major LDS tile (krow already includes this
 // lane's 4*(l/32)), via two LDS transpose loads.  Within a 16-lane group,

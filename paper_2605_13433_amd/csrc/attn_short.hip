@@ -5,14 +5,25 @@
 // two barriers or one a step, so a call is as long as its longest item's
 // chain of steps, and a short item is mostly its start and its end.  Here an
 // item is 32 rows of one head and its four waves take every fourth 32-row
-// tile of the other side, each on its own:
+// tile of the other side:
 //
-//   * no barrier in the loop.  A wave loads its tile's rows from memory
-//     straight into the layout of the score products (lane: one row, 16 bytes
-//     at a time) and keeps the copy that the accumulating products read
-//     transposed in its own part of the LDS;
-//   * the chain is a quarter as long in tiles of half the rows;
-//   * the waves' partial sums are added through LDS in a fixed order.
+//   * a wave loads its tile's rows from memory straight into the layout of the
+//     score products (lane: one row, 16 bytes at a time), on its own;
+//   * the chain is a quarter as long in tiles of half the rows.
+//
+// Forward: a step's four tiles and their packed scores meet in the LDS, and the
+// accumulating products are dealt out by what they add to -- each wave has the
+// even or the odd tiles (the halves of the tile kernels' 64 rows) and half of
+// the dims, and takes its tiles in order.  So every sum is added up in the tile
+// kernels' order and a sequence has the same bits whichever kernel its batch
+// takes.  Two barriers a step, one after the other with only the stores of the
+// tile and the packs between them: summed by each wave for itself and added at
+// the end, one sequence of 502 / 812 / 2 heads of 8022 tokens took 11.8 / 15.2 /
+// 103 us and takes 11.7 / 15.4 / 110 (d = 128, 502: 17.6 and 16.2); with two
+// buffers and one barrier 11.2 / 14.9 / 107 and 16.3, but 56 KB, where three
+// work-groups have 53 each.
+// Backward: each wave sums its own tiles, without a barrier in the loop, and
+// the waves' partial sums are added through LDS in a fixed order.
 //
 // Per score the work is that of the tile kernels (same operands, same
 // roundings, the base-2 domain), and every 32 rows stream the other side
@@ -100,6 +111,10 @@ __device__ __forceinline__ f32x16 score(const Rows<D> &x, const Rows<D> &y, f32x
 #pragma unroll
   for (int ks = 0; ks < D / 16; ++ks) s = mfma32(as_bf16x8(x.r[ks]), as_bf16x8(y.r[ks]), s);
   return s;
+}
+
+__device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
+  return make_uint4(pack2(f[0], f[1]), pack2(f[2], f[3]), pack2(f[4], f[5]), pack2(f[6], f[7]));
 }
 
 // acc[db] += X^T P for the 16 rows of X (in LDS) that half hh of the scores
@@ -228,6 +243,15 @@ __device__ __forceinline__ void stage_table(const SParams &P, ShortTime &t, int 
   }
 }
 
+// The table's value for a gap outside the float-exponent index, scaled as
+// stage_table scales it (rounded by itself: a product fused into the sum would
+// differ from a staged one).
+__device__ __forceinline__ float far_time(const SParams &P, int h, int64_t gap, float scale) {
+#pragma clang fp contract(off)
+  const float v = scale * P.time_w[(int64_t)h * P.nb + time_bucket(gap, P.nb)];
+  return v;
+}
+
 // Timestamp of row `row` of the sequence (its last row's past the end).
 __device__ __forceinline__ int64_t ts_of(const SParams &P, const WorkEntry &e, int row) {
   return P.ts[e.start + (row < e.len ? row : e.len - 1)];
@@ -255,11 +279,82 @@ struct TimeAxis {
   }
 };
 
+// Packed scores of a step's four tiles, as the accumulating products take
+// them: [tile][16-row half][lane].
+typedef uint4 ShortPacks[S_WAVES][2][64];
+
+// acc += X^T P over one streamed tile (its rows in LDS, its packed scores) for
+// the NB 32-dim blocks from `db0` on.
+template <int D, int NB>
+__device__ __forceinline__ void accumulate_from(const u16 *lds, const uint4 (&p)[2][64], int db0,
+                                                int g, int lane, f32x16 (&acc)[NB]) {
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) {
+    const bf16x8 b = as_bf16x8(p[hh][lane]);
+#pragma unroll
+    for (int y = 0; y < NB; ++y)
+      acc[y] = mfma32(read_tr(lds, S_ROW<D>, 16 * hh + 4 * g, 32 * (db0 + y), lane), b, acc[y]);
+  }
+}
+
+// An item's sums on their way out: a wave's NB blocks from dim 32 db0 on to a
+// buffer of the item's rows, then (all waves, after a barrier) the rows below
+// `valid` as bf16, times `scale` and, with `hsrc`, times silu' of the bf16 at
+// the same place.  TWO: the sum of two buffers.
+template <int D, int NB>
+__device__ __forceinline__ void put_sums(float *buf, const f32x16 (&acc)[NB], int db0, int l32,
+                                         int g) {
+  float *p = buf + l32 * S_RED<D> + 32 * db0 + 4 * g;
+#pragma unroll
+  for (int y = 0; y < NB; ++y)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *(float4 *)(p + 32 * y + 8 * q) =
+          make_float4(acc[y][4 * q], acc[y][4 * q + 1], acc[y][4 * q + 2], acc[y][4 * q + 3]);
+}
+
+template <int D, bool TWO>
+__device__ __forceinline__ void emit_rows(const float *buf, int tid, u16 *out, int row_stride,
+                                          int valid, float scale, const u16 *hsrc) {
+#pragma unroll
+  for (int x = 0; x < ST * D / 8 / S_THREADS; ++x) {
+    const int ch = tid + S_THREADS * x, row = ch / (D / 8), c8 = ch % (D / 8);
+    if (row >= valid) continue;
+    float f[8];
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      float4 a = *(const float4 *)(buf + row * S_RED<D> + 8 * c8 + 4 * y);
+      if constexpr (TWO) {
+        const float4 b = *(const float4 *)(buf + (ST + row) * S_RED<D> + 8 * c8 + 4 * y);
+        a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+      }
+      f[4 * y] = scale * a.x;
+      f[4 * y + 1] = scale * a.y;
+      f[4 * y + 2] = scale * a.z;
+      f[4 * y + 3] = scale * a.w;
+    }
+    const int64_t at = (int64_t)row * row_stride + 8 * c8;
+    if (hsrc) {
+      const uint4 hv = *(const uint4 *)(hsrc + at);
+      const uint32_t hw[4] = {hv.x, hv.y, hv.z, hv.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        f[2 * e] *= dsilu_f(__uint_as_float(hw[e] << 16));
+        f[2 * e + 1] *= dsilu_f(__uint_as_float(hw[e] & 0xffff0000u));
+      }
+    }
+    *(uint4 *)(out + at) = pack8(f);
+  }
+}
+
 // ---------------------------------------------------------------- forward
 template <int D>
 struct ShortFwdSmem {
   union {
-    u16 v[S_WAVES][ST * S_ROW<D>];
+    struct {
+      u16 v[S_WAVES][ST * S_ROW<D>];
+      ShortPacks p;
+    };
     float red[2][ST * S_RED<D>];
   };
   ShortTime t;
@@ -273,10 +368,11 @@ __global__ void __launch_bounds__(S_THREADS, D == 64 ? 3 : 2) short_fwd_kernel(S
   WorkEntry e;
   int h, i0;
   if (!short_item(P, P.list_q, blockIdx.x, e, h, i0)) return;
+  constexpr int NB = D / 64;                          // 32-dim blocks of a wave's half
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = i0 + l32, last = i0 / ST;
-  u16 *vs = sm.v[w];
+  const int par = w & 1, db0 = NB * (w >> 1);         // what this wave accumulates
   const __amdgpu_buffer_rsrc_t rk = head_rows<D>(P, P.k, e, h), rv = head_rows<D>(P, P.v, e, h),
                                rp = pos_table(P, POS, h);
   // everything the start needs is asked for at once
@@ -294,61 +390,82 @@ __global__ void __launch_bounds__(S_THREADS, D == 64 ? 3 : 2) short_fwd_kernel(S
     stage_table(P, sm.t, h, tid, L2E);
     __syncthreads();
   }
-  f32x16 acc[D / 32];
-  clear<D>(acc);
+  f32x16 acc[NB];
+#pragma unroll
+  for (int y = 0; y < NB; ++y)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[y][r] = 0.0f;
   const float nl = (float)P.N * L2E;
 
-  for (int kt = w; kt <= last; kt += S_WAVES) {
-    const int j0 = ST * kt, nj = j0 + ST * S_WAVES;
-    vr.store(vs, l32, g);
-    const bool slow = TIME && ax.stage(sm.t.rel[w], tk, lane);
-    wave_lds_fence();
-    f32x16 s;
+  for (int k0 = 0; k0 <= last; k0 += S_WAVES) {
+    const int kt = k0 + w, j0 = ST * kt, nj = j0 + ST * S_WAVES;
+    const bool have = kt <= last, more = kt + S_WAVES <= last;
+    uint4 pk[2];
+    if (have) {
+      const bool slow = TIME && ax.stage(sm.t.rel[w], tk, lane);
+      if (TIME) wave_lds_fence();
+      f32x16 s;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = POS ? pw[r] * P.inv_alpha : 0.0f;
-    s = score<D>(kr, qr, s);
-    if (kt + S_WAVES <= last) {                       // the wave's next tile
-      kr.load(P, rk, nj + l32, g);
-      vr.load(P, rv, nj + l32, g);
-      if (POS) load_pos(P, rp, nj + 4 * g - i, 1, pw);
-      if (TIME) tk = ts_of(P, e, nj + l32);
-    }
+      for (int r = 0; r < 16; ++r) s[r] = POS ? pw[r] * P.inv_alpha : 0.0f;
+      s = score<D>(kr, qr, s);
+      if (more) {                                     // the wave's next tile
+        kr.load(P, rk, nj + l32, g);
+        if (POS) load_pos(P, rp, nj + 4 * g - i, 1, pw);
+        if (TIME) tk = ts_of(P, e, nj + l32);
+      }
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      float x[8], a[8];
+      for (int hh = 0; hh < 2; ++hh) {
+        float x[8], a[8];
+        if (TIME) {
+          if (!slow) {
 #pragma unroll
-      for (int c = 0; c < 8; ++c) x[c] = s[8 * hh + c] * P.al2e;
-      if (TIME) {
-        if (!slow) {
+            for (int q = 0; q < 2; ++q) {
+              const float4 t4 = *(const float4 *)(sm.t.rel[w] + 16 * hh + 8 * q + 4 * g);
+              const int r = 8 * hh + 4 * q;
+              const float *tab = sm.t.tab;
+              x[4 * q + 0] = time_score<D, POS>(s[r], P.al2e, tab[time_index(ax.own_rel - t4.x)]);
+              x[4 * q + 1] = time_score<D, POS>(s[r + 1], P.al2e, tab[time_index(ax.own_rel - t4.y)]);
+              x[4 * q + 2] = time_score<D, POS>(s[r + 2], P.al2e, tab[time_index(ax.own_rel - t4.z)]);
+              x[4 * q + 3] = time_score<D, POS>(s[r + 3], P.al2e, tab[time_index(ax.own_rel - t4.w)]);
+            }
+          } else {
 #pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const float4 t4 = *(const float4 *)(sm.t.rel[w] + 16 * hh + 8 * q + 4 * g);
-            x[4 * q + 0] += sm.t.tab[time_index(ax.own_rel - t4.x)];
-            x[4 * q + 1] += sm.t.tab[time_index(ax.own_rel - t4.y)];
-            x[4 * q + 2] += sm.t.tab[time_index(ax.own_rel - t4.z)];
-            x[4 * q + 3] += sm.t.tab[time_index(ax.own_rel - t4.w)];
+            for (int c = 0; c < 8; ++c)
+              x[c] = time_score<D, POS>(
+                  s[8 * hh + c], P.al2e,
+                  far_time(P, h, ax.own - ts_of(P, e, j0 + c_row(8 * hh + c, g)), L2E));
           }
         } else {
 #pragma unroll
-          for (int c = 0; c < 8; ++c)
-            x[c] += L2E * P.time_w[(int64_t)h * P.nb +
-                                   time_bucket(ax.own - ts_of(P, e, j0 + c_row(8 * hh + c, g)),
-                                               P.nb)];
+          for (int c = 0; c < 8; ++c) x[c] = s[8 * hh + c] * P.al2e;
         }
-      }
 #pragma unroll
-      for (int c = 0; c < 8; ++c) a[c] = silu2_over_n(x[c], nl);
-      if (kt == last) {
+        for (int c = 0; c < 8; ++c) a[c] = silu2_over_n(x[c], nl);
+        if (kt == last) {
 #pragma unroll
-        for (int c = 0; c < 8; ++c)
-          if (j0 + c_row(8 * hh + c, g) > i) a[c] = 0.0f;
+          for (int c = 0; c < 8; ++c)
+            if (j0 + c_row(8 * hh + c, g) > i) a[c] = 0.0f;
+        }
+        pk[hh] = pack8(a);
       }
-      accumulate<D>(vs, a, hh, g, lane, acc);
     }
-    wave_lds_fence();
+    if (k0 > 0) lds_barrier();                        // the step before is read
+    if (have) {
+      vr.store(sm.v[w], l32, g);
+      sm.p[w][0][lane] = pk[0];
+      sm.p[w][1][lane] = pk[1];
+      if (more) vr.load(P, rv, nj + l32, g);
+    }
+    lds_barrier();
+#pragma unroll
+    for (int x = par; x < S_WAVES; x += 2)
+      if (k0 + x <= last) accumulate_from<D>(sm.v[x], sm.p[x], db0, g, lane, acc);
   }
-  short_store<D>(&sm.red[0][0], acc, tid, P.o + ((e.start + i0) * P.H + h) * D, P.H * D,
-                 e.len - i0, 1.0f, nullptr);
+  lds_barrier();
+  put_sums<D>(sm.red[par], acc, db0, l32, g);
+  lds_barrier();
+  emit_rows<D, true>(sm.red[0], tid, P.o + ((e.start + i0) * P.H + h) * D, P.H * D, e.len - i0,
+                     1.0f, nullptr);
 }
 
 // --------------------------------------------------------------- backward
