@@ -328,7 +328,9 @@ int attn_bwd_call(const void *q, const void *k, const void *v, const void *u,
     if (e != hipSuccess) return hip_fail(e, "schedule launch");
   }
   if (p.dtype == HSTU_BF16) {
-    if (bwd_short(p, dev)) {
+    if (p.T == 0) {
+      // no items (and, with at most one sequence, no grid); the tables follow
+    } else if (bwd_short(p, dev)) {
       prof::Scope ps("attn_bwd_short", s);
       e = launch_attn_bwd_short(a, ws + L.dO, io->dq, io->dk, io->dv, go, s);
     } else {
