@@ -53,6 +53,16 @@ __device__ __forceinline__ float time_score(float s, float al2e, float tb) {
   }
 }
 
+// Entry `idx` of a position table that is a buffer source: 0 outside the table,
+// one dword by itself.  The index is opaque because the compiler merges loads of
+// neighbouring entries, and a wide load whose first word lies before the table
+// reads 0 in all of them: the items whose streamed rows are queries walk the
+// table downwards, past its beginning in the last rows of a sequence of max_len.
+__device__ __forceinline__ float pos_entry(__amdgpu_buffer_rsrc_t rs, int idx) {
+  asm("" : "+v"(idx));
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, 4 * idx, 0, 0));
+}
+
 // Operand holding, for lane l, column ncol + (l & 31) of rows krow .. krow+3
 // and krow+8 .. krow+11 of a row-major LDS tile (krow already includes this
 // lane's 4*(l/32)), via two LDS transpose loads.  Within a 16-lane group,

@@ -264,8 +264,7 @@ __device__ __forceinline__ void add_bias(const F32Params &P, const F32Bias &b, f
     float pw[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r)
-      pw[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-          b.pos, 4 * (off + dir * c_row(r, g) + P.N - 1), 0, 0));
+      pw[r] = pos_entry(b.pos, off + dir * c_row(r, g) + P.N - 1);
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[r] = __builtin_fmaf(P.alpha, s[r], pw[r]);
   } else {

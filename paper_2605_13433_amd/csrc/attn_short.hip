@@ -214,15 +214,18 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t pos_table(const SParams &P, bo
                    on ? 4u * (uint32_t)span : 0u);
 }
 
-// Position biases of this lane's 16 pairs, offset j - i = off + dir c_row(r, 0).
-// (One dword each: a wider load that begins before the table reads 0 in all
-// its words.)
+// Position biases of this lane's 16 pairs, offset j - i = off + DIR c_row(r, 0).
+// Up the table the compiler may merge four entries into one load: existing rows
+// begin inside it.
+template <int DIR>
 __device__ __forceinline__ void load_pos(const SParams &P, __amdgpu_buffer_rsrc_t rs, int off,
-                                         int dir, float (&p)[16]) {
+                                         float (&p)[16]) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r)
-    p[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-        rs, 4 * (off + dir * c_row(r, 0) + P.N - 1), 0, 0));
+  for (int r = 0; r < 16; ++r) {
+    const int idx = off + DIR * c_row(r, 0) + P.N - 1;
+    p[r] = DIR > 0 ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, 4 * idx, 0, 0))
+                   : pos_entry(rs, idx);
+  }
 }
 
 // Time side of an item: the head's table by float-exponent index in LDS
@@ -381,7 +384,7 @@ __global__ void __launch_bounds__(S_THREADS, D == 64 ? 3 : 2) short_fwd_kernel(S
   qr.load(P, head_rows<D>(P, P.q, e, h), i, g);
   vr.load(P, rv, ST * w + l32, g);
   float pw[16];
-  if (POS) load_pos(P, rp, ST * w + 4 * g - i, 1, pw);
+  if (POS) load_pos<1>(P, rp, ST * w + 4 * g - i, pw);
   TimeAxis ax{};
   int64_t tk = 0;
   if (TIME) {
@@ -410,7 +413,7 @@ __global__ void __launch_bounds__(S_THREADS, D == 64 ? 3 : 2) short_fwd_kernel(S
       s = score<D>(kr, qr, s);
       if (more) {                                     // the wave's next tile
         kr.load(P, rk, nj + l32, g);
-        if (POS) load_pos(P, rp, nj + 4 * g - i, 1, pw);
+        if (POS) load_pos<1>(P, rp, nj + 4 * g - i, pw);
         if (TIME) tk = ts_of(P, e, nj + l32);
       }
 #pragma unroll
@@ -497,7 +500,7 @@ __device__ __forceinline__ void short_dq(const SParams &P, ShortBwdSmem<D, DET> 
   vr.load(P, rv, ST * w + l32, g);
   dr.load(P, head_rows<D>(P, P.dO, e, h), i, g);
   float pw[16];
-  if (POS) load_pos(P, rp, ST * w + 4 * g - i, 1, pw);
+  if (POS) load_pos<1>(P, rp, ST * w + 4 * g - i, pw);
   TimeAxis ax{};
   int64_t tk = 0;
   if (TIME) {
@@ -522,7 +525,7 @@ __device__ __forceinline__ void short_dq(const SParams &P, ShortBwdSmem<D, DET> 
     if (kt + S_WAVES <= last) {
       kr.load(P, rk, nj + l32, g);
       vr.load(P, rv, nj + l32, g);
-      if (POS) load_pos(P, rp, nj + 4 * g - i, 1, pw);
+      if (POS) load_pos<1>(P, rp, nj + 4 * g - i, pw);
       if (TIME) tk = ts_of(P, e, nj + l32);
     }
 #pragma unroll
@@ -591,7 +594,7 @@ __device__ __forceinline__ void short_dkv(const SParams &P, ShortBwdSmem<D, DET>
   dr.load(P, ro, j0 + ST * w + l32, g);
   vr.load(P, head_rows<D>(P, P.v, e, h), j, g);
   float pw[16];
-  if (POS) load_pos(P, rp, j - (j0 + ST * w + 4 * g), -1, pw);
+  if (POS) load_pos<-1>(P, rp, j - (j0 + ST * w + 4 * g), pw);
   TimeAxis ax{};
   int64_t tq = 0;
   if (TIME) {
@@ -628,7 +631,7 @@ __device__ __forceinline__ void short_dkv(const SParams &P, ShortBwdSmem<D, DET>
     if (qt + S_WAVES < tiles) {
       qr.load(P, rq, ni + l32, g);
       dr.load(P, ro, ni + l32, g);
-      if (POS) load_pos(P, rp, j - (ni + 4 * g), -1, pw);
+      if (POS) load_pos<-1>(P, rp, j - (ni + 4 * g), pw);
       if (TIME) tq = ts_of(P, e, ni + l32);
     }
     float carry = 0.0f;       // d_pos: a quad's row-head sums for the next quad
