@@ -823,28 +823,27 @@ attn_fwd_kernel(KParams P) {
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
         float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = scaled_score(s[8 * hh + e], al2e);
         if (TIME) {
           if (!slow) {
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
               const float4 t4 = *(const float4 *)(sm.ts32[pb] + kb + 8 * (2 * hh + q));
               const int r = 8 * hh + 4 * q;
-              x[4 * q + 0] = time_score<D, POS>(s[r], al2e, ktab[time_index(ts_i32 - t4.x)]);
-              x[4 * q + 1] = time_score<D, POS>(s[r + 1], al2e, ktab[time_index(ts_i32 - t4.y)]);
-              x[4 * q + 2] = time_score<D, POS>(s[r + 2], al2e, ktab[time_index(ts_i32 - t4.z)]);
-              x[4 * q + 3] = time_score<D, POS>(s[r + 3], al2e, ktab[time_index(ts_i32 - t4.w)]);
+              x[4 * q + 0] = time_score<D, POS>(s[r], x[4 * q + 0], al2e, ktab[time_index(ts_i32 - t4.x)]);
+              x[4 * q + 1] = time_score<D, POS>(s[r + 1], x[4 * q + 1], al2e, ktab[time_index(ts_i32 - t4.y)]);
+              x[4 * q + 2] = time_score<D, POS>(s[r + 2], x[4 * q + 2], al2e, ktab[time_index(ts_i32 - t4.z)]);
+              x[4 * q + 3] = time_score<D, POS>(s[r + 3], x[4 * q + 3], al2e, ktab[time_index(ts_i32 - t4.w)]);
             }
           } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e)
               x[e] = time_score<D, POS>(
-                  s[8 * hh + e], al2e,
+                  s[8 * hh + e], x[e], al2e,
                   ktab[KTAB + time_bucket(ts_i_item - sm.ts64[pb][kb + c_row(8 * hh + e, 0)],
                                           P.nb)]);
           }
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) x[e] = s[8 * hh + e] * al2e;
         }
         float av[8];
 #pragma unroll

@@ -39,18 +39,19 @@ __device__ __forceinline__ float silu2_over_n(float xs, float nl) {
 }
 
 // The forward's score of a pair in that domain, s alpha log2(e) + time bias'.
-// Rounded once at d = 64 with a position bias and twice elsewhere, by name: the
-// compiler fuses the product into the sum in one instantiation and not in the
-// next, and a sequence's bits must not depend on which kernel its batch took.
-template <int D, bool POS>
-__device__ __forceinline__ float time_score(float s, float al2e, float tb) {
-  if constexpr (D == 64 && POS) {
-    return __builtin_fmaf(s, al2e, tb);
-  } else {
+// Rounded once (`xs` not used) at d = 64 with a position bias and twice
+// elsewhere (xs = scaled_score(s, al2e)), by name: the compiler fuses the product
+// into the sum in one instantiation and not in the next, and a sequence's bits
+// must not depend on which kernel its batch took.
+template <int D, bool POS> constexpr bool TIME_FUSED = D == 64 && POS;
+__device__ __forceinline__ float scaled_score(float s, float al2e) {
 #pragma clang fp contract(off)
-    const float x = s * al2e;
-    return x + tb;
-  }
+  const float x = s * al2e;
+  return x;
+}
+template <int D, bool POS>
+__device__ __forceinline__ float time_score(float s, float xs, float al2e, float tb) {
+  return TIME_FUSED<D, POS> ? __builtin_fmaf(s, al2e, tb) : xs + tb;
 }
 
 // Entry `idx` of a position table that is a buffer source: 0 outside the table,

@@ -419,6 +419,8 @@ __global__ void __launch_bounds__(S_THREADS, D == 64 ? 3 : 2) short_fwd_kernel(S
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
         float x[8], a[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) x[c] = scaled_score(s[8 * hh + c], P.al2e);
         if (TIME) {
           if (!slow) {
 #pragma unroll
@@ -426,21 +428,18 @@ __global__ void __launch_bounds__(S_THREADS, D == 64 ? 3 : 2) short_fwd_kernel(S
               const float4 t4 = *(const float4 *)(sm.t.rel[w] + 16 * hh + 8 * q + 4 * g);
               const int r = 8 * hh + 4 * q;
               const float *tab = sm.t.tab;
-              x[4 * q + 0] = time_score<D, POS>(s[r], P.al2e, tab[time_index(ax.own_rel - t4.x)]);
-              x[4 * q + 1] = time_score<D, POS>(s[r + 1], P.al2e, tab[time_index(ax.own_rel - t4.y)]);
-              x[4 * q + 2] = time_score<D, POS>(s[r + 2], P.al2e, tab[time_index(ax.own_rel - t4.z)]);
-              x[4 * q + 3] = time_score<D, POS>(s[r + 3], P.al2e, tab[time_index(ax.own_rel - t4.w)]);
+              x[4 * q + 0] = time_score<D, POS>(s[r], x[4 * q + 0], P.al2e, tab[time_index(ax.own_rel - t4.x)]);
+              x[4 * q + 1] = time_score<D, POS>(s[r + 1], x[4 * q + 1], P.al2e, tab[time_index(ax.own_rel - t4.y)]);
+              x[4 * q + 2] = time_score<D, POS>(s[r + 2], x[4 * q + 2], P.al2e, tab[time_index(ax.own_rel - t4.z)]);
+              x[4 * q + 3] = time_score<D, POS>(s[r + 3], x[4 * q + 3], P.al2e, tab[time_index(ax.own_rel - t4.w)]);
             }
           } else {
 #pragma unroll
             for (int c = 0; c < 8; ++c)
               x[c] = time_score<D, POS>(
-                  s[8 * hh + c], P.al2e,
+                  s[8 * hh + c], x[c], P.al2e,
                   far_time(P, h, ax.own - ts_of(P, e, j0 + c_row(8 * hh + c, g)), L2E));
           }
-        } else {
-#pragma unroll
-          for (int c = 0; c < 8; ++c) x[c] = s[8 * hh + c] * P.al2e;
         }
 #pragma unroll
         for (int c = 0; c < 8; ++c) a[c] = silu2_over_n(x[c], nl);
