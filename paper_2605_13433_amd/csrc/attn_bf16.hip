@@ -1143,16 +1143,14 @@ __device__ __forceinline__ void dq_item(const KParams &P, StreamSmem<D> &sm, flo
               x[e] += ktab[KTAB + time_bucket(ts_i - sm.ts64[kb + c_row(8 * hh + e, 0)], P.nb)];
           }
         }
-        // the score is alpha x: sigma(alpha x), silu'(alpha x) =
-        // sigma (1 + x (alpha - alpha sigma))
+        // the score is alpha x: sigma(alpha x)
 #pragma unroll
         for (int e = 0; e < 8; ++e) sg[e] = __builtin_amdgcn_exp2f(x[e] * P.neg_al2e);
 #pragma unroll
         for (int e = 0; e < 8; ++e) sg[e] = __builtin_amdgcn_rcpf(1.0f + sg[e]);
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-          dsv[e] = (sg[e] * da[8 * hh + e]) *
-                   __builtin_fmaf(x[e], __builtin_fmaf(-P.alpha, sg[e], P.alpha), 1.0f);
+          dsv[e] = dq_ds(sg[e], da[8 * hh + e], x[e], P.alpha);
         if (kt == qt) {
 #pragma unroll
           for (int e = 0; e < 8; ++e)
@@ -1453,13 +1451,9 @@ __device__ __forceinline__ void dkv_item(const KParams &P, DkvSmem<D, POS, DET> 
         }
       }
 
-      // a = silu(x)/N, dS = dA silu'(x)/N = dA (sg + a (1 - sg))/N with
-      // a = x sg, the table gradients, then dV += A^T dO and dK += dS^T Q,
-      // one 16-query half at a time (half the temporaries live at once).
-      // Both are carried multiplied by log2e (A' = u sg with u = x log2e,
-      // dS' = dA (sg log2e + A' (1 - sg))): one multiply per element fewer
-      // than natural units; the stores divide it out, and the table
-      // partials keep it until the finalize pass.
+      // A and dS times log2e (dkv_ds), the table gradients, then dV += A^T dO and
+      // dK += dS^T Q, one 16-query half at a time (half the temporaries live at
+      // once).
       // Query rows past the sequence have dO = 0, hence dA = 0 and dS = 0,
       // and contribute a * 0 to dV: only the diagonal tile needs a mask (the
       // causal one).
@@ -1502,7 +1496,7 @@ __device__ __forceinline__ void dkv_item(const KParams &P, DkvSmem<D, POS, DET> 
         for (int e = 0; e < 8; ++e) {
           const float a1 = u[e] * sg[e];
           av[e] = a1;
-          dsv[e] = da[8 * hh + e] * __builtin_fmaf(-a1, sg[e], __builtin_fmaf(sg[e], L2E, a1));
+          dsv[e] = dkv_ds(a1, sg[e], da[8 * hh + e]);
         }
         if (qt == kt) {
           // a real branch: selected without it, the mask's compares and

@@ -80,6 +80,21 @@ __device__ __forceinline__ bf16x8 read_tr(const u16 *lds, int stride, int krow,
   return __builtin_bit_cast(bf16x8, x);
 }
 
+// The backward's dS of a pair from sg = sigma(score) and da = <dO, v>, in natural
+// units for dQ.  The score is alpha x (biases staged divided by alpha):
+// silu'(alpha x) = sigma (1 + x (alpha - alpha sigma)).
+__device__ __forceinline__ float dq_ds(float sg, float da, float x, float alpha) {
+  return (sg * da) * __builtin_fmaf(x, __builtin_fmaf(-alpha, sg, alpha), 1.0f);
+}
+
+// As dq_ds for dK/dV, which carry a = silu and dS = dA silu' = dA (sg + a (1 - sg))
+// multiplied by log2e (A' = u sg with u = score log2e, dS' = dA (sg log2e +
+// A' (1 - sg))): one multiply per element fewer than natural units; the stores
+// divide it out, and the table partials keep it until the finalize pass.
+__device__ __forceinline__ float dkv_ds(float a, float sg, float da) {
+  return da * __builtin_fmaf(-a, sg, __builtin_fmaf(sg, L2E, a));
+}
+
 // Table-gradient accumulation types: LDS sums in double and global partials
 // in float (d_pos: one per sequence and diagonal) or double (d_time: one per
 // item), or (deterministic mode) all as 64-bit fixed point, whose integer

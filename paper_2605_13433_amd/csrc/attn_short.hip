@@ -58,7 +58,8 @@ struct SParams {
   int32_t out_stride;                        // row stride of the gradients (elements)
   void *dpos_part, *dtime_part;              // see TabAcc
   int64_t T;
-  int32_t B, H, N, nb, direct, copies;
+  int32_t B, H, N, nb, direct;
+  int32_t time_cs;                           // log2 of the d_time counters per bucket
   float alpha, inv_alpha, neg_al2e, al2e, dqk_scale, dk_scale_l2, dv_scale_l2;
 };
 
@@ -550,12 +551,10 @@ __device__ __forceinline__ void short_dq(const SParams &P, ShortBwdSmem<D, DET> 
                              time_bucket(ax.own - ts_of(P, e, j0 + c_row(8 * hh + c, g)), P.nb)];
         }
       }
-      // the score is alpha x: silu'(alpha x) = sigma (1 + x (alpha - alpha sigma))
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
         const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x[c] * P.neg_al2e));
-        ds[c] = (sg * da[8 * hh + c]) *
-                __builtin_fmaf(x[c], __builtin_fmaf(-P.alpha, sg, P.alpha), 1.0f);
+        ds[c] = dq_ds(sg, da[8 * hh + c], x[c], P.alpha);
       }
       if (kt == last) {
 #pragma unroll
@@ -571,9 +570,7 @@ __device__ __forceinline__ void short_dq(const SParams &P, ShortBwdSmem<D, DET> 
                  P.h_dq ? P.h_dq + at : nullptr);
 }
 
-// `hist`: the item's d_time sums, [nb][copies] (lanes spread over the copies:
-// neighbouring keys meet in the same bucket, and atomics of a wave on one
-// address are served one by one).
+// `hist`: the item's d_time sums, [nb][2^time_cs].
 template <int D, bool POS, bool TIME, bool DET>
 __device__ __forceinline__ void short_dkv(const SParams &P, ShortBwdSmem<D, DET> &sm,
                                           typename TabAcc<DET>::L *hist, int item) {
@@ -599,7 +596,7 @@ __device__ __forceinline__ void short_dkv(const SParams &P, ShortBwdSmem<D, DET>
   if (TIME) {
     tq = ts_of(P, e, j0 + ST * w + l32);
     ax.set(P, e, j);
-    for (int x = tid; x < P.nb * P.copies; x += S_THREADS) hist[x] = 0;
+    for (int x = tid; x < P.nb << P.time_cs; x += S_THREADS) hist[x] = 0;
     stage_table(P, sm.t, h, tid, P.inv_alpha);
   }
   if (POS) {
@@ -607,11 +604,9 @@ __device__ __forceinline__ void short_dkv(const SParams &P, ShortBwdSmem<D, DET>
     sm.win[w][1][lane] = 0;
   }
   if (TIME) __syncthreads();
-  typename A::L *my_t = hist + (lane & (P.copies - 1));
+  typename A::L *my_t = hist + (lane & ((1 << P.time_cs) - 1));
   typename A::G *dp = POS ? (typename A::G *)P.dpos_part + e.start * P.H + h : nullptr;
-  float run = 0.0f;                           // this lane's run of time index `cur`
-  int cur = -1;
-  auto flush = [&](int bucket, float v) { atomicAdd(&my_t[bucket * P.copies], A::lds(v)); };
+  TimeRun<A> run;
   f32x16 dk[D / 32], dv[D / 32];
   clear<D>(dk);
   clear<D>(dv);
@@ -660,14 +655,13 @@ __device__ __forceinline__ void short_dkv(const SParams &P, ShortBwdSmem<D, DET>
           }
         }
       }
-      // A and dS multiplied by log2e (the stores and the finalize pass divide
-      // it out): u = x log2e, A' = u sigma, dS' = dA (sigma log2e + A' (1 - sigma))
+      // A and dS times log2e
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
         const float u = x[c] * P.al2e;
         const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-u));
         a[c] = u * sg;
-        ds[c] = da[8 * hh + c] * __builtin_fmaf(-a[c], sg, __builtin_fmaf(sg, L2E, a[c]));
+        ds[c] = dkv_ds(a[c], sg, da[8 * hh + c]);
       }
       // query rows past the sequence have dO = 0: only the diagonal tile needs
       // the causal mask (keys past the sequence lie in it alone)
@@ -677,12 +671,9 @@ __device__ __forceinline__ void short_dkv(const SParams &P, ShortBwdSmem<D, DET>
           if (i0 + c_row(8 * hh + c, g) < j) { a[c] = 0.0f; ds[c] = 0.0f; }
       }
       if constexpr (POS) {
-        // slot i - j + 31 (- the tile's offset).  A register quad holds four
-        // consecutive queries of the lane's key: it is summed along its
-        // diagonals inside the 16-lane rows first (band: lane l adds lanes
-        // l+k, k = 0..3); the six elements no band reaches (head) lie on the
-        // band diagonals of lanes 5..7 of the next quad, which adds them; the
-        // last quad flushes its heads itself.  Five atomics instead of 16.
+        // slot i - j + 31 (- the tile's offset); summed along the diagonals as in
+        // the tile kernels' dK/dV items.  (A function for both: the tile kernels
+        // up to 1% slower, scheduled otherwise.)
         typename A::L *pd = &sm.win[w][g][4 * g + ST - 1 - l32];
         const bool row_head = (lane & 15) < 3;
 #pragma unroll
@@ -702,18 +693,13 @@ __device__ __forceinline__ void short_dkv(const SParams &P, ShortBwdSmem<D, DET>
       }
       if (TIME) {
         if (!slow) {
-          if (hh == 0) cur = cur < 0 ? tk[0] : cur;
+          if (hh == 0) run.start(tk[0]);
 #pragma unroll
-          for (int c = 0; c < 8; ++c) {
-            const bool change = tk[c] != cur;
-            if (change) flush(bucket_of_index(cur, P.nb), run);
-            run = change ? ds[c] : run + ds[c];
-            cur = tk[c];
-          }
+          for (int c = 0; c < 8; ++c) run.add(my_t, P.nb, P.time_cs, tk[c], ds[c]);
         } else {
 #pragma unroll
           for (int c = 0; c < 8; ++c)
-            if (ds[c] != 0.0f) flush(tk[c], ds[c]);
+            if (ds[c] != 0.0f) atomicAdd(&my_t[tk[c] << P.time_cs], A::lds(ds[c]));
         }
       }
       accumulate<D>(os, a, hh, g, lane, dv);
@@ -730,7 +716,7 @@ __device__ __forceinline__ void short_dkv(const SParams &P, ShortBwdSmem<D, DET>
     }
     wave_lds_fence();
   }
-  if (TIME && cur >= 0) flush(bucket_of_index(cur, P.nb), run);
+  if (TIME) run.flush(my_t, P.nb, P.time_cs);
   const int64_t at = (e.start + j0) * P.out_stride + h * D;
   short_store<D>(&sm.red[0][0], dk, tid, P.dk + at, P.out_stride, e.len - j0, P.dk_scale_l2,
                  P.h_dk ? P.h_dk + at : nullptr);
@@ -741,7 +727,7 @@ __device__ __forceinline__ void short_dkv(const SParams &P, ShortBwdSmem<D, DET>
                           ((int64_t)(item % DTIME_BINS) * P.H + h) * P.nb;
     for (int x = tid; x < P.nb; x += S_THREADS) {
       typename A::L v = 0;
-      for (int c = 0; c < P.copies; ++c) v += hist[x * P.copies + c];
+      for (int c = 0; c < 1 << P.time_cs; ++c) v += hist[(x << P.time_cs) + c];
       if (v != 0) atomicAdd(&part[x], (typename A::GT)v);
     }
   }
@@ -776,7 +762,7 @@ SParams make_params(const AttnArgs &a) {
   P.N = a.p.N;
   P.nb = a.p.has_time ? a.p.nb : 0;
   P.out_stride = a.p.H * a.p.d;
-  P.copies = 1 << hist_copies_log2(P.nb);
+  P.time_cs = hist_copies_log2(P.nb);
   P.alpha = a.p.alpha;
   P.inv_alpha = 1.0f / a.p.alpha;
   P.neg_al2e = -a.p.alpha * L2E;
@@ -860,7 +846,7 @@ hipError_t launch_attn_bwd_short(const AttnArgs &a, const void *dO, void *dq, vo
                        : (p.deterministic ? pick_bwd<128, true>(p.has_pos, p.has_time)
                                           : pick_bwd<128, false>(p.has_pos, p.has_time));
   hipLaunchKernelGGL(kfn, dim3((unsigned)(4 * p.max_entries * p.H)), dim3(S_THREADS),
-                     p.has_time ? sizeof(double) * (size_t)P.nb * P.copies : 0, s, P);
+                     p.has_time ? sizeof(double) * (size_t)P.nb << P.time_cs : 0, s, P);
   return hipGetLastError();
 }
 
