@@ -11,19 +11,22 @@
 //     score products (lane: one row, 16 bytes at a time), on its own;
 //   * the chain is a quarter as long in tiles of half the rows.
 //
-// Forward: a step's four tiles and their packed scores meet in the LDS, and the
-// accumulating products are dealt out by what they add to -- each wave has the
-// even or the odd tiles (the halves of the tile kernels' 64 rows) and half of
-// the dims, and takes its tiles in order.  So every sum is added up in the tile
-// kernels' order and a sequence has the same bits whichever kernel its batch
-// takes.  Two barriers a step, one after the other with only the stores of the
-// tile and the packs between them: summed by each wave for itself and added at
-// the end, one sequence of 502 / 812 / 2 heads of 8022 tokens took 11.8 / 15.2 /
-// 103 us and takes 11.7 / 15.4 / 110 (d = 128, 502: 17.6 and 16.2); with two
-// buffers and one barrier 11.2 / 14.9 / 107 and 16.3, but 56 KB, where three
-// work-groups have 53 each.
-// Backward: each wave sums its own tiles, without a barrier in the loop, and
-// the waves' partial sums are added through LDS in a fixed order.
+// A step's four tiles and their packed scores meet in the LDS, and the
+// accumulating products are dealt out by what they add to, so that every sum is
+// added up in the tile kernels' order and a sequence has the same bits whichever
+// kernel its batch takes.  Forward, dQ, and dK/dV at d = 64: each wave has the
+// even or the odd tiles (the halves of the tile kernels' 64 rows) and half of the
+// dims; dK/dV at d = 128: one of the two and half of the dims, over every tile.
+// dQ has room for two buffers and needs one barrier a step; the others have two,
+// the forward's one after the other with only the stores between them.
+// Summed by each wave for itself and added at the end, without a barrier, the
+// forward for one sequence of 502 / 812 / 2 heads of 8022 tokens took 11.8 / 15.2 /
+// 103 us and takes 11.7 / 15.4 / 110 (d = 128, 502: 17.6 and 16.2), the backward
+// of 8 sequences of up to 100 tokens at d = 128 20.8 and 19.2, of one of 502 / 812
+// 27.4 / 37.1 and 27.7 / 38.7, of one of 2000 at d = 128 72 and 85: the waves wait
+// for the slowest one's table sums in every step.
+// Forward with two buffers and one barrier: 11.2 / 14.9 / 107, but 54 KB, which
+// leaves a compute unit two work-groups instead of three.
 //
 // Per score the work is that of the tile kernels (same operands, same
 // roundings, the base-2 domain), and every 32 rows stream the other side
@@ -116,96 +119,6 @@ __device__ __forceinline__ f32x16 score(const Rows<D> &x, const Rows<D> &y, f32x
 
 __device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
   return make_uint4(pack2(f[0], f[1]), pack2(f[2], f[3]), pack2(f[4], f[5]), pack2(f[6], f[7]));
-}
-
-// acc[db] += X^T P for the 16 rows of X (in LDS) that half hh of the scores
-// covers: register r of lane (l32, g) of acc[db] is dim 32 db + c_row(r, g) of
-// stationary row l32.
-template <int D>
-__device__ __forceinline__ void accumulate(const u16 *lds, const float (&p)[8], int hh, int g,
-                                           int lane, f32x16 (&acc)[D / 32]) {
-  uint4 pk;
-  pk.x = pack2(p[0], p[1]);
-  pk.y = pack2(p[2], p[3]);
-  pk.z = pack2(p[4], p[5]);
-  pk.w = pack2(p[6], p[7]);
-  const bf16x8 b = as_bf16x8(pk);
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-    acc[db] = mfma32(read_tr(lds, S_ROW<D>, 16 * hh + 4 * g, 32 * db, lane), b, acc[db]);
-}
-
-template <int D>
-__device__ __forceinline__ void clear(f32x16 (&acc)[D / 32]) {
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[db][r] = 0.0f;
-}
-
-// Sum of the waves' accumulators ((w0 + w2) + (w1 + w3), through two buffers)
-// and the bf16 store of the item's rows below `valid`, times `scale` and, with
-// `hsrc`, times silu' of the bf16 at the same place.
-template <int D>
-__device__ __forceinline__ void short_store(float *red, const f32x16 (&acc)[D / 32], int tid,
-                                            u16 *out, int row_stride, int valid, float scale,
-                                            const u16 *hsrc) {
-  constexpr int BUF = ST * S_RED<D>;
-  const int lane = tid & 63, l32 = lane & 31, g = lane >> 5, w = tid >> 6;
-  float *mine = red + (w & 1) * BUF + l32 * S_RED<D> + 4 * g;
-  __syncthreads();
-  if (w >= 2) {
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *(float4 *)(mine + 32 * db + 8 * q) = make_float4(acc[db][4 * q], acc[db][4 * q + 1],
-                                                          acc[db][4 * q + 2], acc[db][4 * q + 3]);
-  }
-  __syncthreads();
-  if (w < 2) {
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float4 *p = (float4 *)(mine + 32 * db + 8 * q);
-        const float4 x = *p;
-        *p = make_float4(acc[db][4 * q] + x.x, acc[db][4 * q + 1] + x.y, acc[db][4 * q + 2] + x.z,
-                         acc[db][4 * q + 3] + x.w);
-      }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int x = 0; x < ST * D / 8 / S_THREADS; ++x) {
-    const int ch = tid + S_THREADS * x, row = ch / (D / 8), c8 = ch % (D / 8);
-    if (row >= valid) continue;
-    float f[8];
-#pragma unroll
-    for (int y = 0; y < 2; ++y) {
-      const float4 a = *(const float4 *)(red + row * S_RED<D> + 8 * c8 + 4 * y);
-      const float4 b = *(const float4 *)(red + BUF + row * S_RED<D> + 8 * c8 + 4 * y);
-      f[4 * y] = scale * (a.x + b.x);
-      f[4 * y + 1] = scale * (a.y + b.y);
-      f[4 * y + 2] = scale * (a.z + b.z);
-      f[4 * y + 3] = scale * (a.w + b.w);
-    }
-    const int64_t at = (int64_t)row * row_stride + 8 * c8;
-    if (hsrc) {
-      const uint4 hv = *(const uint4 *)(hsrc + at);
-      const uint32_t hw[4] = {hv.x, hv.y, hv.z, hv.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        f[2 * e] *= dsilu_f(__uint_as_float(hw[e] << 16));
-        f[2 * e + 1] *= dsilu_f(__uint_as_float(hw[e] & 0xffff0000u));
-      }
-    }
-    uint4 pk;
-    pk.x = pack2(f[0], f[1]);
-    pk.y = pack2(f[2], f[3]);
-    pk.z = pack2(f[4], f[5]);
-    pk.w = pack2(f[6], f[7]);
-    *(uint4 *)(out + at) = pk;
-  }
 }
 
 // Position table of a head as a buffer source (entries outside it read 0).
@@ -351,6 +264,14 @@ __device__ __forceinline__ void emit_rows(const float *buf, int tid, u16 *out, i
   }
 }
 
+template <int NB>
+__device__ __forceinline__ void clear(f32x16 (&acc)[NB]) {
+#pragma unroll
+  for (int y = 0; y < NB; ++y)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[y][r] = 0.0f;
+}
+
 // ---------------------------------------------------------------- forward
 template <int D>
 struct ShortFwdSmem {
@@ -395,10 +316,7 @@ __global__ void __launch_bounds__(S_THREADS, D == 64 ? 3 : 2) short_fwd_kernel(S
     __syncthreads();
   }
   f32x16 acc[NB];
-#pragma unroll
-  for (int y = 0; y < NB; ++y)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[y][r] = 0.0f;
+  clear(acc);
   const float nl = (float)P.N * L2E;
 
   for (int k0 = 0; k0 <= last; k0 += S_WAVES) {
@@ -475,23 +393,31 @@ __global__ void __launch_bounds__(S_THREADS, D == 64 ? 3 : 2) short_fwd_kernel(S
 template <int D, bool DET>
 struct ShortBwdSmem {
   union {
-    u16 x[S_WAVES][2][ST * S_ROW<D>];        // dQ: K; dK/dV: Q, dO
-    float red[2][ST * S_RED<D>];
+    struct {
+      u16 x[S_WAVES][2][ST * S_ROW<D>];      // dQ: K, by the step's parity; dK/dV: Q, dO
+      ShortPacks p[2];                       // dQ: by the step's parity; dK/dV: A, dS
+    };
+    float red[D == 64 ? 4 : 2][ST * S_RED<D>];
   };
   ShortTime t;
   // diagonal sums of each wave's tile, one copy per lane group
   typename TabAcc<DET>::L win[S_WAVES][2][2 * ST];
 };
 
+// At d = 64 the tile kernels' dK/dV items compute dQ of a sequence's first 64
+// rows, out of their base-2 dS and in one chain over the keys; so do the items of
+// those rows here.
 template <int D, bool POS, bool TIME, bool DET>
 __device__ __forceinline__ void short_dq(const SParams &P, ShortBwdSmem<D, DET> &sm, int item) {
   WorkEntry e;
   int h, i0;
   if (!short_item(P, P.list_q, item, e, h, i0)) return;
+  constexpr int NB = D / 64;
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = i0 + l32, last = i0 / ST;
-  u16 *ks = sm.x[w][0];
+  const int par = w & 1, db0 = NB * (w >> 1);
+  const bool first64 = D == 64 && e.tile == 0;
   const __amdgpu_buffer_rsrc_t rk = head_rows<D>(P, P.k, e, h), rv = head_rows<D>(P, P.v, e, h),
                                rp = pos_table(P, POS, h);
   Rows<D> kr, vr, qr, dr;
@@ -509,65 +435,77 @@ __device__ __forceinline__ void short_dq(const SParams &P, ShortBwdSmem<D, DET> 
     stage_table(P, sm.t, h, tid, P.inv_alpha);
     __syncthreads();
   }
-  f32x16 acc[D / 32];
-  clear<D>(acc);
+  f32x16 acc[NB];
+  clear(acc);
 
-  for (int kt = w; kt <= last; kt += S_WAVES) {
-    const int j0 = ST * kt, nj = j0 + ST * S_WAVES;
-    kr.store(ks, l32, g);
-    const bool slow = TIME && ax.stage(sm.t.rel[w], tk, lane);
-    wave_lds_fence();
-    f32x16 s, da;
+  for (int k0 = 0, b = 0; k0 <= last; k0 += S_WAVES, b ^= 1) {
+    const int kt = k0 + w, j0 = ST * kt, nj = j0 + ST * S_WAVES;
+    if (kt <= last) {
+      kr.store(sm.x[w][b], l32, g);
+      const bool slow = TIME && ax.stage(sm.t.rel[w], tk, lane);
+      if (TIME) wave_lds_fence();
+      f32x16 s, da;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { s[r] = POS ? pw[r] * P.inv_alpha : 0.0f; da[r] = 0.0f; }
-    s = score<D>(kr, qr, s);
-    da = score<D>(vr, dr, da);
-    if (kt + S_WAVES <= last) {
-      kr.load(P, rk, nj + l32, g);
-      vr.load(P, rv, nj + l32, g);
-      if (POS) load_pos<1>(P, rp, nj + 4 * g - i, pw);
-      if (TIME) tk = ts_of(P, e, nj + l32);
-    }
+      for (int r = 0; r < 16; ++r) { s[r] = POS ? pw[r] * P.inv_alpha : 0.0f; da[r] = 0.0f; }
+      s = score<D>(kr, qr, s);
+      da = score<D>(vr, dr, da);
+      if (kt + S_WAVES <= last) {
+        kr.load(P, rk, nj + l32, g);
+        vr.load(P, rv, nj + l32, g);
+        if (POS) load_pos<1>(P, rp, nj + 4 * g - i, pw);
+        if (TIME) tk = ts_of(P, e, nj + l32);
+      }
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      float x[8], ds[8];
+      for (int hh = 0; hh < 2; ++hh) {
+        float x[8], ds[8];
 #pragma unroll
-      for (int c = 0; c < 8; ++c) x[c] = s[8 * hh + c];
-      if (TIME) {
-        if (!slow) {
+        for (int c = 0; c < 8; ++c) x[c] = s[8 * hh + c];
+        if (TIME) {
+          if (!slow) {
 #pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const float4 t4 = *(const float4 *)(sm.t.rel[w] + 16 * hh + 8 * q + 4 * g);
-            x[4 * q + 0] += sm.t.tab[time_index(ax.own_rel - t4.x)];
-            x[4 * q + 1] += sm.t.tab[time_index(ax.own_rel - t4.y)];
-            x[4 * q + 2] += sm.t.tab[time_index(ax.own_rel - t4.z)];
-            x[4 * q + 3] += sm.t.tab[time_index(ax.own_rel - t4.w)];
+            for (int q = 0; q < 2; ++q) {
+              const float4 t4 = *(const float4 *)(sm.t.rel[w] + 16 * hh + 8 * q + 4 * g);
+              x[4 * q + 0] += sm.t.tab[time_index(ax.own_rel - t4.x)];
+              x[4 * q + 1] += sm.t.tab[time_index(ax.own_rel - t4.y)];
+              x[4 * q + 2] += sm.t.tab[time_index(ax.own_rel - t4.z)];
+              x[4 * q + 3] += sm.t.tab[time_index(ax.own_rel - t4.w)];
+            }
+          } else {
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+              x[c] += far_time(P, h, ax.own - ts_of(P, e, j0 + c_row(8 * hh + c, g)), P.inv_alpha);
           }
-        } else {
+        }
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          if (first64) {
+            const float u = x[c] * P.al2e;
+            const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-u));
+            ds[c] = dkv_ds(u * sg, sg, da[8 * hh + c]);
+          } else {
+            const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x[c] * P.neg_al2e));
+            ds[c] = dq_ds(sg, da[8 * hh + c], x[c], P.alpha);
+          }
+        }
+        if (kt == last) {
 #pragma unroll
           for (int c = 0; c < 8; ++c)
-            x[c] += P.inv_alpha *
-                    P.time_w[(int64_t)h * P.nb +
-                             time_bucket(ax.own - ts_of(P, e, j0 + c_row(8 * hh + c, g)), P.nb)];
+            if (j0 + c_row(8 * hh + c, g) > i) ds[c] = 0.0f;
         }
+        sm.p[b][w][hh][lane] = pack8(ds);
       }
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x[c] * P.neg_al2e));
-        ds[c] = dq_ds(sg, da[8 * hh + c], x[c], P.alpha);
-      }
-      if (kt == last) {
-#pragma unroll
-        for (int c = 0; c < 8; ++c)
-          if (j0 + c_row(8 * hh + c, g) > i) ds[c] = 0.0f;
-      }
-      accumulate<D>(ks, ds, hh, g, lane, acc);
     }
-    wave_lds_fence();
+    lds_barrier();
+    const int x0 = first64 ? (par ? S_WAVES : 0) : par, dx = first64 ? 1 : 2;
+    for (int x = x0; x < S_WAVES; x += dx)
+      if (k0 + x <= last) accumulate_from<D>(sm.x[x][b], sm.p[b][x], db0, g, lane, acc);
   }
+  lds_barrier();
+  put_sums<D>(sm.red[par], acc, db0, l32, g);
+  lds_barrier();
   const int64_t at = (e.start + i0) * P.out_stride + h * D;
-  short_store<D>(&sm.red[0][0], acc, tid, P.dq + at, P.out_stride, e.len - i0, P.dqk_scale,
-                 P.h_dq ? P.h_dq + at : nullptr);
+  emit_rows<D, true>(sm.red[0], tid, P.dq + at, P.out_stride, e.len - i0,
+                     first64 ? P.dk_scale_l2 : P.dqk_scale, P.h_dq ? P.h_dq + at : nullptr);
 }
 
 // `hist`: the item's d_time sums, [nb][2^time_cs].
@@ -581,6 +519,12 @@ __device__ __forceinline__ void short_dkv(const SParams &P, ShortBwdSmem<D, DET>
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = j0 + l32, first = j0 / ST, tiles = (e.len + ST - 1) / ST;
+  // What this wave accumulates, in the tile kernels' order.  d = 64: dV and dK
+  // of half the dims over the even or the odd tiles (par), which are added at
+  // the end; d = 128: one of the two (par) for half the dims over every tile.
+  constexpr bool SPLIT = D == 128;
+  constexpr int NB = D / 64;
+  const int par = w & 1, db0 = NB * (w >> 1);
   u16 *qs = sm.x[w][0], *os = sm.x[w][1];
   const __amdgpu_buffer_rsrc_t rq = head_rows<D>(P, P.q, e, h), ro = head_rows<D>(P, P.dO, e, h),
                                rp = pos_table(P, POS, h);
@@ -607,121 +551,140 @@ __device__ __forceinline__ void short_dkv(const SParams &P, ShortBwdSmem<D, DET>
   typename A::L *my_t = hist + (lane & ((1 << P.time_cs) - 1));
   typename A::G *dp = POS ? (typename A::G *)P.dpos_part + e.start * P.H + h : nullptr;
   TimeRun<A> run;
-  f32x16 dk[D / 32], dv[D / 32];
-  clear<D>(dk);
-  clear<D>(dv);
+  f32x16 dv[NB], dk[SPLIT ? 1 : NB];            // (SPLIT: dV or dK, in dv)
+  clear(dv);
+  clear(dk);
 
-  for (int qt = first + w; qt < tiles; qt += S_WAVES) {
-    const int i0 = ST * qt, ni = i0 + ST * S_WAVES;
-    qr.store(qs, l32, g);
-    dr.store(os, l32, g);
-    const bool slow = TIME && ax.stage(sm.t.rel[w], tq, lane);
-    wave_lds_fence();
-    f32x16 s, da;
+  for (int q0 = first; q0 < tiles; q0 += S_WAVES) {
+    const int qt = q0 + w, i0 = ST * qt, ni = i0 + ST * S_WAVES;
+    if (q0 > first) lds_barrier();              // the step before is read
+    if (qt < tiles) {
+      qr.store(qs, l32, g);
+      dr.store(os, l32, g);
+      const bool slow = TIME && ax.stage(sm.t.rel[w], tq, lane);
+      if (TIME) wave_lds_fence();
+      f32x16 s, da;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { s[r] = POS ? pw[r] * P.inv_alpha : 0.0f; da[r] = 0.0f; }
-    s = score<D>(qr, kr, s);
-    da = score<D>(dr, vr, da);
-    if (qt + S_WAVES < tiles) {
-      qr.load(P, rq, ni + l32, g);
-      dr.load(P, ro, ni + l32, g);
-      if (POS) load_pos<-1>(P, rp, j - (ni + 4 * g), pw);
-      if (TIME) tq = ts_of(P, e, ni + l32);
-    }
-    float carry = 0.0f;       // d_pos: a quad's row-head sums for the next quad
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      float x[8], a[8], ds[8];
-      int tk[8];
-#pragma unroll
-      for (int c = 0; c < 8; ++c) x[c] = s[8 * hh + c];
-      if (TIME) {
-        if (!slow) {
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const float4 t4 = *(const float4 *)(sm.t.rel[w] + 16 * hh + 8 * q + 4 * g);
-            tk[4 * q + 0] = time_index(t4.x - ax.own_rel);
-            tk[4 * q + 1] = time_index(t4.y - ax.own_rel);
-            tk[4 * q + 2] = time_index(t4.z - ax.own_rel);
-            tk[4 * q + 3] = time_index(t4.w - ax.own_rel);
-          }
-#pragma unroll
-          for (int c = 0; c < 8; ++c) x[c] += sm.t.tab[tk[c]];
-        } else {
-#pragma unroll
-          for (int c = 0; c < 8; ++c) {
-            tk[c] = time_bucket(ts_of(P, e, i0 + c_row(8 * hh + c, g)) - ax.own, P.nb);
-            x[c] += P.inv_alpha * P.time_w[(int64_t)h * P.nb + tk[c]];
-          }
-        }
+      for (int r = 0; r < 16; ++r) { s[r] = POS ? pw[r] * P.inv_alpha : 0.0f; da[r] = 0.0f; }
+      s = score<D>(qr, kr, s);
+      da = score<D>(dr, vr, da);
+      if (qt + S_WAVES < tiles) {
+        qr.load(P, rq, ni + l32, g);
+        dr.load(P, ro, ni + l32, g);
+        if (POS) load_pos<-1>(P, rp, j - (ni + 4 * g), pw);
+        if (TIME) tq = ts_of(P, e, ni + l32);
       }
-      // A and dS times log2e
+      float carry = 0.0f;       // d_pos: a quad's row-head sums for the next quad
 #pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const float u = x[c] * P.al2e;
-        const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-u));
-        a[c] = u * sg;
-        ds[c] = dkv_ds(a[c], sg, da[8 * hh + c]);
-      }
-      // query rows past the sequence have dO = 0: only the diagonal tile needs
-      // the causal mask (keys past the sequence lie in it alone)
-      if (qt == first) {
+      for (int hh = 0; hh < 2; ++hh) {
+        float x[8], a[8], ds[8];
+        int tk[8];
 #pragma unroll
-        for (int c = 0; c < 8; ++c)
-          if (i0 + c_row(8 * hh + c, g) < j) { a[c] = 0.0f; ds[c] = 0.0f; }
-      }
-      if constexpr (POS) {
-        // slot i - j + 31 (- the tile's offset); summed along the diagonals as in
-        // the tile kernels' dK/dV items.  (A function for both: the tile kernels
-        // up to 1% slower, scheduled otherwise.)
-        typename A::L *pd = &sm.win[w][g][4 * g + ST - 1 - l32];
-        const bool row_head = (lane & 15) < 3;
+        for (int c = 0; c < 8; ++c) x[c] = s[8 * hh + c];
+        if (TIME) {
+          if (!slow) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const float *v = ds + 4 * q;
-          const float b4 = ((v[0] + row_shl<1>(v[1])) + row_shl<2>(v[2])) + row_shl<3>(v[3]);
-          const float band = hh == 0 && q == 0 ? b4 : b4 + carry;
-          const float head = (v[3] + row_shr<1>(v[2])) + row_shr<2>(v[1]);
-          const int at = 16 * hh + 8 * q;
-          atomicAdd(pd + at, A::lds(band));
-          if (hh == 1 && q == 1) {
-            if (row_head) atomicAdd(pd + at + 3, A::lds(head));
+            for (int q = 0; q < 2; ++q) {
+              const float4 t4 = *(const float4 *)(sm.t.rel[w] + 16 * hh + 8 * q + 4 * g);
+              tk[4 * q + 0] = time_index(t4.x - ax.own_rel);
+              tk[4 * q + 1] = time_index(t4.y - ax.own_rel);
+              tk[4 * q + 2] = time_index(t4.z - ax.own_rel);
+              tk[4 * q + 3] = time_index(t4.w - ax.own_rel);
+            }
+#pragma unroll
+            for (int c = 0; c < 8; ++c) x[c] += sm.t.tab[tk[c]];
           } else {
-            carry = row_shr<5>(row_head ? head : 0.0f);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+              const int64_t gap = ts_of(P, e, i0 + c_row(8 * hh + c, g)) - ax.own;
+              tk[c] = time_bucket(gap, P.nb);
+              x[c] += far_time(P, h, gap, P.inv_alpha);
+            }
           }
         }
-      }
-      if (TIME) {
-        if (!slow) {
-          if (hh == 0) run.start(tk[0]);
+        // A and dS times log2e
 #pragma unroll
-          for (int c = 0; c < 8; ++c) run.add(my_t, P.nb, P.time_cs, tk[c], ds[c]);
-        } else {
+        for (int c = 0; c < 8; ++c) {
+          const float u = x[c] * P.al2e;
+          const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-u));
+          a[c] = u * sg;
+          ds[c] = dkv_ds(a[c], sg, da[8 * hh + c]);
+        }
+        // query rows past the sequence have dO = 0: only the diagonal tile needs
+        // the causal mask (keys past the sequence lie in it alone)
+        if (qt == first) {
 #pragma unroll
           for (int c = 0; c < 8; ++c)
-            if (ds[c] != 0.0f) atomicAdd(&my_t[tk[c] << P.time_cs], A::lds(ds[c]));
+            if (i0 + c_row(8 * hh + c, g) < j) { a[c] = 0.0f; ds[c] = 0.0f; }
         }
+        if constexpr (POS) {
+          // slot i - j + 31 (- the tile's offset); summed along the diagonals as in
+          // the tile kernels' dK/dV items.  (A function for both: the tile kernels
+          // up to 1% slower, scheduled otherwise.)
+          typename A::L *pd = &sm.win[w][g][4 * g + ST - 1 - l32];
+          const bool row_head = (lane & 15) < 3;
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const float *v = ds + 4 * q;
+            const float b4 = ((v[0] + row_shl<1>(v[1])) + row_shl<2>(v[2])) + row_shl<3>(v[3]);
+            const float band = hh == 0 && q == 0 ? b4 : b4 + carry;
+            const float head = (v[3] + row_shr<1>(v[2])) + row_shr<2>(v[1]);
+            const int at = 16 * hh + 8 * q;
+            atomicAdd(pd + at, A::lds(band));
+            if (hh == 1 && q == 1) {
+              if (row_head) atomicAdd(pd + at + 3, A::lds(head));
+            } else {
+              carry = row_shr<5>(row_head ? head : 0.0f);
+            }
+          }
+        }
+        if (TIME) {
+          if (!slow) {
+            if (hh == 0) run.start(tk[0]);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) run.add(my_t, P.nb, P.time_cs, tk[c], ds[c]);
+          } else {
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+              if (ds[c] != 0.0f) atomicAdd(&my_t[tk[c] << P.time_cs], A::lds(ds[c]));
+          }
+        }
+        sm.p[0][w][hh][lane] = pack8(a);
+        sm.p[1][w][hh][lane] = pack8(ds);
       }
-      accumulate<D>(os, a, hh, g, lane, dv);
-      accumulate<D>(qs, ds, hh, g, lane, dk);
+      if constexpr (POS) {
+        // the tile's 63 diagonals to the sequence's partials
+        wave_lds_fence();
+        const typename A::L v = sm.win[w][0][lane] + sm.win[w][1][lane];
+        sm.win[w][0][lane] = 0;
+        sm.win[w][1][lane] = 0;
+        const int m = i0 - j0 + lane - (ST - 1);
+        if (v != 0 && m >= 0 && m < e.len) atomicAdd(&dp[(int64_t)m * P.H], A::glob(v));
+      }
     }
-    if constexpr (POS) {
-      // the tile's 63 diagonals to the sequence's partials
-      wave_lds_fence();
-      const typename A::L v = sm.win[w][0][lane] + sm.win[w][1][lane];
-      sm.win[w][0][lane] = 0;
-      sm.win[w][1][lane] = 0;
-      const int m = i0 - j0 + lane - (ST - 1);
-      if (v != 0 && m >= 0 && m < e.len) atomicAdd(&dp[(int64_t)m * P.H], A::glob(v));
+    lds_barrier();
+    if constexpr (SPLIT) {
+      for (int x = 0; x < S_WAVES; ++x)
+        if (q0 + x < tiles)
+          accumulate_from<D>(sm.x[x][par ? 0 : 1], sm.p[par][x], db0, g, lane, dv);
+    } else {
+      for (int x = (par ^ q0) & 1; x < S_WAVES; x += 2)
+        if (q0 + x < tiles) {
+          accumulate_from<D>(sm.x[x][1], sm.p[0][x], db0, g, lane, dv);
+          accumulate_from<D>(sm.x[x][0], sm.p[1][x], db0, g, lane, dk);
+        }
     }
-    wave_lds_fence();
   }
   if (TIME) run.flush(my_t, P.nb, P.time_cs);
+  lds_barrier();
+  put_sums<D>(sm.red[par], dv, db0, l32, g);
+  if constexpr (!SPLIT) put_sums<D>(sm.red[2 + par], dk, db0, l32, g);
+  lds_barrier();
   const int64_t at = (e.start + j0) * P.out_stride + h * D;
-  short_store<D>(&sm.red[0][0], dk, tid, P.dk + at, P.out_stride, e.len - j0, P.dk_scale_l2,
-                 P.h_dk ? P.h_dk + at : nullptr);
-  short_store<D>(&sm.red[0][0], dv, tid, P.dv + at, P.out_stride, e.len - j0, P.dv_scale_l2,
-                 P.h_dv ? P.h_dv + at : nullptr);
+  emit_rows<D, !SPLIT>(sm.red[SPLIT ? 1 : 2], tid, P.dk + at, P.out_stride, e.len - j0,
+                       P.dk_scale_l2, P.h_dk ? P.h_dk + at : nullptr);
+  emit_rows<D, !SPLIT>(sm.red[0], tid, P.dv + at, P.out_stride, e.len - j0, P.dv_scale_l2,
+                       P.h_dv ? P.h_dv + at : nullptr);
   if (TIME) {
     typename A::GT *part = (typename A::GT *)P.dtime_part +
                           ((int64_t)(item % DTIME_BINS) * P.H + h) * P.nb;

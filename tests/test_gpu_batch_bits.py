@@ -1,8 +1,10 @@
 """A sequence's outputs do not depend on the batch around it, bit for bit: the
 same sequences in a batch small enough for the short kernels (32-row items)
 and in batches past that line, where the tile kernels' one-tile, direct and
-two-tile items take them.  Ragged lengths at the edges of the 32-row items,
-of the waves' shares and of the 64-row tiles."""
+two-tile items and both launches of the backward take them.  Ragged lengths at
+the edges of the 32-row items, of the waves' shares and of the 64-row tiles.
+(The one exception is in the tile kernels alone: at d = 64 the backward in two
+launches rounds dQ of a sequence's first 64 rows otherwise than the one in one.)"""
 import pytest
 import torch
 
@@ -28,13 +30,33 @@ def forward_is_short(w):
     return 2 * hstu.max_entries(w.B, w.N, w.T) * w.H <= (3 if w.d == 64 else 1) * cus
 
 
-def forward(w, alpha=1.0):
+def backward_is_short(w):
+    """The backward's: two work-groups an item, two on a compute unit (one at
+    d = 128)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return 4 * hstu.max_entries(w.B, w.N, w.T) * w.H <= (2 if w.d == 64 else 1) * cus
+
+
+def run(w, alpha=1.0, backward=False):
     q, k, v, u, off = (to_dev(x) for x in (w.q, w.k, w.v, w.u, w.seq_offsets))
     plan = hstu.Plan(q, off, w.N, to_dev(w.pos_w), to_dev(w.time_w), to_dev(w.timestamps),
-                     w.num_buckets, backward=False, alpha=alpha)
+                     w.num_buckets, backward=backward, alpha=alpha)
     f = plan.forward(q, k, v, u, off)
+    out = dict(o=f.o, y=f.y, mean=f.ln_mean, rstd=f.ln_rstd)
+    if backward:
+        g = plan.backward(q, k, v, u, off, to_dev(w.dy))
+        out.update(dq=g.dq, dk=g.dk, dv=g.dv, du=g.du)
     torch.cuda.synchronize()
-    return dict(o=f.o, y=f.y, mean=f.ln_mean, rstd=f.ln_rstd)
+    return out
+
+
+def same(small, large, names, **kw):
+    a, b = run(small, **kw), run(large, **kw)
+    for n in names:
+        assert torch.equal(a[n], b[n][:small.T]), n
+
+
+FORWARD, BACKWARD = ("o", "y", "mean", "rstd"), ("dq", "dk", "dv", "du")
 
 
 def batches(lengths, filler, far, **kw):
@@ -60,9 +82,7 @@ def test_forward_bits(d, pos, time, far, filler):
         small, large = batches(LENGTHS, filler, far, H=2, d=d, N=700, pos=pos, time=time,
                                seed=600 + d)
         assert forward_is_short(small) and not forward_is_short(large)
-        a, b = forward(small, alpha), forward(large, alpha)
-        for n in a:
-            assert torch.equal(a[n], b[n][:small.T]), n
+        same(small, large, FORWARD, alpha=alpha)
 
 
 @pytest.mark.parametrize("d,B", [(64, 1), (128, 1), (64, 3)])
@@ -70,6 +90,37 @@ def test_forward_bits_long(d, B):
     """Many tiles a wave, the last step ragged."""
     small, large = batches([1650, 700, 31][:B], [650] * 40, False, H=2, d=d, N=1700, seed=610 + d)
     assert forward_is_short(small) and not forward_is_short(large)
-    a, b = forward(small), forward(large)
-    for n in a:
-        assert torch.equal(a[n], b[n][:small.T]), n
+    same(small, large, FORWARD)
+
+
+def two_launches(w):
+    """Past this many items (4 for each of at most 4 work-groups a compute
+    unit) the tile kernels' backward is two launches; it is one below 4 for each
+    of one work-group."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    items = hstu.max_entries(w.B, w.N, w.T) * w.H
+    assert items >= 16 * cus or items < 4 * cus
+    return items >= 16 * cus
+
+
+@pytest.mark.parametrize("filler", [[100] * 60, [40] * 1500], ids=["one", "two"])
+@pytest.mark.parametrize("pos,time,far", [(True, True, False), (True, True, True),
+                                          (True, False, False), (False, True, False),
+                                          (False, True, True), (False, False, False)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_backward_bits(d, pos, time, far, filler):
+    say(f"batch bits backward d={d} pos={pos} time={time} far={far} filler={len(filler)}")
+    small, large = batches(LENGTHS[:-2] if d == 128 else LENGTHS, filler, far, H=2, d=d, N=700,
+                           pos=pos, time=time, seed=620 + d)
+    assert backward_is_short(small) and not backward_is_short(large)
+    assert two_launches(large) == (len(filler) == 1500)
+    names = BACKWARD[1:] if d == 64 and two_launches(large) else BACKWARD
+    for alpha in (1.0, -0.7):
+        same(small, large, names, alpha=alpha, backward=True)
+
+
+@pytest.mark.parametrize("d,L", [(64, 1650), (128, 1650), (64, 1027)])
+def test_backward_bits_long(d, L):
+    small, large = batches([L], [100] * 60, False, H=2, d=d, N=1700, seed=630 + d)
+    assert backward_is_short(small) and not backward_is_short(large)
+    same(small, large, BACKWARD, backward=True)
