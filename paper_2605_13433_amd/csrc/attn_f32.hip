@@ -252,24 +252,21 @@ struct Buckets {
   __device__ __forceinline__ int at(int r) const { return (int)((b[r >> 2] >> (8 * (r & 3))) & 255u); }
 };
 
-// s = alpha s + biases of the tile's pairs.  `off` = j - i of the pair of
-// streamed row 0 and this lane's stationary row, `dir` the change of j - i
-// per streamed row (+1 where the streamed side is keys, -1 queries); `bk`
-// receives the time buckets.  The scheduling barrier keeps the bias loads
+// s = alpha s + (position + time bias) of the tile's pairs: the biases are added
+// first, so that two that cancel leave the score its precision.  `off` = j - i
+// of the pair of streamed row 0 and this lane's stationary row, `dir` the change
+// of j - i per streamed row (+1 where the streamed side is keys, -1 queries);
+// `bk` receives the time buckets.  The scheduling barrier keeps the bias loads
 // out of the products' registers.
 __device__ __forceinline__ void add_bias(const F32Params &P, const F32Bias &b, f32x16 &s, int off,
                                          int dir, const int64_t *ts, int g, Buckets &bk) {
   __builtin_amdgcn_sched_barrier(0);
+  float w[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) w[r] = 0.0f;
   if (P.pos_w) {
-    float pw[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      pw[r] = pos_entry(b.pos, off + dir * c_row(r, g) + P.N - 1);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = __builtin_fmaf(P.alpha, s[r], pw[r]);
-  } else {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] *= P.alpha;
+    for (int r = 0; r < 16; ++r) w[r] = pos_entry(b.pos, off + dir * c_row(r, g) + P.N - 1);
   }
   if (P.time_w) {
 #pragma unroll
@@ -284,8 +281,10 @@ __device__ __forceinline__ void add_bias(const F32Params &P, const F32Bias &b, f
 #pragma unroll
     for (int r = 0; r < 16; ++r) tw[r] = b.time[bk.at(r)];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] += tw[r];
+    for (int r = 0; r < 16; ++r) w[r] += tw[r];
   }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s[r] = __builtin_fmaf(P.alpha, s[r], w[r]);
 }
 
 // Timestamps of the streamed tile in the wave's part of LDS (rows past the

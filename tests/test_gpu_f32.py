@@ -89,3 +89,17 @@ def test_nonfinite_rows_stay_causal(d):
         assert torch.equal(dk[p + 1:], base[3][p + 1:]), "dk after the row"
         assert torch.equal(dv[p + 1:], base[4][p + 1:]), "dv after the row"
         assert not np.isfinite(dv[:p + 1].cpu().numpy()).any()
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_cancelling_biases(d):
+    """Position and time biases of 1000 that cancel to about one: the score keeps
+    the precision of their sum (rounded at 1000 on the way it is off by 3e-5,
+    three times the bound)."""
+    w = inputs.make_workload([97, 1, 130, 64], H=2, d=d, N=130, dtype=torch.float32, seed=940 + d)
+    w.pos_w += 1000.0
+    w.time_w -= 1000.0
+    got = run_gpu(w)
+    ref = dict(oracle.fwd_workload(w), **oracle.bwd_workload(w))
+    for n in ("o", "y", "dq", "dk", "dv", "du", "d_pos", "d_time"):
+        check(n, got[n], ref[n], TOL[w.dtype])
