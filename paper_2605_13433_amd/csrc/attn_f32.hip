@@ -197,11 +197,12 @@ __device__ __forceinline__ void tile_accumulate(float *lds, const float (&p)[16]
 
 // Sum of the NW waves' accumulators (each through its own LDS part, in
 // wave order) and the store of the item's rows (those below `valid`) times
-// `scale`.
+// `scale`.  With `more`, on top of what an earlier call stored with scale 1
+// (every thread reads back its own elements).
 template <int D, int NW>
 __device__ __forceinline__ void sum_store(float *lds0, int part, const f32x16 (&acc)[D / 32],
                                           int tid, float *out, int row_stride, int valid,
-                                          float scale) {
+                                          float scale, bool more = false) {
   const int lane = tid & 63, l32 = lane & 31, g = lane >> 5;
   float *mine = lds0 + (tid >> 6) * part;
   __syncthreads();
@@ -216,15 +217,27 @@ __device__ __forceinline__ void sum_store(float *lds0, int part, const f32x16 (&
   for (int x = 0; x < FT * D / 4 / (64 * NW); ++x) {
     const int ch = tid + 64 * NW * x, row = ch / (D / 4), col = ch % (D / 4);
     if (row >= valid) continue;
+    float *dst = out + (int64_t)row * row_stride + 4 * col;
     float4 s = *(const float4 *)(lds0 + row * F32_ROW<D> + 4 * col);
+    if (NW == 2 && more) {
+      const float4 b = *(const float4 *)dst;
+      s.x += b.x; s.y += b.y; s.z += b.z; s.w += b.w;
+    }
 #pragma unroll
     for (int w = 1; w < NW; ++w) {
       const float4 t = *(const float4 *)(lds0 + w * part + row * F32_ROW<D> + 4 * col);
       s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
     }
-    *(float4 *)(out + (int64_t)row * row_stride + 4 * col) =
-        make_float4(scale * s.x, scale * s.y, scale * s.z, scale * s.w);
+    *(float4 *)dst = make_float4(scale * s.x, scale * s.y, scale * s.z, scale * s.w);
   }
+}
+
+template <int D>
+__device__ __forceinline__ void clear(f32x16 (&acc)[D / 32]) {
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[db][r] = 0.0f;
 }
 
 // The bias sources of one head of one item.
@@ -328,6 +341,16 @@ __device__ __forceinline__ bool item_of(const F32Params &P, const WorkEntry *lis
   return row0 < e.len;
 }
 
+// Whether an item of `tiles` streamed tiles goes into its second round after
+// this wave's tile (two waves only, see two_waves: at most four tiles, so both
+// waves meet here).  The first round's sum is then stored and the waves start
+// anew, so that every sum is the one of four waves with a tile each, added in
+// the same order: a sequence has the same bits in either form.
+template <int NW>
+__device__ __forceinline__ bool second_round(int tile, int tiles) {
+  return NW == 2 && tile < NW && tiles > NW;
+}
+
 template <int D, int NW>
 struct F32FwdSmem {
   float tile[NW][2][FT * F32_ROW<D>];     // K, V of each wave's tile
@@ -352,10 +375,8 @@ __device__ __forceinline__ void f32_fwd_item(const F32Params &P, F32FwdSmem<D, N
   load_rows<D>(P, rq, i, g, qreg);
   const F32Bias bias = bias_of(P, e, h, i);
   f32x16 acc[D / 32];
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[db][r] = 0.0f;
+  clear<D>(acc);
+  float *out = P.o + ((e.start + i0) * P.H + h) * D;
 
   const int last = i0 / FT;
   for (int kt = w; kt <= last; kt += NW) {
@@ -382,9 +403,15 @@ __device__ __forceinline__ void f32_fwd_item(const F32Params &P, F32FwdSmem<D, N
     }
     tile_accumulate<D>(vs, a, edge, ok, l32, g, acc);
     wave_lds_fence();
+    if (second_round<NW>(kt, last + 1)) {
+      sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, acc, tid, out, P.H * D, e.len - i0,
+                       1.0f);
+      clear<D>(acc);
+      __syncthreads();                  // the next tile overwrites what was read
+    }
   }
-  sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, acc, tid,
-               P.o + ((e.start + i0) * P.H + h) * D, P.H * D, e.len - i0, 1.0f);
+  sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, acc, tid, out, P.H * D, e.len - i0,
+                   1.0f, last >= NW);
 }
 
 template <int D, int NW>
@@ -440,10 +467,8 @@ __device__ __forceinline__ void f32_dq_item(const F32Params &P, F32BwdSmem<D, DE
   load_rows<D>(P, rows_of(P, P.dO, e, h, D), i, g, oreg);
   const F32Bias bias = bias_of(P, e, h, i);
   f32x16 acc[D / 32];
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[db][r] = 0.0f;
+  clear<D>(acc);
+  float *out = P.dq + ((e.start + i0) * P.H + h) * D;
 
   const int last = i0 / FT;
   for (int kt = w; kt <= last; kt += NW) {
@@ -474,9 +499,15 @@ __device__ __forceinline__ void f32_dq_item(const F32Params &P, F32BwdSmem<D, DE
     }
     tile_accumulate<D>(ks, ds, edge, ok, l32, g, acc);
     wave_lds_fence();
+    if (second_round<NW>(kt, last + 1)) {
+      sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, acc, tid, out, P.H * D, e.len - i0,
+                       1.0f);
+      clear<D>(acc);
+      __syncthreads();                  // the next tile overwrites what was read
+    }
   }
-  sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, acc, tid,
-               P.dq + ((e.start + i0) * P.H + h) * D, P.H * D, e.len - i0, P.alpha);
+  sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, acc, tid, out, P.H * D, e.len - i0,
+                   P.alpha, last >= NW);
 }
 
 template <int D, bool DET, int NW>
@@ -517,10 +548,9 @@ __device__ __forceinline__ void f32_dkv_item(const F32Params &P, F32BwdSmem<D, D
   };
   __syncthreads();
   f32x16 dk[D / 32], dv[D / 32];
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { dk[db][r] = 0.0f; dv[db][r] = 0.0f; }
+  clear<D>(dk);
+  clear<D>(dv);
+  const int64_t at = ((e.start + j0) * P.H + h) * D;
 
   for (int qt = first + w; qt < tiles; qt += NW) {
     const int i0 = FT * qt;
@@ -580,12 +610,21 @@ __device__ __forceinline__ void f32_dkv_item(const F32Params &P, F32BwdSmem<D, D
     tile_accumulate<D>(os, a, edge, ok, l32, g, dv);
     tile_accumulate<D>(qs, ds, edge, ok, l32, g, dk);
     wave_lds_fence();
+    if (second_round<NW>(qt - first, tiles - first)) {
+      sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dk, tid, P.dk + at, P.H * D,
+                       e.len - j0, 1.0f);
+      sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dv, tid, P.dv + at, P.H * D,
+                       e.len - j0, 1.0f);
+      clear<D>(dk);
+      clear<D>(dv);
+      __syncthreads();                  // the next tile overwrites what was read
+    }
   }
   if (time_g && cur >= 0) flush();
-  sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dk, tid,
-               P.dk + ((e.start + j0) * P.H + h) * D, P.H * D, e.len - j0, P.alpha);
-  sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dv, tid,
-               P.dv + ((e.start + j0) * P.H + h) * D, P.H * D, e.len - j0, 1.0f);
+  sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dk, tid, P.dk + at, P.H * D,
+                   e.len - j0, P.alpha, tiles - first > NW);
+  sum_store<D, NW>(&sm.tile[0][0][0], 2 * FT * F32_ROW<D>, dv, tid, P.dv + at, P.H * D,
+                   e.len - j0, 1.0f, tiles - first > NW);
   if (time_g && in_lds)
     for (int x = tid; x < P.nb; x += 64 * NW) {
       typename A::T v = 0;
@@ -642,11 +681,13 @@ dim3 f32_grid(const Problem &p, int per) {
 // 32-row tiles and the work-groups (`per` to a list entry and head) queue for
 // the device: the third and fourth wave of most items would have no tile, and
 // only hold their place.  Forward / backward (us), four waves and two: 300
-// sequences of up to 100 tokens, 8 heads of 64, 149 / 547 and 104 / 425; 200 of
-// up to 110, 8 heads of 128, 272 / 954 and 182 / 599; just above the line, 24 of
-// 100..128, 4 heads of 64, 16 / 54 and 16 / 49; but 4 of up to 700, 4 heads of 64,
-// 37 / 83 and 60 / 130, where the chain of tiles doubles.  Resident to a compute
-// unit with four waves: one at d = 128, three of the d = 32 forward (48 of
+// sequences of up to 100 tokens, 8 heads of 64, 141 / 518 and 102 / 438; 200 of
+// up to 110, 8 heads of 128, 257 / 900 and 182 / 672; 300 of up to 128, 4 heads of
+// 32, 51 / 190 and 48 / 135; just above the line, 48 of 100..128, 4 heads of 64,
+// 31 / 82 and 30 / 82; but 4 of 60..128, 2 heads of 64, 12 / 25 and 15 / 34, where
+// the chain of tiles doubles.  (Without second_round, whose sums spill: 96 / 414,
+// 168 / 561, 41 / 127, 28 / 74, and other bits than four waves give.)  Resident to
+// a compute unit with four waves: one at d = 128, three of the d = 32 forward (48 of
 // 100..128, 4 heads, which all fit: 20.0 with four and 21.2 with two), else two.
 bool two_waves(const Problem &p, int per) {
   int dev = 0;

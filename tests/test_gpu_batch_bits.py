@@ -124,3 +124,29 @@ def test_backward_bits_long(d, L):
     small, large = batches([L], [100] * 60, False, H=2, d=d, N=1700, seed=630 + d)
     assert backward_is_short(small) and not backward_is_short(large)
     same(small, large, BACKWARD, backward=True)
+
+
+def f32_waves(w, per):
+    """Two where sequences have at most four 32-row tiles and the work-groups
+    (`per` to a list entry and head) queue for the device, else four."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    resident = 1 if w.d == 128 else 3 if w.d == 32 and per == 2 else 2
+    queue = per * hstu.max_entries(w.B, w.N, w.T) * w.H > resident * cus
+    return 2 if w.N <= 128 and queue else 4
+
+
+@pytest.mark.parametrize("pos,time", [(True, True), (False, False)])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_f32_bits(d, pos, time):
+    """fp32: work-groups of four waves and of two."""
+    say(f"batch bits fp32 d={d} pos={pos} time={time}")
+    lengths = [1, 31, 32, 33, 0, 63, 64, 65, 95, 96, 97, 127, 128]
+    small, large = batches(lengths, [70] * 300, False, H=2, d=d, N=128, dtype=torch.float32,
+                           pos=pos, time=time, seed=640 + d)
+    small = inputs.subset(small, [0, 1, 3, 4, 7, 10, 12])
+    assert f32_waves(small, 4) == 4 and f32_waves(large, 2) == 2
+    off = large.seq_offsets.tolist()
+    rows = torch.cat([torch.arange(off[b], off[b + 1]) for b in (0, 1, 3, 4, 7, 10, 12)]).cuda()
+    a, b = run(small, backward=True), run(large, backward=True)
+    for n in FORWARD + BACKWARD:
+        assert torch.equal(a[n], b[n][rows]), n
