@@ -1757,11 +1757,20 @@ int persistent_grid(K kernel, size_t dyn, int64_t items, int dev, int block = TH
 // leave its third work-group no room on a CU (128 power-law sequences 60.6 ->
 // 56.5 us with per-item slots), while the backward, at two, prefers them all
 // (400 sequences of up to 300 tokens 407 us against 424).
-// The dK/dV items at d=128 fill a CU with two work-groups and DKV128_ROOM bytes
+// The dK/dV items at d=128 fill a CU with two work-groups and dkv128_room bytes
 // each beside their tiles: one slot and the d_time histogram.
 enum class Pass { FWD, DQ, DKV };
 constexpr size_t ALL_HEADS_BUDGET = 32 * 1024;
-constexpr int64_t DKV128_ROOM = 80 * 1024 - 74784;
+constexpr int64_t LDS_BYTES = 160 * 1024;            // of a compute unit
+int64_t dkv128_room(const Problem &p) {
+  static_assert(sizeof(DkvSmem<128, true, true>) == sizeof(DkvSmem<128, true, false>) &&
+                sizeof(DkvSmem<128, false, true>) == sizeof(DkvSmem<128, false, false>));
+  return LDS_BYTES / 2 - (int64_t)(p.has_pos ? sizeof(DkvSmem<128, true, false>)
+                                             : sizeof(DkvSmem<128, false, false>));
+}
+// a slot of 128 buckets and two counters for each fit
+static_assert(LDS_BYTES / 2 - sizeof(DkvSmem<128, true, false>) >=
+              sizeof(float) * (KTAB + 128) + 2 * sizeof(double) * 128);
 bool all_heads(const Problem &p, Pass pass) {
   const size_t budget = p.d != 64          ? ALL_HEADS_BUDGET / 4
                         : pass == Pass::FWD ? ALL_HEADS_BUDGET / 2
@@ -1776,19 +1785,20 @@ size_t slots_bytes(const Problem &p, Pass pass) { return slot_bytes(p, all_heads
 size_t q_dyn_bytes(const Problem &p) { return slots_bytes(p, Pass::DQ); }
 size_t fwd_dyn_bytes(const Problem &p) { return slots_bytes(p, Pass::FWD); }
 // The dK/dV work-group's d_time histogram: every head's, folded once at the
-// work-group's end, where those take at most KEEP_BYTES (so that they still have
-// two or more counters a bucket), else the item's head's with more counters,
+// work-group's end, where those take at most KEEP_BYTES (two or more counters a
+// bucket still, but one for a single head of over 230 buckets at d=128, which
+// would have no more by itself), else the item's head's with more counters,
 // folded at the item's end.  Backward (us), kept and per item: 150 sequences of
 // 15..615 tokens, 4 heads of 128, 128 buckets (4 KB) 331 and 325; 400 of up to
 // 300, 2 heads of 64, 64 buckets (1 KB) 122.4 and 124.3; 2 heads of 128, 32
-// buckets 334.8 and 337.0.  At d=128 the counters fit DKV128_ROOM: 309 sequences
+// buckets 334.8 and 337.0.  At d=128 the counters fit dkv128_room: 309 sequences
 // of 15..615, 2 heads, took 445 with one work-group a CU, 335 with two.
 struct TimeHist { int cs, hs, n; };
 constexpr int64_t KEEP_BYTES = 2048;
 TimeHist time_hist(const Problem &p) {
   int64_t room = HIST_BYTES;
   if (p.d != 64)
-    room = std::min(room, DKV128_ROOM - (int64_t)slots_bytes(p, Pass::DKV));
+    room = std::min(room, dkv128_room(p) - (int64_t)slots_bytes(p, Pass::DKV));
   const bool keep = p.H * (int64_t)p.nb * 8 <= std::min(room, KEEP_BYTES);
   TimeHist t;
   t.n = keep ? p.H * p.nb : p.nb;
