@@ -766,7 +766,7 @@ attn_fwd_kernel(KParams P) {
       // pop the item after next one step before the last (as late as the
       // atomic's latency allows), older than this step's loads, so that no
       // wait for them also waits for the atomic
-      if (kt == (kt_end > 0 ? kt_end - 1 : 0) && tid == 0)
+      if (!DIRECT && kt == (kt_end > 0 ? kt_end - 1 : 0) && tid == 0)
         nxt2 = atomicAdd(P.pop, 1);     // + 2 gridDim.x where it is published
       if (!last) {         // stream the next key tile into the other buffer
         const int k_valid = it.len - (kt + 1) * TILE;
@@ -875,7 +875,7 @@ attn_fwd_kernel(KParams P) {
     // the popped index goes out through the epilogue's barriers; sum the
     // two key halves of each query tile in the last tile's buffer, store O
     // (bf16)
-    if (tid == 0) sm.next[item_no & 1] = nxt2 + 2 * (int)gridDim.x;
+    if (!DIRECT && tid == 0) sm.next[item_no & 1] = nxt2 + 2 * (int)gridDim.x;
 #pragma unroll
     for (int sq = 0; sq < QT; ++sq) {
       const int tq = QT * it.tile + sq;
@@ -1860,22 +1860,16 @@ KParams make_params(const AttnArgs &a, int32_t *pop, const WorkEntry *list) {
 template <int D, bool POS, bool TIME>
 constexpr auto attn_fwd_direct = attn_fwd_kernel<D, POS, TIME, 1, true>;
 
-// As HSTU_DISPATCH, with a fourth template argument QT (forward items of QT
-// query tiles).
-#define HSTU_DISPATCH_Q(KERNEL, D, POS, TIME, QT, ...)                              \
-  do {                                                                              \
-    if (D == 64) {                                                                  \
-      if (POS && TIME) { auto kfn = KERNEL<64, true, true, QT>; __VA_ARGS__; }      \
-      else if (POS) { auto kfn = KERNEL<64, true, false, QT>; __VA_ARGS__; }       \
-      else if (TIME) { auto kfn = KERNEL<64, false, true, QT>; __VA_ARGS__; }      \
-      else { auto kfn = KERNEL<64, false, false, QT>; __VA_ARGS__; }               \
-    } else {                                                                        \
-      if (POS && TIME) { auto kfn = KERNEL<128, true, true, QT>; __VA_ARGS__; }     \
-      else if (POS) { auto kfn = KERNEL<128, true, false, QT>; __VA_ARGS__; }      \
-      else if (TIME) { auto kfn = KERNEL<128, false, true, QT>; __VA_ARGS__; }     \
-      else { auto kfn = KERNEL<128, false, false, QT>; __VA_ARGS__; }              \
-    }                                                                               \
-  } while (0)
+template <int D, bool POS, bool TIME>
+constexpr auto attn_fwd_single = attn_fwd_kernel<D, POS, TIME, 1>;
+
+// The forward's items of two query tiles (d = 64 only, see fwd_pairs).
+auto attn_fwd_pair(const Problem &p) {
+  return p.has_pos ? (p.has_time ? attn_fwd_kernel<64, true, true, 2>
+                                 : attn_fwd_kernel<64, true, false, 2>)
+                   : (p.has_time ? attn_fwd_kernel<64, false, true, 2>
+                                 : attn_fwd_kernel<64, false, false, 2>);
+}
 
 // As HSTU_DISPATCH, for the kernels that accumulate the table gradients
 // (a fourth template argument: the deterministic fixed-point mode).
@@ -1934,14 +1928,12 @@ bool fwd_pairs(const Problem &p) {
 }
 
 int attn_fwd_grid(const Problem &p, int dev) {
-  int grid = 1;
+  const int64_t items = p.max_entries * p.H;
   if (fwd_pairs(p))
-    HSTU_DISPATCH_Q(attn_fwd_kernel, p.d, p.has_pos, p.has_time, 2,
-                    grid = persistent_grid(kfn, fwd_dyn_bytes(p), p.max_entries * p.H, dev,
-                                           2 * THREADS));
-  else
-    HSTU_DISPATCH_Q(attn_fwd_kernel, p.d, p.has_pos, p.has_time, 1,
-                    grid = persistent_grid(kfn, fwd_dyn_bytes(p), p.max_entries * p.H, dev));
+    return persistent_grid(attn_fwd_pair(p), fwd_dyn_bytes(p), items, dev, 2 * THREADS);
+  int grid = 1;
+  HSTU_DISPATCH(attn_fwd_single, p.d, p.has_pos, p.has_time,
+                grid = persistent_grid(kfn, fwd_dyn_bytes(p), items, dev));
   return grid;
 }
 
@@ -1971,7 +1963,6 @@ hipError_t launch_attn_fwd_bf16(const AttnArgs &a, void *o, bool direct, hipStre
   const Problem &p = a.p;
   if (direct) {
     KParams P = make_params(a, nullptr, nullptr);
-    P.pop = (int32_t *)(ws + a.L.ctrl) + CTRL_POP_FWD;    // popped once, not used
     P.out0 = (u16 *)o;
     P.off = a.off;
     P.T = p.T;
@@ -1988,11 +1979,10 @@ hipError_t launch_attn_fwd_bf16(const AttnArgs &a, void *o, bool direct, hipStre
   P.all_heads = all_heads(p, Pass::FWD) ? 1 : 0;
   const int grid = attn_fwd_grid(p, current_dev());
   if (pairs)
-    HSTU_DISPATCH_Q(attn_fwd_kernel, p.d, p.has_pos, p.has_time, 2,
-                    hipLaunchKernelGGL(kfn, dim3(grid), dim3(2 * THREADS), fwd_dyn_bytes(p), s, P));
+    hipLaunchKernelGGL(attn_fwd_pair(p), dim3(grid), dim3(2 * THREADS), fwd_dyn_bytes(p), s, P);
   else
-    HSTU_DISPATCH_Q(attn_fwd_kernel, p.d, p.has_pos, p.has_time, 1,
-                    hipLaunchKernelGGL(kfn, dim3(grid), dim3(THREADS), fwd_dyn_bytes(p), s, P));
+    HSTU_DISPATCH(attn_fwd_single, p.d, p.has_pos, p.has_time,
+                  hipLaunchKernelGGL(kfn, dim3(grid), dim3(THREADS), fwd_dyn_bytes(p), s, P));
   return hipGetLastError();
 }
 
