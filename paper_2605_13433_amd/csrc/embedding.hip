@@ -296,7 +296,8 @@ __global__ void __launch_bounds__(ET) emb_chunk_kernel(BwdArgs<K> a) {
   __shared__ int64_t s_row[MAX_CPB * CHUNK];           // element offset of the gradient row
   __shared__ uint32_t s_rank[MAX_CPB * CHUNK];         // distinct rows up to the position
   __shared__ uint32_t s_sum[ET / 64], s_wave[MAX_CPB * CHUNK / 64], s_state[MAX_CPB];
-  __shared__ float s_part[2][ET * NE];                 // cpb > 1: chunk g's pieces at g D
+  __shared__ __attribute__((aligned(16))) float s_part[2][ET * NE];   // cpb > 1: chunk g's
+                                                                     // pieces at g D
   const int tid = threadIdx.x, lane = tid & 63;
   const int g = tid / tpc, lt = tid % tpc;
   const int64_t chunk0 = (int64_t)blockIdx.x * cpb, chunk = chunk0 + g;
