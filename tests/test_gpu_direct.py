@@ -22,8 +22,7 @@ def _gpu():
 CASES = [
     # lengths, H, d, dtype: one entry; empty sequences around and between;
     # 63/64/65-row tails; the second 64 sequences of a wave; the last batch
-    # size taken directly and the first that is not; long enough on average
-    # for the scheduler's two-tile items
+    # size taken directly and the first that is not; few long ones
     ([1], 1, 64, torch.bfloat16),
     ([0, 0, 63, 0, 64, 65, 0, 129, 0], 2, 128, torch.bfloat16),
     ([(37 * b) % 90 for b in range(128)], 2, 64, torch.bfloat16),
@@ -31,6 +30,12 @@ CASES = [
     ([700, 3, 513], 2, 64, torch.bfloat16),
     ([0, 33, 64, 0, 65, 1], 2, 32, torch.float32),
     ([(29 * b) % 70 for b in range(100)], 1, 64, torch.float32),
+    # past the short kernels' line (2 items of 32 rows to an entry and head, three
+    # work-groups a compute unit at d=64 and one at d=128), and still direct: the
+    # tile kernels' one-tile items, beside one- and two-tile ones from the lists
+    ([90] * 110, 2, 128, torch.bfloat16),
+    ([130, 1, 0, 64] * 30, 3, 64, torch.bfloat16),
+    ([700] * 20 + [3, 513], 2, 64, torch.bfloat16),
 ]
 
 

@@ -63,10 +63,10 @@ def test_small_bf16(case):
     compare(w, got, oracle.fwd_workload(w), oracle.bwd_workload(w))
 
 
-# Mean length >= 256 tokens: the bf16 d=64 forward takes items of two query
-# tiles (the pair list; the d=128 cases run the same batches through the
-# one-tile items).  Odd and even tile counts (the last pair of an odd count
-# has no upper tile), one-tile and empty sequences, L = max_len.
+# Mean length >= 256 tokens, odd and even tile counts, one-tile and empty
+# sequences, L = max_len.  These batches are small enough for the short kernels;
+# the two-tile items that larger ones of such lengths take are in
+# test_gpu_tile_paths.py.
 PAIRS = [
     ([256, 320, 64, 65, 1, 767, 0, 639], 2, 64, 768, True, True),
     ([256, 320, 64, 65, 1, 767, 0, 639], 2, 128, 768, True, True),

@@ -70,7 +70,7 @@ CASES = [
     ("bf16 d64 pos+time", [70, 1, 130, 0, 64, 200], 2, 64, 256, torch.bfloat16),
     ("bf16 d128 pos+time", [150, 33, 1, 260], 2, 128, 320, torch.bfloat16),
     ("fp32 d64 pos+time", [40, 1, 75], 2, 64, 96, torch.float32),
-    # mean length >= 256: the d=64 forward's items of two query tiles
+    # mean length >= 256 (two-tile items past the short kernels: test_gpu_tile_paths.py)
     ("bf16 d64 pairs", [256, 320, 64, 65, 1, 767, 0, 639], 2, 64, 768, torch.bfloat16),
 ]
 
