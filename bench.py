@@ -40,8 +40,8 @@ PEAK_FP32_TFLOPS = 157.3           # MI355X fp32 vector
 PEAK_HBM_GBS = 8000.0              # MI355X HBM3E
 RIDGE = PEAK_BF16_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9)   # flop per byte
 
-KERNEL_SOURCES = ["device.h", "internal.h", "sched_impl.h", "sched.hip", "attn_bf16.hip",
-                  "attn_f32.hip", "norm.hip", "api.cpp"]
+KERNEL_SOURCES = ["device.h", "internal.h", "attn_common.h", "sched_impl.h", "sched.hip",
+                  "attn_bf16.hip", "attn_short.hip", "attn_f32.hip", "norm.hip", "api.cpp"]
 
 
 def _code_only(text: str) -> str:
