@@ -504,7 +504,7 @@ SHORT_KERNEL = {"attn_fwd_kernel": "attn_fwd", "attn_bwd_kernel": "attn_bwd",
 
 def counters_commands(workload: int):
     run = (f"python3 bench.py --workload {workload} --steps 5 --warmup 2 --no-cpu-baseline "
-           f"--cold-steps 0 --no-configs")
+           f"--cold-steps 0 --no-configs --no-embedding")
     return {
         "trace": f"rocprofv3 --kernel-trace --stats --output-format csv -d <dir> -o trace -- {run}",
         "sq_a": f"rocprofv3 --pmc {' '.join(SQ_PASS_A)} --output-format csv -d <dir> -o sqa -- {run}",
