@@ -25,9 +25,16 @@
 // rows c_row(r, 0) and c_row(r, 1).
 // Measured against one thread per row on the vector ALUs (48 power-law
 // sequences of 16..512 tokens, H = 4, d = 64, both biases): forward 582 ->
-// 32 us, backward 7796 -> 103 us (6886 of them were one double atomic on a
-// table entry per pair), error against 64 bits 4.3e-7 -> 3.6e-7; four
-// sequences of up to 64 tokens, H = 2, d = 32: forward 27 -> 6.4 us.
+// 30 us, backward 7796 -> 108 us (6886 of them were one double atomic on a
+// table entry per pair); four sequences of up to 64 tokens, H = 2, d = 32:
+// forward 27 -> 6.5 us.  Error against 64 bits (relative, the whole output), nine
+// batches of 37 to 432 sequences, d = 32, 64 and 128, two draws each: o 0.64 to
+// 0.94 times the former kernels', dv 0.66 to 0.96, y and du 0.75 to 1.02, dq and
+// dk 0.7 to 1.2 (a few short sequences' LayerNorm decides those); on the batch
+// above o 3.0e-7 -> 2.1e-7, dk 4.2e-7 -> 3.6e-7.
+// What is left beside the chain of tiles: the d = 64 backward spills registers
+// (the 256-register cap), and every score gathers its two biases from memory.
+// Matrix cores busy 16% of the cycles, the vector ALUs 13%.
 #include <algorithm>
 
 #include "internal.h"

@@ -757,15 +757,16 @@ auto pick_bwd(bool pos, bool time) {
 // the chain here is the shorter one.  Beyond it the items queue, each with its
 // exposed start, where the tile kernels' persistent work-groups hide theirs.
 // Tile kernels / these, both biases, H = 4 where not said (us):
-//   forward d = 64:  B=1 L=502 20.3 / 16.7, B=1 L=812 26.0 / 19.7, B=1 L=8022 H=2
-//     148 / 109, B=12 L<=250 16.3 / 15.6, B=4 L<=1630 43.8 / 37.1; past it B=12
-//     L<=1000 34.5 / 40.5
-//   forward d = 128: B=1 L=502 25.3 / 22.5, B=4 L<=512 23.7 / 21.3; past it B=12
-//     L<=250 19.5 / 20.5
-//   backward d = 64: B=1 L=90 27.7 / 20.8, B=1 L=812 62.5 / 40.5, B=4 L<=512 45.2 /
-//     32.7, B=32 L<=100 H=2 28.8 / 24.3; past it B=32 L<=300 46.4 / 62.3
-//   backward d = 128: B=1 L=502 49.9 / 38.2, B=4 L<=512 H=2 46.5 / 37.0; past it
-//     B=12 L<=250 39.9 / 54.7
+//   forward d = 64:  B=1 L=502 16.2 / 11.7, B=1 L=812 21.8 / 15.3, B=1 L=8022 H=2
+//     148 / 110, B=12 L<=250 10.7 / 8.9, B=4 L<=1630 28.5 / 24.4; past it B=12
+//     L<=1000 26.7 / 27.9, B=32 L<=300 15.3 / 17.9
+//   forward d = 128: B=1 L=502 19.9 / 16.5, B=4 L<=512 18.4 / 16.0, B=1 L=2000 H=1
+//     53.8 / 37.7; past it B=12 L<=250 14.3 / 14.0
+//   backward d = 64: B=1 L=90 23.3 / 16.3, B=1 L=812 57.9 / 39.1, B=4 L<=512 42.6 /
+//     28.4, B=32 L<=100 H=2 23.4 / 19.2; past it B=32 L<=300 38.0 / 51.1, B=12 L<=1000
+//     68.5 / 78.5
+//   backward d = 128: B=1 L=502 45.3 / 33.9, B=1 L=2000 H=1 123 / 85, B=4 L<=512 H=2
+//     44.1 / 32.3; past it B=12 L<=250 34.3 / 38.6
 static int64_t short_items(const Problem &p) { return 2 * p.max_entries * p.H; }
 
 bool fwd_short(const Problem &p, int dev) {

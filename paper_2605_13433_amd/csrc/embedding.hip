@@ -24,11 +24,14 @@
 // parallel instead of by one serial loop.
 //
 // Measured on 8 tables of 2^22 .. 2^7 rows, 77 971 ids each, D = 128, fp32:
-// backward 265 -> 215 us.  The chunk pass (131 us) reads 319 MB of gradients
-// just after the forward wrote as much: plain loads of those bytes take 66 us
-// from clean memory and 111-130 us behind 1 GiB of dirty lines, in sorted or
-// sequential order alike.  Sort passes 25 -> 15 us each, fix-up 29 -> 10 us, the
-// rows' numbering 17 -> 8 us.  Non-temporal forward stores changed nothing.
+// backward 265 -> 218 us where the forward ran just before it (chunk pass 133,
+// keys 6, sort with its clears 62, rows' numbering 8, fix-up 9.5), 187 us by
+// itself (chunk pass 104, the others the same).  The chunk pass reads 319 MB of
+// gradients: plain loads of those bytes take 66 us from clean memory and
+// 111-130 us behind 1 GiB of dirty lines, in sorted or sequential order alike.
+// Sort passes 25 -> 15 us each, fix-up 29 -> 9, the rows' numbering 17 -> 8.
+// Non-temporal forward stores changed nothing.  bf16, backward by itself: 130
+// (chunk pass 49).
 #include <rocprim/device/device_radix_sort.hpp>
 
 #include <algorithm>
